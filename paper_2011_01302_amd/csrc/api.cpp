@@ -91,6 +91,7 @@ void ios_graph_destroy(ios_graph *g) {
     if (op.d_dw_row) (void)hipFree(op.d_dw_row);
     if (op.d_pw_row) (void)hipFree(op.d_pw_row);
     if (op.d_wg) (void)hipFree(op.d_wg);
+    if (op.d_wsp) (void)hipFree(op.d_wsp);
     if (op.d_pw_pipe) (void)hipFree(op.d_pw_pipe);
     if (op.d_pw_line) (void)hipFree(op.d_pw_line);
   }
@@ -277,6 +278,9 @@ int ios_schedule_from_stages(ios_graph *g, int32_t n_stages, const int32_t *stag
 // fills the GPU by itself; inside a stage other operators share the CUs, so
 // larger tiles can pay off there.
 static constexpr double kStageTileSlack = 0.02;
+// A value whose stage is slower than the best by more than this in a few
+// launches is not measured in full.
+static constexpr double kStageScreen = 1.15;
 
 int ios_schedule_tune_tiles(ios_graph *g, ios_schedule_t *q, const ios_sched_opts *opts,
                             int64_t *cost_ns) {
@@ -308,6 +312,11 @@ int ios_schedule_tune_tiles(ios_graph *g, ios_schedule_t *q, const ios_sched_opt
         }
         const int strat = q->strategies[k];
         auto measure = [&] { return profile_stage(g, ops, strat, o.warmup, o.reps, o.repeats); };
+        // whether a value is worth measuring in full: a few launches first
+        auto worth = [&](int64_t best) {
+          if (o.reps * o.repeats < 8) return true;
+          return (double)profile_stage(g, ops, strat, 1, std::max(2, o.reps / 2), 1) <= (double)best * kStageScreen;
+        };
         for (int op : ops) g->ops[op].xcd_lg = -1;
         int64_t best = measure();
         // the XCD run length of the stage's tile order (see the stage kernel):
@@ -373,6 +382,7 @@ int ios_schedule_tune_tiles(ios_graph *g, ios_schedule_t *q, const ios_sched_opt
               if (!change) continue;
               for (size_t i = 0; i < kn.ops.size(); ++i)
                 val(kn.ops[i], kn.sep) = ok(kn.ops[i], kn.sep, v) ? v : keep[i];
+              if (!worth(best)) continue;
               const int64_t ns = measure();
               if ((double)ns < (double)best * (1.0 - kStageTileSlack)) {
                 best = ns;

@@ -13,18 +13,18 @@
 //     op's buffer, which stands in for the split operator (Sec. 3).
 // GenerateStage measures a stage by launching it repeatedly between HIP
 // events (Sec. 4.1).
-#include <tuple>
-#include <set>
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <numeric>
 
 #include "ios_internal.h"
 
 namespace ios {
 
-int choose_conv_tile(int64_t M, int N, bool pipe_ok);
+int choose_conv_tile(int64_t M, int N, const std::function<bool(int)> &ok);
 
 static int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 static int round_up(int a, int b) { return (a + b - 1) / b * b; }
@@ -104,8 +104,19 @@ static int choose_xcd_runs(const std::vector<DevOp> &ops, const std::vector<int3
   const int n = start.back();
   double best = -1.0;
   int best_lg = 0;
+  // (XCD, M-tile) and (XCD, N-tile) of every op, numbered through
+  std::vector<int> a0, b0;
+  int na = 0, nb = 0;
+  for (const DevOp &d : ops) {
+    a0.push_back(na);
+    b0.push_back(nb);
+    na += kXcdsHost * d.tiles_m;
+    nb += kXcdsHost * d.tiles_n;
+  }
+  std::vector<char> a_seen(na), b_seen(nb);
   for (int lg : {0, 2, 4}) {
-    std::set<std::tuple<int, int, int>> a_seen, b_seen;
+    std::fill(a_seen.begin(), a_seen.end(), 0);
+    std::fill(b_seen.begin(), b_seen.end(), 0);
     double bytes = 0.0;
     for (int b = 0; b < grid; ++b)
       for (int base = 0; base + b < n; base += grid) {
@@ -114,8 +125,14 @@ static int choose_xcd_runs(const std::vector<DevOp> &ops, const std::vector<int3
         const DevOp &d = ops[i];
         if (d.kind != DK_CONV || t - start[i] >= d.n_tiles) continue;   // padding between op ranges
         const int ti = t - start[i], tm = ti / d.tiles_n, tn = ti % d.tiles_n;
-        if (a_seen.insert({i, b & 7, tm}).second) bytes += 4.0 * tile_bm(d.tcfg) * d.CinP * d.kh;
-        if (b_seen.insert({i, b & 7, tn}).second)
+        char &sa = a_seen[a0[i] + (b & 7) * d.tiles_m + tm], &sb = b_seen[b0[i] + (b & 7) * d.tiles_n + tn];
+        if (!sa) bytes += 4.0 * tile_bm(d.tcfg) * d.CinP * d.kh;
+        sa = 1;
+        if (sb) continue;
+        sb = 1;
+        if (tile_is_split(d.tcfg))
+          bytes += 6.0 * tile_bn(d.tcfg) * round_up(d.Cin, kSplitCK) * d.kh * d.kw;
+        else
           bytes += 4.0 * tile_bn(d.tcfg) * (tile_is_pipe(d.tcfg) ? (double)kPipeKB : 16.0) * d.NG;
       }
     if (best < 0.0 || bytes < best) {
@@ -130,6 +147,9 @@ static int choose_xcd_runs(const std::vector<DevOp> &ops, const std::vector<int3
 double tile_work(const DevOp &d) {
   switch (d.kind) {
     case DK_CONV: {
+      // a bf16 product counts a sixteenth of an fp32 one, and there are six of them
+      if (tile_is_split(d.tcfg))
+        return (double)tile_bm(d.tcfg) * tile_bn(d.tcfg) * round_up(d.Cin, kSplitCK) * d.kh * d.kw * (6.0 / 16.0) / kWaves;
       if (tile_is_pipe(d.tcfg)) return (double)tile_bm(d.tcfg) * tile_bn(d.tcfg) * kPipeKB * d.NG / kWaves;
       TileShape s = tile_shape(d.tcfg);
       return (double)tile_bm(d.tcfg) * tile_bn(d.tcfg) * 16.0 * d.NG / s.wk;
@@ -145,8 +165,9 @@ double tile_work(const DevOp &d) {
   }
 }
 
+// `n_copy` > 0: only that many elements are copied.
 template <class T>
-void grow_upload(T **dptr, size_t *cap, const std::vector<T> &v, bool reuse) {
+void grow_upload(T **dptr, size_t *cap, const std::vector<T> &v, bool reuse, size_t n_copy = 0) {
   size_t n = std::max<size_t>(v.size(), 1);
   if (!reuse || *cap < n) {
     if (reuse && *dptr) (void)hipFree(*dptr);
@@ -154,7 +175,7 @@ void grow_upload(T **dptr, size_t *cap, const std::vector<T> &v, bool reuse) {
     if (reuse) *cap = n;
   }
   if (!v.empty())
-    hip_check(hipMemcpy(*dptr, v.data(), sizeof(T) * v.size(), hipMemcpyHostToDevice),
+    hip_check(hipMemcpy(*dptr, v.data(), sizeof(T) * (n_copy ? n_copy : v.size()), hipMemcpyHostToDevice),
               "hipMemcpy(stage)");
 }
 
@@ -181,11 +202,108 @@ void pack_conv_weights(const float *w, int cout, int cin, int kh, int kw, std::v
 void pack_conv_pipe(const float *w, int cout, int cin, int kh, int kw, std::vector<float> &out, int *nkb) {
   const int taps = kh * kw, K = taps * cin, ldw = round_up(cout, 128), nb = cdiv(K, kPipeKB);
   out.assign((size_t)nb * kPipeKB * ldw, 0.f);
-  for (int n = 0; n < cout; ++n)
+  for (int n0 = 0; n0 < cout; n0 += 16)                // 16 output channels at a time: whole cache lines written
     for (int c = 0; c < cin; ++c)
-      for (int t = 0; t < taps; ++t) out[((size_t)t * cin + c) * ldw + n] = w[((size_t)n * cin + c) * taps + t];
+      for (int t = 0; t < taps; ++t)
+        for (int n = n0; n < std::min(cout, n0 + 16); ++n)
+          out[((size_t)t * cin + c) * ldw + n] = w[((size_t)n * cin + c) * taps + t];
   *nkb = nb;
 }
+
+bool split_weights_ok(const float *w, size_t n) {
+  float m = 0.f;
+  for (size_t i = 0; i < n; ++i) {
+    if (!std::isfinite(w[i])) return false;
+    m = std::max(m, std::fabs(w[i]));
+  }
+  return m == 0.f || (m <= 0x1p40f && m >= 0x1p-30f);
+}
+
+SplitGeom split_geometry(int cfg, int N, int cin, int cout, int H, int W, int Ho, int Wo, int kh, int kw, int sh,
+                         int sw) {
+  SplitGeom g;
+  const SplitShape s = split_shape(cfg);
+  const int bm = tile_bm(cfg), bn = tile_bn(cfg), taps = kh * kw;
+  g.nch = cdiv(cin, kSplitCK);
+  g.gather = taps == 1;
+  if (g.gather) {
+    g.np = bm;
+    g.w2 = g.hv = 1;
+  } else {
+    // output rows (img, oh) that bm consecutive pixels touch at most, image
+    // boundaries among them, and the virtual rows those need
+    const int64_t rows = std::min<int64_t>((int64_t)N * Ho, (Wo - 1 + bm - 1) / Wo + 1);
+    const int64_t cross = rows < 2 ? 0 : std::min<int64_t>(N - 1, 1 + (rows - 2) / Ho);
+    const int64_t v = (rows - 1) * sh + kh + cross * std::max(0, kh - sh);
+    g.w2 = (Wo - 1) * sw + kw;
+    g.hv = (Ho - 1) * sh + kh;
+    if (v * g.w2 * kSplitPosBytes > kSplitLdsAlone || (int64_t)N * g.hv >= (1 << 30)) return g;
+    g.np = (int)(v * g.w2);
+  }
+  g.pp = round_up(g.np, 32);
+  // Sub-chunks per round: as few rounds as the LDS allows (a round costs a
+  // load and barrier round trip of about kRound cycles that only another
+  // workgroup of the CU hides), but no k-steps of a round for a part of the wk
+  // waves only.  Half a CU's LDS where the launch has more workgroups than
+  // CUs, so that two of them share one.
+  constexpr int kRound = 2400, kStep = 400;
+  const int64_t tiles = (int64_t)cdiv((int64_t)N * Ho * Wo, bm) * cdiv(cout, bn);
+  const int red = s.wk > 1 ? s.wk * bm * bn * 4 : 0, tail = kSplitTail + bn * 4;
+  const int per = g.pp * kSplitPosBytes;
+  int cap = tiles > 256 ? kSplitLdsShared : kSplitLdsAlone;
+  if (std::max(red, per) + tail > cap) cap = kSplitLdsAlone;
+  if (std::max(red, per) + tail > cap) return g;
+  int64_t best = -1;
+  for (int sc = 1; sc <= g.nch && sc * per + tail <= cap; ++sc) {
+    const int full = g.nch / sc, rest = g.nch % sc, rounds = full + (rest > 0);
+    const int64_t steps = (int64_t)full * cdiv(sc * taps, s.wk) + cdiv(rest * taps, s.wk);
+    const int64_t cost = (int64_t)rounds * kRound + steps * kStep * s.pb;
+    if (best < 0 || cost < best) {
+      best = cost;
+      g.sc = sc;
+    }
+  }
+  g.body = std::max(red, g.sc * per);
+  g.lds = g.body + tail;
+  if ((int64_t)cdiv(cout, 32) * g.nch * taps * kSplitWords * 4 >= ((int64_t)1 << 31)) return g;
+  g.ok = true;
+  return g;
+}
+
+namespace {
+// The split tile's descriptor, from the operator's final fields and sizes.
+void set_split(DevOp &d, const float *w, const float *w32, bool raw) {
+  const SplitShape s = split_shape(d.tcfg);
+  const SplitGeom g = split_geometry(d.tcfg, d.N, d.Cin, d.Cout, d.H, d.W, d.Ho, d.Wo, d.kh, d.kw, d.sh, d.sw);
+  if (!g.ok) fail(IOS_E_UNSUPPORTED, "conv split tile does not apply");
+  SplitDesc &p = d.sp;
+  p.lwm = 31 - __builtin_clz((unsigned)s.wm);
+  p.lwn = 31 - __builtin_clz((unsigned)s.wn);
+  p.wk = s.wk;
+  p.sc = g.sc; p.nch = g.nch; p.np = g.np; p.pp = g.pp;
+  p.w2 = g.w2; p.hv = g.hv; p.gather = g.gather; p.tail = g.body;
+  p.Ho = d.Ho; p.Wo = d.Wo; p.howo = d.Ho * d.Wo; p.M = d.N * p.howo;
+  p.N = d.N; p.H = d.H; p.W = d.W; p.Cin = d.Cin; p.Cout = d.Cout;
+  p.kh = d.kh; p.kw = d.kw; p.taps = d.kh * d.kw;
+  p.sh = d.sh; p.sw = d.sw; p.ph = d.ph; p.pw = d.pw;
+  p.in_slot = d.in_slot[0]; p.in_coff = d.in_coff[0]; p.in_ctot = d.in_ctot[0]; p.in_bytes = d.in_bytes[0];
+  p.pre_relu = d.pre_relu; p.post_relu = d.post_relu;
+  p.n_routes = d.n_routes; p.route_slot = d.route_slot[0];
+  p.route_coff = d.route_coff[0]; p.route_ctot = d.route_ctot[0];
+  p.tiles_n = cdiv(d.Cout, tile_bn(d.tcfg));
+  p.w_bytes = (int32_t)((size_t)cdiv(d.Cout, 32) * g.nch * p.taps * kSplitWords * sizeof(float));
+  p.fd_tn = make_fdiv((uint32_t)p.tiles_n);
+  p.fd_wo = make_fdiv((uint32_t)d.Wo);
+  p.fd_ho = make_fdiv((uint32_t)d.Ho);
+  p.fd_howo = make_fdiv((uint32_t)p.howo);
+  p.fd_pp = make_fdiv((uint32_t)g.pp);
+  p.fd_taps = make_fdiv((uint32_t)p.taps);
+  p.fd_kw = make_fdiv((uint32_t)d.kw);
+  p.fd_w2 = make_fdiv((uint32_t)g.w2);
+  p.fd_hv = make_fdiv((uint32_t)g.hv);
+  p.w = w; p.bias = d.bias; p.w32 = w32; p.raw = raw;
+}
+}  // namespace
 
 SepGeom sep_geometry(int tile, int cin, int cout, int w, int ho, int wo, int kh, int kw) {
   SepGeom g;
@@ -237,6 +355,8 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
   SlotMap sm;
   std::vector<DevOp> dops;
   std::vector<float> mw, mb;
+  size_t wsp_off = 0;            // merge on a split tile: the place of the bf16 parts in mw
+  bool merge_held = false;       // the profiler's stage holds this merge's packed weights already
   if (strategy == IOS_MERGE) {
     if (!stage_mergeable(g, ops)) fail(IOS_E_NOT_MERGEABLE, "stage cannot be merged");
     if ((int)ops.size() > kMaxRoutes) fail(IOS_E_UNSUPPORTED, "merge of more than 8 convs");
@@ -255,53 +375,87 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
     d.pw = o0.d.pad_w + (KW - o0.d.kw) / 2;
     d.Cout = total;
     d.CinP = round_up(o0.cin, 4);
-    // merged kernel [total][cin][KH][KW]: each op's kernel centred, stacked
-    // along output channels in ascending unit id (the concat order)
-    std::vector<float> wm((size_t)total * o0.cin * KH * KW, 0.f);
-    mb.assign(round_up(total, 16), 0.f);
+    // output ranges in ascending unit id (the concat order)
     int n0 = 0;
     d.n_routes = (int)ops.size();
     for (size_t r = 0; r < ops.size(); ++r) {
-      const Op &o = g->ops[ops[r]];
-      int dh = (KH - o.d.kh) / 2, dwc = (KW - o.d.kw) / 2;
-      for (int co = 0; co < o.d.cout; ++co) {
-        mb[n0 + co] = o.b[co];
-        for (int ci = 0; ci < o.cin; ++ci)
-          for (int u = 0; u < o.d.kh; ++u)
-            for (int v = 0; v < o.d.kw; ++v)
-              wm[(((size_t)(n0 + co) * o0.cin + ci) * KH + u + dh) * KW + v + dwc] =
-                  o.w[(((size_t)co * o.cin + ci) * o.d.kh + u) * o.d.kw + v];
-      }
-      set_route(g, d, (int)r, n0, o.out, sm);
-      n0 += o.d.cout;
+      set_route(g, d, (int)r, n0, g->ops[ops[r]].out, sm);
+      n0 += g->ops[ops[r]].d.cout;
     }
     // tile shape: forced one, else the measured choice of the largest conv
     int largest = ops[0];
     for (int i : ops)
       if (op_flops(g, g->ops[i]) > op_flops(g, g->ops[largest])) largest = i;
-    const bool pipe_ok = pipe_conv_ok(o0.cin, KH * KW, o0.d.pre_relu);
-    d.tcfg = std::getenv("IOS_CONV_TILE") ? choose_conv_tile((int64_t)g->batch * o0.ho * o0.wo, total, pipe_ok)
+    bool split_ok = true;
+    for (int i : ops) split_ok &= g->ops[i].split_ok;
+    const auto merged_ok = [&](int v) {
+      if (tile_is_pipe(v)) return pipe_conv_ok(o0.cin, KH * KW, o0.d.pre_relu);
+      if (!tile_is_split(v)) return true;
+      return split_ok && split_geometry(v, g->batch, o0.cin, total, o0.h, o0.wd, o0.ho, o0.wo, KH, KW, d.sh, d.sw).ok;
+    };
+    d.tcfg = std::getenv("IOS_CONV_TILE") ? choose_conv_tile((int64_t)g->batch * o0.ho * o0.wo, total, merged_ok)
                                            : g->ops[largest].tcfg;
-    if (tile_is_pipe(d.tcfg) && !pipe_ok) d.tcfg = TC_16x32_K8;   // the merged window has more than 32 taps
+    if (!merged_ok(d.tcfg)) d.tcfg = TC_16x32_K8;   // the merged window has more than 32 taps, or does not fit
+    const int layout = tile_is_split(d.tcfg) ? 2 : tile_is_pipe(d.tcfg) ? 1 : 0;
     int nb = 0;
-    if (tile_is_pipe(d.tcfg)) {
-      pack_conv_pipe(wm.data(), total, o0.cin, KH, KW, mw, &d.NG);
-      d.pipe_ldw = round_up(total, 128);
-      d.Npad = round_up(total, 16);
+    merge_held = reuse && g->prof_merge_ops == ops && g->prof_merge_layout == layout;
+    if (merge_held) {
+      d.NG = g->prof_merge_ng;
+      nb = g->prof_merge_nb;
+      wsp_off = g->prof_merge_wsp;
     } else {
-      pack_conv_weights(wm.data(), total, o0.cin, KH, KW, mw, &d.NG, &nb);
-      d.Npad = nb * 16;
+      // merged kernel [total][cin][KH][KW]: each op's kernel centred, stacked
+      // along output channels
+      std::vector<float> wm((size_t)total * o0.cin * KH * KW, 0.f);
+      mb.assign(round_up(total, 16), 0.f);
+      for (size_t r = 0; r < ops.size(); ++r) {
+        const Op &o = g->ops[ops[r]];
+        const int dh = (KH - o.d.kh) / 2, dwc = (KW - o.d.kw) / 2, f0 = d.route_n0[r];
+        for (int co = 0; co < o.d.cout; ++co) {
+          mb[f0 + co] = o.b[co];
+          for (int ci = 0; ci < o.cin; ++ci)
+            for (int u = 0; u < o.d.kh; ++u)
+              for (int v = 0; v < o.d.kw; ++v)
+                wm[(((size_t)(f0 + co) * o0.cin + ci) * KH + u + dh) * KW + v + dwc] =
+                    o.w[(((size_t)co * o.cin + ci) * o.d.kh + u) * o.d.kw + v];
+        }
+      }
+      if (layout == 2) {
+        // the fp32 weights as they are, room for the bf16 parts behind them
+        wsp_off = (wm.size() + 63) & ~(size_t)63;
+        mw = std::move(wm);
+        mw.resize(wsp_off + split_words(total, o0.cin, KH, KW));
+        nb = round_up(total, 16) / 16;
+      } else if (layout == 1) {
+        pack_conv_pipe(wm.data(), total, o0.cin, KH, KW, mw, &d.NG);
+        nb = round_up(total, 16) / 16;
+      } else {
+        pack_conv_weights(wm.data(), total, o0.cin, KH, KW, mw, &d.NG, &nb);
+      }
+    }
+    d.Npad = nb * 16;
+    if (layout == 1) d.pipe_ldw = round_up(total, 128);
+    d.w_bytes = (int32_t)((layout == 1 ? (size_t)d.NG * kPipeKB * d.pipe_ldw : (size_t)nb * d.NG * 256) * sizeof(float));
+    if (reuse) {                 // (prof_merge_ops is set once they are uploaded)
+      if (!merge_held) g->prof_merge_ops.clear();
+      g->prof_merge_layout = layout;
+      g->prof_merge_ng = d.NG;
+      g->prof_merge_nb = nb;
+      g->prof_merge_wsp = wsp_off;
     }
     set_inputs(g, o0, d, sm);
     d.route_n0[d.n_routes] = total;
-    d.w_bytes = (int32_t)(mw.size() * sizeof(float));
     dops.push_back(d);
   } else if (strategy == IOS_CONCURRENT) {
     // a pipelined conv tile's LDS rings beside the stage table must fit a
     // workgroup; in a stage of very many operators such a conv takes 16x32
     const int n_ops = (int)ops.size();
-    const bool pipe_fits = (kSlotWords + ((4 + n_ops + 1 + 3) & ~3) + n_ops * kDevOpWords) * (int)sizeof(int32_t) +
-                               pipe_lds_bytes(TC_W128x64) <= kMaxLdsBytes;
+    const int table_bytes = (kSlotWords + ((4 + n_ops + 1 + 3) & ~3) + n_ops * kDevOpWords) * (int)sizeof(int32_t);
+    const bool pipe_fits = table_bytes + pipe_lds_bytes(TC_W128x64) <= kMaxLdsBytes;
+    // a split tile runs in the variant without SEPCONV tiles, and its patch
+    // must fit beside the table too
+    bool any_sep = false;
+    for (int i : ops) any_sep |= g->ops[i].d.kind == IOS_SEPCONV;
     for (size_t i = 0; i < ops.size(); ++i) {
       const Op &o = g->ops[ops[i]];
       DevOp d{};
@@ -316,7 +470,14 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
           d.kind = DK_CONV; d.tcfg = o.tcfg; d.CinP = o.CinP; d.Npad = o.Npad;
           d.bias = o.d_bias;
           if (tile_is_pipe(d.tcfg) && !pipe_fits) d.tcfg = TC_16x32_K8;
-          if (tile_is_pipe(d.tcfg)) {
+          if (tile_is_split(d.tcfg)) {
+            const SplitGeom sg = split_geometry(d.tcfg, d.N, d.Cin, d.Cout, d.H, d.W, d.Ho, d.Wo, d.kh, d.kw, d.sh, d.sw);
+            if (any_sep || !sg.ok || table_bytes + sg.lds > kMaxLdsBytes) d.tcfg = TC_16x32_K8;
+          }
+          if (tile_is_split(d.tcfg)) {
+            d.NG = o.NG;
+            set_split(d, o.d_wsp, o.d_wpk, false);
+          } else if (tile_is_pipe(d.tcfg)) {
             d.NG = o.pipe_nkb;
             d.pipe_ldw = round_up(o.d.cout, 128);
             d.wpk = o.d_wg;
@@ -519,7 +680,7 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
   for (int i = 0; i < n; ++i) pos[order[i]] = i;
   std::vector<DevOp> sorted;
   std::vector<int32_t> start{0};
-  bool persistent = false, big_conv = false, has_sep = false, has_row = false, has_pipe = false;
+  bool persistent = false, big_conv = false, has_sep = false, has_row = false, has_pipe = false, has_split = false;
   for (const DevOp &d : dops) persistent |= d.n_deps > 0;
   int lds = 0;
   for (size_t k = 0; k < order.size(); ++k) {
@@ -535,8 +696,9 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
     int end = start.back() + d.n_tiles;
     if (!persistent && k + 1 < order.size()) end = round_up(end, kXcdsHost);
     start.push_back(end);
-    big_conv |= d.kind == DK_CONV && !tile_is_light(d.tcfg) && !tile_is_pipe(d.tcfg);
+    big_conv |= d.kind == DK_CONV && !tile_is_light(d.tcfg) && !tile_is_pipe(d.tcfg) && !tile_is_split(d.tcfg);
     has_pipe |= d.kind == DK_CONV && tile_is_pipe(d.tcfg);
+    has_split |= d.kind == DK_CONV && tile_is_split(d.tcfg);
     has_sep |= d.kind == DK_SEP && (d.sep_row == 0 || d.sep_row == 2);
     has_row |= d.kind == DK_SEP && (d.sep_row == 1 || d.sep_row == 3);
     lds = std::max(lds, op_lds_bytes(d));
@@ -550,11 +712,12 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
   cs->lds_bytes = (kSlotWords + table_words) * (int)sizeof(int32_t) + lds;
   if (cs->lds_bytes > kMaxLdsBytes) fail(IOS_E_UNSUPPORTED, "stage needs more LDS than a workgroup has");
   cs->persistent = persistent;
-  const int kinds = (int)has_sep + (int)has_row + (int)has_pipe;
+  const int kinds = (int)has_sep + (int)has_row + (int)has_pipe + (int)has_split;
   cs->variant = big_conv || kinds > 1 ? KV_FULL
                 : has_sep            ? KV_SEP
                 : has_row            ? KV_SEPROW
                 : has_pipe           ? KV_PIPE
+                : has_split          ? KV_SPLIT
                                      : KV_LIGHT;
   cs->grid = start.back();
   if (persistent) {
@@ -567,10 +730,17 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
   if (!mw.empty()) {
     size_t *wc = reuse ? &g->prof_w_cap : nullptr, *bc = reuse ? &g->prof_b_cap : nullptr;
     size_t dummy_w = 0, dummy_b = 0;
-    grow_upload(&cs->d_mw, wc ? wc : &dummy_w, mw, reuse);
+    if (reuse) g->prof_merge_ops.clear();              // until both are uploaded
+    grow_upload(&cs->d_mw, wc ? wc : &dummy_w, mw, reuse, wsp_off);
+    if (wsp_off)
+      pack_conv_split(cs->d_mw, cs->ops[0].Cout, cs->ops[0].Cin, cs->ops[0].kh, cs->ops[0].kw, cs->d_mw + wsp_off, g->stream);
     grow_upload(&cs->d_mb, bc ? bc : &dummy_b, mb, reuse);
+    if (reuse) g->prof_merge_ops = ops;
+  }
+  if (!mw.empty() || merge_held) {
     cs->ops[0].wpk = cs->d_mw;
     cs->ops[0].bias = cs->d_mb;
+    if (tile_is_split(cs->ops[0].tcfg)) set_split(cs->ops[0], cs->d_mw + wsp_off, cs->d_mw, true);
   }
   cs->table.assign(table_words, 0);
   cs->table[0] = n;

@@ -355,8 +355,11 @@ static T *upload(const std::vector<T> &v) {
 }
 
 bool conv_tile_ok(const Op &op, int cfg) {
-  return cfg >= 0 && cfg < TC_COUNT &&
-         (!tile_is_pipe(cfg) || pipe_conv_ok(op.cin, op.d.kh * op.d.kw, op.d.pre_relu));
+  if (cfg < 0 || cfg >= TC_COUNT) return false;
+  if (tile_is_split(cfg))
+    return op.split_ok && split_geometry(cfg, op.batch, op.cin, op.d.cout, op.h, op.wd, op.ho, op.wo, op.d.kh,
+                                         op.d.kw, op.d.stride_h, op.d.stride_w).ok;
+  return !tile_is_pipe(cfg) || pipe_conv_ok(op.cin, op.d.kh * op.d.kw, op.d.pre_relu);
 }
 
 bool sep_tile_ok(const Op &op, int tile) {
@@ -384,19 +387,22 @@ static int choose_sep_tile(const Op &op) {
   return sep_tile_ok(op, v) ? v : 0;
 }
 
-// Conv tile shape for an M x N output before measurement.  IOS_CONV_TILE=<0..8>
+// Conv tile shape for an M x N output before measurement.  IOS_CONV_TILE=<0..19>
 // in the environment (read when a graph is finalized or a merged stage is
 // built) forces one shape for every conv, for tuning and for tests; a
-// pipelined shape is forced only on convs it applies to (pipe_ok).
-// Tuning: warm-up time before the first measurement, and the fraction of the
-// fastest time within which a conv tile shape with fewer workgroups is taken.
+// pipelined or split shape is forced only on convs it applies to (ok).
+// Tuning: warm-up time before the first measurement, the fraction of the
+// fastest time within which a conv tile shape with fewer workgroups is taken,
+// and how far from the fastest of a first round of a few launches a shape is
+// measured in full.
 constexpr int kTuneWarmMs = 50;
 constexpr double kTuneSlack = 0.03;
+constexpr double kTuneScreen = 1.5;
 
-int choose_conv_tile(int64_t M, int N, bool pipe_ok) {
+int choose_conv_tile(int64_t M, int N, const std::function<bool(int)> &ok) {
   if (const char *e = std::getenv("IOS_CONV_TILE")) {
     int v = std::atoi(e);
-    if (v >= 0 && v < TC_COUNT && (pipe_ok || !tile_is_pipe(v))) return v;
+    if (v >= 0 && v < TC_COUNT && ok(v)) return v;
   }
   int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64);
   int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32);
@@ -418,8 +424,10 @@ void finalize_graph(ios_graph *g) {
     if (op.d.kind == IOS_CONV) {
       op.CinP = round_up(op.cin, 4);
       op.Npad = round_up(op.d.cout, 16);
+      op.batch = g->batch;
+      op.split_ok = split_weights_ok(op.w.data(), op.w.size());
       op.tcfg = choose_conv_tile((int64_t)g->batch * op.ho * op.wo, op.d.cout,
-                                 pipe_conv_ok(op.cin, op.d.kh * op.d.kw, op.d.pre_relu));
+                                 [&](int v) { return conv_tile_ok(op, v); });
     } else if (op.d.kind == IOS_SEPCONV) {
       op.CinP = round_up(op.cin, 16);
       op.Npad = round_up(op.d.cout, 16);
@@ -461,6 +469,13 @@ void ensure_device(ios_graph *g) {
       std::vector<float> wg;
       pack_conv_pipe(op.w.data(), op.d.cout, op.cin, op.d.kh, op.d.kw, wg, &op.pipe_nkb);
       op.d_wg = upload(wg);
+      if (op.split_ok) {
+        float *raw = upload(op.w);
+        const hipError_t e = hipMalloc(&op.d_wsp, split_words(op.d.cout, op.cin, op.d.kh, op.d.kw) * sizeof(float));
+        if (e == hipSuccess) pack_conv_split(raw, op.d.cout, op.cin, op.d.kh, op.d.kw, op.d_wsp, g->stream);
+        (void)hipFree(raw);
+        hip_check(e, "hipMalloc(weights)");
+      }
     } else if (op.d.kind == IOS_SEPCONV) {
       // depthwise [CinP][kh * kw] (channels past cin zero); pointwise packed
       // like a 1x1 conv's weights (groups of 4 k-steps = 16 input channels)
@@ -548,13 +563,22 @@ void ensure_device(ios_graph *g) {
       Op &op = g->ops[oi];
       if (op.d.kind != IOS_CONV) continue;
       const int64_t M = (int64_t)g->batch * op.ho * op.wo;
-      std::vector<std::pair<int64_t, int>> meas;   // (ns, cfg)
+      // a few launches of every shape, then the full measurement of those
+      // within kTuneScreen of the fastest
+      std::vector<std::pair<int64_t, int>> quick, meas;   // (ns, cfg)
+      int64_t fastest = INT64_MAX;
       for (int cfg = 0; cfg < TC_COUNT; ++cfg) {
         if (!conv_tile_ok(op, cfg)) continue;
         op.tcfg = cfg;
-        meas.push_back({profile_stage(g, {oi}, IOS_CONCURRENT, 3, 20, 5), cfg});
+        quick.push_back({profile_stage(g, {oi}, IOS_CONCURRENT, 2, 3, 1), cfg});
+        fastest = std::min(fastest, quick.back().first);
       }
-      int64_t fastest = INT64_MAX;
+      for (auto &m : quick) {
+        if ((double)m.first > (double)fastest * kTuneScreen) continue;
+        op.tcfg = m.second;
+        meas.push_back({profile_stage(g, {oi}, IOS_CONCURRENT, 3, 20, 5), m.second});
+      }
+      fastest = INT64_MAX;
       for (auto &m : meas) fastest = std::min(fastest, m.first);
       auto tiles = [&](int cfg) {
         return ((M + tile_bm(cfg) - 1) / tile_bm(cfg)) * ((op.d.cout + tile_bn(cfg) - 1) / tile_bn(cfg));

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <map>
 #include <memory>
@@ -61,7 +62,17 @@ enum TileCfg : int32_t {
   TC_W128x64 = 9,
   TC_W256x32 = 10,
   TC_W64x128 = 11,
-  TC_COUNT = 12,
+  // split tiles (see the stage kernel): pixels x channels, each operand split
+  // into three bf16 parts, products on v_mfma_f32_32x32x16_bf16
+  TC_S256x64 = 12,
+  TC_S128x128 = 13,
+  TC_S128x64 = 14,
+  TC_S64x64 = 15,
+  TC_S128x32 = 16,
+  TC_S64x32 = 17,
+  TC_S32x64 = 18,
+  TC_S32x32 = 19,
+  TC_COUNT = 20,
 };
 static_assert(TC_COUNT == IOS_CONV_TILE_SHAPES, "tile shapes of the public API");
 
@@ -78,19 +89,39 @@ inline TileShape tile_shape(int cfg) {
 }
 // Tile shapes the light kernel variant contains (one 16-pixel block per wave).
 inline bool tile_is_light(int cfg) { return cfg == TC_16x16_K8 || cfg == TC_16x32_K8; }
-inline bool tile_is_pipe(int cfg) { return cfg >= TC_P128x64 && cfg < TC_COUNT; }
-inline bool tile_is_wave_ring(int cfg) { return cfg >= TC_W128x64 && cfg < TC_COUNT; }
+inline bool tile_is_pipe(int cfg) { return cfg >= TC_P128x64 && cfg < TC_S256x64; }
+inline bool tile_is_wave_ring(int cfg) { return cfg >= TC_W128x64 && cfg < TC_S256x64; }
+inline bool tile_is_split(int cfg) { return cfg >= TC_S256x64 && cfg < TC_COUNT; }
+__host__ __device__ inline bool tile_is_split_pb2(int cfg) { return cfg >= TC_S256x64 && cfg <= TC_S128x32; }
+// split tiles: 8 waves arranged wm (pixels) x wn (channels) x wk (reduction),
+// each with pb blocks of 32 pixels x one block of 32 channels
+struct SplitShape { int pb, wm, wn, wk; };
+inline SplitShape split_shape(int cfg) {
+  switch (cfg) {
+    case TC_S256x64: return {2, 4, 2, 1};
+    case TC_S128x128: return {2, 2, 4, 1};
+    case TC_S128x64: return {2, 2, 2, 2};
+    case TC_S64x64: return {2, 1, 2, 4};
+    case TC_S128x32: return {2, 2, 1, 4};
+    case TC_S64x32: return {1, 2, 1, 4};
+    case TC_S32x64: return {1, 1, 2, 4};
+    default: return {1, 1, 1, 8};
+  }
+}
+static_assert(TC_S128x32 == TC_S64x64 + 1 && TC_S64x32 == TC_S128x32 + 1, "the tiles with two pixel blocks per wave come first");
 // pipelined tiles: waves along pixels (and kWaves / that along channels)
 inline int pipe_wm(int cfg) {
   const int k = tile_is_wave_ring(cfg) ? cfg - TC_W128x64 : cfg - TC_P128x64;
   return k == 0 ? 4 : k == 1 ? 8 : 2;
 }
 inline int tile_bm(int cfg) {
+  if (tile_is_split(cfg)) return 32 * split_shape(cfg).pb * split_shape(cfg).wm;
   if (tile_is_pipe(cfg)) return 32 * pipe_wm(cfg);
   TileShape s = tile_shape(cfg);
   return 16 * s.fm * s.wm;
 }
 inline int tile_bn(int cfg) {
+  if (tile_is_split(cfg)) return 32 * split_shape(cfg).wn;
   if (tile_is_pipe(cfg)) return 32 * (kWaves / pipe_wm(cfg));
   TileShape s = tile_shape(cfg);
   return 16 * s.fn * s.wn;
@@ -116,6 +147,31 @@ inline int pipe_lds_bytes(int cfg) {
 inline bool pipe_conv_ok(int cin, int taps, int pre_relu) {
   return cin > 0 && cin % kPipeKB == 0 && taps <= 32 && !pre_relu;
 }
+
+// Split tiles: the input channels are reduced in sub-chunks of kSplitCK = 16;
+// a round stages sc of them in LDS, each as three bf16 parts x two halves of 8
+// channels x pp positions of 16 bytes (kSplitPosBytes per position).  A
+// position is a pixel of the patch of input rows that the tile's windows
+// read, over the whole batch: virtual row v = img hv + oh sh + u (hv rows per
+// image, the padding included) and column c = ow sw + v, w2 columns, row v_lo
+// of the tile's first pixel first; 1 x 1 windows take one position per output
+// pixel (gather).  ok = false: the patch does not fit.
+constexpr int kSplitCK = 16;
+constexpr int kSplitPosBytes = 96;
+constexpr int kSplitTail = 256;              // LDS bytes of the range flags, before the biases
+constexpr int kSplitLdsShared = 74 * 1024;   // two workgroups per CU, the stage tables included
+constexpr int kSplitLdsAlone = 140 * 1024;   // one workgroup per CU (the stage table comes on top)
+constexpr int kSplitWords = 768;             // words of packed weights per (32 channels, 16 input channels, tap)
+struct SplitGeom {
+  bool ok = false, gather = false;
+  int sc = 0, nch = 0, np = 0, pp = 0, w2 = 0, hv = 0, body = 0, lds = 0;
+};
+SplitGeom split_geometry(int cfg, int N, int cin, int cout, int H, int W, int Ho, int Wo, int kh, int kw, int sh,
+                         int sw);
+// Whether every weight is finite and in the range where the three bf16 parts
+// of both operands and the partial sums keep every bit that matters (see the
+// stage kernel's range check of the activations).
+bool split_weights_ok(const float *w, size_t n);
 
 // SEPCONV tile: BM = 16 << tile consecutive output pixels of one image x
 // sep_nbt blocks of 16 output channels; the input channels are reduced in
@@ -286,6 +342,31 @@ inline FDiv make_fdiv(uint32_t d) {
   return {(uint32_t)(((1ull << 32) * ((1ull << l) - d)) / d + 1), l};
 }
 
+// What a split tile reads of its operator, one word for each lane of a wave
+// (the fields as in DevOp and SplitGeom).
+struct SplitDesc {
+  int32_t lwm, lwn, wk, sc;    // SplitShape (wm, wn as log2), sub-chunks per round
+  int32_t nch, np, pp, raw;    // sub-chunks in all, positions, rounded up to 32; layout of w32
+  int32_t w2, hv, gather, tail;// patch row length, virtual rows per image, LDS byte offset of flags and biases
+  int32_t M, Ho, Wo, howo;     // output pixels of the batch
+  int32_t N, H, W, Cin;
+  int32_t Cout, kh, kw, taps;
+  int32_t sh, sw, ph, pw;
+  int32_t in_slot, in_coff, in_ctot, in_bytes;
+  int32_t pre_relu, post_relu, n_routes, route_slot;
+  int32_t route_coff, route_ctot, tiles_n, w_bytes;
+  FDiv fd_tn, fd_wo;
+  FDiv fd_ho, fd_howo;
+  FDiv fd_pp, fd_taps;
+  FDiv fd_kw, fd_w2;
+  FDiv fd_hv;
+  const void *w;               // pack_conv_split
+  const float *bias;           // [Npad], at least Cout floats
+  const float *w32;            // the weights in fp32, for values out of range: raw [cout][cin][kh][kw], else
+                               // packed (pack_conv_weights; CinP, NG)
+};
+static_assert(sizeof(SplitDesc) == 256, "one word per lane");
+
 // One operator of a compiled stage, as the kernel sees it.
 struct alignas(16) DevOp {
   int32_t kind, tcfg;
@@ -341,6 +422,7 @@ struct alignas(16) DevOp {
   const float *wpk;            // CONV: see pack_conv_weights; SEP: the pointwise weights packed the same way
   const float *bias;           // [Npad]
   const float *dw;             // SEP: depthwise [round16(Cin)][kh * kw], channels past Cin zero
+  SplitDesc sp;                // CONV split tile
 };
 
 // A compiled stage's table in device memory (int32 words): a header
@@ -366,7 +448,7 @@ struct StageArgs {
 // Launch one stage (defined in the HIP translation unit).
 // Kernel variant of a stage (see the stage kernel): the smallest one that
 // contains every tile kind the stage uses.
-enum KernelVariant { KV_LIGHT = 0, KV_SEP = 1, KV_FULL = 2, KV_SEPROW = 3, KV_PIPE = 4, KV_COUNT = 5 };
+enum KernelVariant { KV_LIGHT = 0, KV_SEP = 1, KV_FULL = 2, KV_SEPROW = 3, KV_PIPE = 4, KV_SPLIT = 5, KV_COUNT = 6 };
 // table / table_words: the compiled stage's table (a multiple of 4 words);
 // lds_bytes: the dynamic LDS, slots and table included.
 hipError_t launch_stage(const int32_t *table, int table_words, const StageArgs &args, bool persistent,
@@ -406,6 +488,7 @@ struct Op {
   int unit = -1;                 // index among schedule units, -1 for views
   int block = -1, local = -1;    // block and bit inside the block
   int cin = 0, h = 0, wd = 0, ho = 0, wo = 0;
+  int batch = 1;                 // CONV: the graph's batch, set at finalize
   // device copies (units only)
   int CinP = 0, Npad = 0, NG = 0, tcfg = TC_16x32_K8;
   int sep_tile = 1;              // SEPCONV: tile choice (16 << sep_tile output pixels per tile)
@@ -414,6 +497,8 @@ struct Op {
   float *d_pw_pipe = nullptr;    // SEPCONV GEMM tile: pointwise weights packed like a pipelined 1x1 conv's
   float *d_dw_row = nullptr, *d_pw_row = nullptr;   // SEPCONV row tile: [CinP4][kkp(K)], [CinP4][Npad]
   float *d_pw_line = nullptr;    // SEPCONV line tile: pointwise [ceil(Cout/32)][ceil(Cin/2)][64] (A operands)
+  float *d_wsp = nullptr;        // CONV, split tiles: see pack_conv_split
+  bool split_ok = false;         // CONV: split tiles may run it (split_weights_ok)
   float *d_wg = nullptr;         // CONV, pipelined tiles: [nkb * kPipeKB][round128(Cout)]
   int pipe_nkb = 0;
 };
@@ -461,6 +546,11 @@ struct ios_graph {
   // the stage profiler's compiled stage (reused by every candidate stage)
   ios::CompiledStage prof_stage;
   size_t prof_ops_cap = 0, prof_ctr_cap = 0, prof_w_cap = 0, prof_b_cap = 0;
+  // the merge stage whose packed weights prof_stage holds (empty: none), their
+  // layout (0 direct, 1 pipelined, 2 split) and what packing them returned
+  std::vector<int> prof_merge_ops;
+  int prof_merge_layout = -1, prof_merge_ng = 0, prof_merge_nb = 0;
+  size_t prof_merge_wsp = 0;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   // ios_run_noalloc: byte offset of each intermediate buffer in the scratch
   // array (counters first), and the bytes the graph needs there
@@ -494,6 +584,16 @@ void set_last_error_text(const char *msg);
 // counters); the counter block's size, which the intermediates follow
 void noalloc_setup(int device);
 size_t noalloc_counter_bytes();
+
+// pack.hip: conv weights for the split tiles, from w[cout][cin][kh][kw] in
+// device memory: per block of 32 output channels, chunk of 16 input channels
+// and tap, three parts (w = w1 + w2 + w3, each the bf16 nearest to what the
+// parts before it leave) of 64 lanes x 8 bf16, lane l holding output channel
+// l % 32, input channels 8 (l / 32) .. + 7: the A operands of
+// v_mfma_f32_32x32x16_bf16.  Zero past cin and cout; split_words floats.
+// Returns when the packing is done.
+size_t split_words(int cout, int cin, int kh, int kw);
+void pack_conv_split(const float *d_w, int cout, int cin, int kh, int kw, float *d_out, hipStream_t stream);
 
 // graph.cpp
 int unit_op_of_tensor(const ios_graph *g, int tensor_id);   // op index or throws

@@ -14,7 +14,7 @@
 //   DK_POOL_* / DK_ADD / DK_MEAN   elementwise tiles on the vector ALUs.
 // Operators of one group run in order (Sec. 3: a group is executed
 // sequentially): a consumer tile waits until every tile of its producers has
-// finished (see ios_stage_kernel for why the waits always end).
+// finished (see stage_body for why the waits always end).
 #pragma once
 #include <utility>
 
@@ -641,6 +641,340 @@ __device__ __forceinline__ void conv_wave_tile(const Slots &sl, const DevOp &op,
       }
     }
   }
+}
+
+// max(v, 0) in one instruction (median of v, 0 and +inf)
+__device__ __forceinline__ float relu1(float v) { return __builtin_amdgcn_fmed3f(v, 0.f, __builtin_inff()); }
+
+// ------------------------------------------------------------------ split conv
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ floatx16 mfma32x32x16(uintx4 a, uintx4 b, floatx16 c) {
+  // D[32x32] += A[32x16] * B[16x32] in bf16, sums in fp32; lane l supplies
+  // A[l%32][8 (l/32) .. + 7] and B[8 (l/32) .. + 7][l%32]; D as mfma32x32x2.
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                 0, 0);
+}
+
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{a, b}, bf16x2));
+}
+
+// Eight values as three bf16 parts each, v = p[0] + p[1] + p[2] but for at
+// most 2^-27 of it (every part is the nearest bf16 to what is left of v).
+__device__ __forceinline__ void split3(const float (&v)[8], uintx4 (&p)[3]) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float a = v[2 * i], b = v[2 * i + 1];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+      const uint32_t h = bf16_pair(a, b);
+      p[s][i] = h;
+      a -= __builtin_bit_cast(float, h << 16);
+      b -= __builtin_bit_cast(float, h & 0xFFFF0000u);
+    }
+  }
+}
+
+// The range of magnitudes in which the products of the bf16 parts and their
+// sums lose nothing (with the weights' range, see split_weights_ok: no part
+// below the smallest normal number that matters, no sum past the largest), as
+// magnitude bits.  A tile whose largest input lies outside, or that holds an
+// infinity or a NaN, is computed in fp32 instead.
+constexpr uint32_t kSplitHi = (127u + 70u) << 23, kSplitLo = (127u - 40u) << 23;
+
+// Implicit-GEMM convolution tile on the bf16 matrix cores, in fp32 accuracy:
+// every operand is split into three bf16 parts (x = x1 + x2 + x3, 24 bits),
+// and the six products x_i w_j with i + j <= 4 are summed in fp32, which
+// leaves out terms below 2^-26 of a product.  v_mfma_f32_32x32x16_bf16 does
+// 16 times the multiply-adds per cycle of v_mfma_f32_32x32x2_f32, so a
+// product costs 6/16 of an fp32 one.  x1 w1 has an accumulator of its own, the
+// five small products another (added at the end): the large one is rounded
+// once per 16 channels and tap.  The 2-norm error against 64 bits is below the
+// fp32 tiles' at every size measured.
+//
+// BM = 32 PB WM output pixels (flattened over the batch) x BN = 32 WN output
+// channels; wave (wm, wn, wk) owns PB blocks of 32 pixels, one of 32 channels
+// and every wk-th k-step (16 channels of one tap).  Per round the workgroup
+// stages sp_sc sub-chunks of 16 channels of the patch of input rows that its
+// windows read (SplitGeom): each value is loaded and split once and then read
+// by every tap and every wave, as one 16-byte LDS read per part.  A lane of
+// the staging loads holds 8 channels of one position (8 loads, consecutive
+// lanes on consecutive columns) and writes three 16-byte words, conflict-free;
+// two workgroups share a CU, one multiplying while the other stages.  The
+// weights come from memory as they are packed, 3 loads of 16 bytes per lane
+// and k-step for 6 PB products, one k-step ahead.
+//
+// A load's per-lane offset is its position's (or kOOB), its scalar offset the
+// channel's, which the range check does not cover: channels past Cin take
+// kOOB.
+template <int PB, bool COH>
+__device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op, const SplitDesc &o, int t, float *lds) {
+  constexpr int SB = PB == 1 ? 3 : 2;                  // staging items loaded at once
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lwm = o.lwm, lwn = o.lwn, WK = o.wk, WN = 1 << lwn;
+  const int wm = wave & ((1 << lwm) - 1), wn = (wave >> lwm) & (WN - 1), wk = wave >> (lwm + lwn);
+  const int BM = (32 * PB) << lwm, BN = 32 << lwn;
+  const int tm = fdiv(t, o.fd_tn), tn = t - tm * o.tiles_n;
+  const int Wo = o.Wo, Ho = o.Ho, howo = o.howo, M = o.M, H = o.H, W = o.W, Cin = o.Cin;
+  const int m0 = tm * BM, n0 = tn * BN, nch = o.nch, SC = o.sc, PP = o.pp, np = o.np;
+  const int taps = o.taps, kw = o.kw, W2 = o.w2, hv = o.hv, hw4 = H * W * 4;
+  const bool gather = o.gather;
+  char *lb = (char *)lds;
+  uint32_t *flags = (uint32_t *)(lb + o.tail);
+  float *biasl = (float *)(lb + o.tail + kSplitTail);
+  const __amdgpu_buffer_rsrc_t xr = rsrc(sl[o.in_slot], o.in_bytes);
+  const __amdgpu_buffer_rsrc_t wr = rsrc(o.w, o.w_bytes);
+
+  if (tid < 3) flags[tid] = 0;
+  const float bias = tid < BN ? bld(rsrc(o.bias, o.Cout * 4), (n0 + tid) * 4, 0) : 0.f;
+
+  // this wave's weights: block nb of 32 channels (clamped: columns past Cout
+  // are never stored); its k-steps of a round are ks = wk, wk + WK, ... of the
+  // round's sub-chunks x taps
+  const int nb = min(tn * WN + wn, ((o.Cout + 31) >> 5) - 1);
+  const int alane = lane * 16, arow = nb * nch * taps, alast = (nb + 1) * nch * taps - 1;
+  auto weights = [&](int c0, int ks, uintx4 (&a)[3]) {
+    const int soff = min(arow + c0 * taps + ks, alast) * (kSplitWords * 4);
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      a[k] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(wr, alane + k * 1024, soff, 0));
+  };
+  uintx4 a0[3], a1[3];
+
+  // virtual row of the tile's first pixel
+  int vlo = 0;
+  if (!gather) {
+    const int gr = fdiv(m0, o.fd_wo), img = fdiv(gr, o.fd_ho);
+    vlo = img * hv + (gr - img * Ho) * o.sh;
+  }
+  // byte offset of position p's pixel in channel 0 of the input's slice, or kOOB
+  auto source = [&](int p) {
+    int img, ih, iw;
+    bool ok;
+    if (gather) {
+      const int m = m0 + p, gr = fdiv(m, o.fd_wo);
+      img = fdiv(gr, o.fd_ho);
+      ih = (gr - img * Ho) * o.sh - o.ph;
+      iw = (m - gr * Wo) * o.sw - o.pw;
+      ok = p < np && m < M;
+    } else {
+      const int vr = fdiv(p, o.fd_w2), v = vlo + vr;
+      img = fdiv(v, o.fd_hv);
+      ih = v - img * hv - o.ph;
+      iw = p - vr * W2 - o.pw;
+      ok = p < np && img < o.N;
+    }
+    ok = ok && ih >= 0 && ih < H && iw >= 0 && iw < W;
+    return ok ? (((img * o.in_ctot + o.in_coff) * H + ih) * W + iw) * 4 : kOOB;
+  };
+  // Staging element e of a round: position e % PP of channels 8 hg .. + 7, hg =
+  // e / PP.  A wave takes elements 64 (wave + 8 i) + lane, SB such items at
+  // once.
+  const bool relu_in = o.pre_relu != 0;
+  int32_t pmax = 0;                                    // largest bits of the values staged by this thread, as
+  uint32_t umax = 0;                                   // signed and as unsigned numbers
+  auto stage = [&](int c0) {
+    const int n64 = min(SC, nch - c0) * 2 * PP, cb = c0 * kSplitCK;
+#pragma unroll 1
+    for (int e0 = wave * 64; e0 < n64; e0 += SB * kThreads) {   // uniform
+      float x[SB][8];
+      int hg[SB];
+#pragma unroll
+      for (int i = 0; i < SB; ++i) {
+        const int e = e0 + i * kThreads + lane;
+        hg[i] = fdiv(e, o.fd_pp);
+        // channels past Cin (in the last chunk) read 0: the per-lane offset leaves the buffer
+        const int left = e < n64 ? Cin - cb - hg[i] * 8 : 0, off = source(e - hg[i] * PP);
+        const int voff = off == kOOB ? kOOB : off + hg[i] * 8 * hw4;
+        if ((Cin & 7) == 0) {                          // uniform: all of an item's channels exist, or none
+          const int w = left > 0 ? voff : kOOB;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) x[i][j] = bld(xr, w, (cb + j) * hw4);
+        } else {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) x[i][j] = bld(xr, j < left ? voff : kOOB, (cb + j) * hw4);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < SB; ++i) {
+        const int e = e0 + i * kThreads + lane;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          if (relu_in) x[i][j] = relu1(x[i][j]);
+          pmax = max(pmax, __builtin_bit_cast(int32_t, x[i][j]));
+          umax = max(umax, __builtin_bit_cast(uint32_t, x[i][j]));
+        }
+        uintx4 q[3];
+        split3(x[i], q);
+        // part k of sub-chunk hg / 2, half hg % 2: 16 bytes per position
+        char *d = lb + (e + 4 * (hg[i] >> 1) * PP) * 16;
+        if (e < n64)
+#pragma unroll
+          for (int k = 0; k < 3; ++k) *(uintx4 *)(d + k * 2 * PP * 16) = q[k];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+
+  // this lane's pixels' positions
+  int bpos[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) {
+    const int ml = (wm * PB + pb) * 32 + l32, m = min(m0 + ml, M - 1);
+    int pos = ml;
+    if (!gather) {
+      const int gr = fdiv(m, o.fd_wo), ow = m - gr * Wo, img = fdiv(gr, o.fd_ho), oh = gr - img * Ho;
+      pos = (img * hv + oh * o.sh - vlo) * W2 + ow * o.sw;
+    }
+    bpos[pb] = (pos + half * PP) * 16;
+  }
+  floatx16 big[PB], sml[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) big[pb][i] = sml[pb][i] = 0.f;
+  auto step = [&](int ks, const uintx4 (&a)[3]) {
+    const int sc = fdiv(ks, o.fd_taps), tap = ks - sc * taps, u = fdiv(tap, o.fd_kw), v = tap - u * kw;
+    const char *b0 = lb + (sc * 6 * PP + u * W2 + v) * 16;
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+      uintx4 b[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) b[k] = *(const uintx4 *)(b0 + bpos[pb] + k * 2 * PP * 16);
+      big[pb] = mfma32x32x16(a[0], b[0], big[pb]);
+      sml[pb] = mfma32x32x16(a[0], b[1], sml[pb]);
+      sml[pb] = mfma32x32x16(a[1], b[0], sml[pb]);
+      sml[pb] = mfma32x32x16(a[1], b[1], sml[pb]);
+      sml[pb] = mfma32x32x16(a[0], b[2], sml[pb]);
+      sml[pb] = mfma32x32x16(a[2], b[0], sml[pb]);
+    }
+  };
+
+  for (int c0 = 0;;) {
+    if constexpr (PB == 1) weights(c0, wk, a0);        // the first weights in flight beside the patch
+    stage(c0);
+    if constexpr (PB != 1) weights(c0, wk, a0);
+    if (c0 == 0 && tid < BN) biasl[tid] = bias;
+    ring_barrier();
+    const int nks = min(SC, nch - c0) * taps;
+    for (int ks = wk; ks < nks;) {                     // one k-step of weights in flight
+      weights(c0, ks + WK, a1);
+      __builtin_amdgcn_sched_barrier(0);
+      step(ks, a0);
+      ks += WK;
+      if (ks >= nks) break;
+      weights(c0, ks + WK, a0);
+      __builtin_amdgcn_sched_barrier(0);
+      step(ks, a1);
+      ks += WK;
+    }
+    ring_barrier();                                    // the patch is no longer read
+    if ((c0 += SC) >= nch) break;
+  }
+
+  // the tile's range check
+  const uint32_t vmax = max((uint32_t)pmax, umax & 0x7FFFFFFFu);
+  if (__ballot(vmax >= kSplitHi) && lane == 0) atomicOr(&flags[0], 1u);
+  if (__ballot(vmax >= kSplitLo) && lane == 0) atomicOr(&flags[1], 1u);
+  if (__ballot(vmax != 0) && lane == 0) atomicOr(&flags[2], 1u);
+  float *red = lds;                                   // [wk][block][16][64]
+  const int nblk = (PB << lwm) << lwn;
+  if (WK > 1) {
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+      const int blk = ((wm * PB + pb) << lwn) + wn;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) red[((wk * nblk + blk) * 16 + i) * 64 + lane] = big[pb][i] + sml[pb][i];
+    }
+  }
+  ring_barrier();
+  const bool post = o.post_relu != 0;
+  // output n of image img, pixel pix (a merged conv has several destinations)
+  float *const out0 = sl[o.route_slot];
+  const int n_routes = o.n_routes, rctot = o.route_ctot, rcoff = o.route_coff;
+  auto dest = [&](int n, int img, int pix) {
+    if (n_routes == 1) return out0 + ((size_t)img * rctot + rcoff + n) * howo + pix;
+    int r = 0;
+    while (r + 1 < n_routes && n >= op.route_n0[r + 1]) ++r;
+    return sl.p[op.route_slot[r]] +
+           ((size_t)img * op.route_ctot[r] + op.route_coff[r] + (n - op.route_n0[r])) * howo + pix;
+  };
+  if (__builtin_amdgcn_readfirstlane((int)(flags[0] | (flags[2] & ~flags[1])))) {
+    // out of range: plain fp32, one thread per output
+    const int spt = U(op.CinP) >> 2, lbm = 31 - __builtin_clz(BM), NG = U(op.NG);
+    const float *xp = sl[o.in_slot];
+    for (int idx = tid; idx < BM * BN; idx += kThreads) {
+      const int m = m0 + (idx & (BM - 1)), nl = idx >> lbm, n = n0 + nl;
+      if (m >= M || n >= o.Cout) continue;
+      const int gr = fdiv(m, o.fd_wo), ow = m - gr * Wo, img = fdiv(gr, o.fd_ho), oh = gr - img * Ho;
+      float v = biasl[nl];
+      for (int u = 0; u < o.kh; ++u)
+        for (int q = 0; q < kw; ++q) {
+          const int ih = oh * o.sh - o.ph + u, iw = ow * o.sw - o.pw + q;
+          if (ih < 0 || ih >= H || iw < 0 || iw >= W) continue;
+          const float *px = xp + ((size_t)(img * o.in_ctot + o.in_coff) * H + ih) * W + iw;
+          for (int c = 0; c < Cin; ++c) {
+            const int tap = u * kw + q, ks = tap * spt + (c >> 2);
+            const float w = o.w32[o.raw ? ((size_t)n * Cin + c) * taps + tap
+                                        : (((size_t)(n >> 4) * NG + (ks >> 2)) * 64 + (c & 3) * 16 + (n & 15)) * 4 + (ks & 3)];
+            const float xv = px[(size_t)c * H * W];
+            v = fmaf(relu_in ? relu1(xv) : xv, w, v);
+          }
+        }
+      if (post) v = fmaxf(v, 0.f);
+      st<COH>(dest(n, img, m - img * howo), v);
+    }
+    return;
+  }
+  if (WK == 1) {
+    // element r of lane l is channel 8 (r/4) + 4 (l/32) + r%4 of its block, pixel l%32
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb) {
+      const int m = m0 + (wm * PB + pb) * 32 + l32;
+      if (m < M) {
+        const int img = fdiv(m, o.fd_howo), pix = m - img * howo;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int nl = wn * 32 + 8 * (r >> 2) + 4 * half + (r & 3), n = n0 + nl;
+          if (n < o.Cout) {
+            float v = big[pb][r] + sml[pb][r] + biasl[nl];
+            if (post) v = fmaxf(v, 0.f);
+            st<COH>(dest(n, img, pix), v);
+          }
+        }
+      }
+    }
+  } else {
+    for (int idx = tid; idx < nblk * 1024; idx += kThreads) {
+      const int blk = idx >> 10, i = (idx >> 6) & 15;
+      const int m = m0 + (blk >> lwn) * 32 + l32, nl = (blk & (WN - 1)) * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
+      const int n = n0 + nl;
+      if (m >= M || n >= o.Cout) continue;
+      float v = red[(blk * 16 + i) * 64 + lane];
+      for (int w = 1; w < WK; ++w) v += red[((w * nblk + blk) * 16 + i) * 64 + lane];
+      v += biasl[nl];
+      if (post) v = fmaxf(v, 0.f);
+      const int img = fdiv(m, o.fd_howo);
+      st<COH>(dest(n, img, m - img * howo), v);
+    }
+  }
+}
+
+// The descriptor of a split tile in scalar registers: word i from lane i (one
+// LDS read), as op_scalars.
+__device__ __forceinline__ SplitDesc split_desc(const SplitDesc &g) {
+  static_assert(sizeof(SplitDesc) == 256, "one word per lane");
+  const int v = ((const int *)&g)[threadIdx.x & 63];
+  int w[64];
+#pragma unroll
+  for (int i = 0; i < 64; ++i) w[i] = __builtin_amdgcn_readlane(v, i);
+  return __builtin_bit_cast(SplitDesc, w);
 }
 
 // ------------------------------------------------------------------ sepconv
@@ -1368,9 +1702,6 @@ __device__ __forceinline__ void wait_vmcnt_upto(int n) {
   }
 }
 
-// max(v, 0) in one instruction (median of v, 0 and +inf)
-__device__ __forceinline__ float relu1(float v) { return __builtin_amdgcn_fmed3f(v, 0.f, __builtin_inff()); }
-
 // Depthwise outputs of one (channel, strip of 2 output columns) for RG
 // output rows, from its staged plane (rows with the window's halo, columns
 // with a zero halo of pw on each side: no column test), the input ReLU
@@ -1733,6 +2064,7 @@ __device__ __forceinline__ void sum_tile(const Slots &sl, const DevOp &op, const
 //   KV_SEP     KV_LIGHT + staged SEPCONV tiles
 //   KV_SEPROW  KV_LIGHT + row SEPCONV tiles
 //   KV_PIPE    KV_LIGHT + pipelined conv tiles
+//   KV_SPLIT   KV_LIGHT + split conv tiles
 //   KV_FULL    every tile kind and conv tile shape
 // A conv tile with the input ReLU and the channel check resolved at compile
 // time (no branch between its loads and MFMAs).
@@ -1808,55 +2140,73 @@ __device__ __forceinline__ void run_tile(const Slots &sl, const DevOp &op, const
   }
 }
 
+// A tile's wait for the in-stage producers of its op (n_deps > 0).
+__device__ __forceinline__ void tile_wait(const StageArgs &a, const DevOp *ops, const DevOp &op, int n_deps) {
+  // one thread polls the producers' counters with coherent loads (its own
+  // copy of each, so the pollers of a stage spread over kCtrCopies memory
+  // channels), then invalidates stale cache lines once; the workgroup
+  // reads the producers' outputs only after that (barrier)
+  if (threadIdx.x == 0) {
+    int32_t *mine = a.ctr + 2 + kCtrStride * (blockIdx.x % kCtrCopies);
+    for (int k = 0; k < n_deps; ++k) {
+      const int d = op.dep[k];
+      const int need = ops[d].n_tiles;
+      int spins = 0;
+      while (__hip_atomic_load(&mine[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) {
+        __builtin_amdgcn_s_sleep(4);
+        if (++spins > a.spin_limit) {
+          __hip_atomic_fetch_or(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          break;
+        }
+      }
+    }
+    // drop lines of this CU / XCD that may predate the producers' stores
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  }
+  __syncthreads();
+}
+
+// A tile's signal to the ops of the stage that read its outputs.
+__device__ __forceinline__ void tile_signal(const StageArgs &a, int opi) {
+  // The tile's outputs were written with agent-coherent stores.  Every wave
+  // waits until its stores have been performed, then one wave moves every
+  // copy of the op's counter; a consumer reads the outputs only after
+  // seeing the final count and invalidating its stale lines, so it sees
+  // every value.  This orders like a release/acquire pair without a
+  // per-tile L2 writeback.
+  __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+  __syncthreads();
+  if (threadIdx.x < kCtrCopies)
+    __hip_atomic_fetch_add(&a.ctr[2 + opi + kCtrStride * threadIdx.x], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Wait for in-stage producers, compute, signal (one tile of op `opi`, whose
 // descriptor is `op` in LDS and `o` for uniform use).
 template <int KV>
 __device__ __forceinline__ void tile_body(const StageArgs &a, const Slots &sl, const DevOp *ops, const DevOp &op,
                                           const DevOp &o, int opi, int ti, float *lds) {
-  const int tid = threadIdx.x;
   const int n_deps = o.n_deps, signal = o.signal;
-  if (n_deps) {
-    // one thread polls the producers' counters with coherent loads (its own
-    // copy of each, so the pollers of a stage spread over kCtrCopies memory
-    // channels), then invalidates stale cache lines once; the workgroup
-    // reads the producers' outputs only after that (barrier)
-    if (tid == 0) {
-      int32_t *mine = a.ctr + 2 + kCtrStride * (blockIdx.x % kCtrCopies);
-      for (int k = 0; k < n_deps; ++k) {
-        const int d = op.dep[k];
-        const int need = ops[d].n_tiles;
-        int spins = 0;
-        while (__hip_atomic_load(&mine[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) {
-          __builtin_amdgcn_s_sleep(4);
-          if (++spins > a.spin_limit) {
-            __hip_atomic_fetch_or(a.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            break;
-          }
-        }
-      }
-      // drop lines of this CU / XCD that may predate the producers' stores
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    }
-    __syncthreads();
-  }
-
+  if (n_deps) tile_wait(a, ops, op, n_deps);
   if (n_deps || signal) run_tile<true, KV>(sl, op, o, ti, lds);
   else run_tile<false, KV>(sl, op, o, ti, lds);
-
-  if (signal) {
-    // The tile's outputs were written with agent-coherent stores.  Every wave
-    // waits until its stores have been performed, then one wave moves every
-    // copy of the op's counter; a consumer reads the outputs only after
-    // seeing the final count and invalidating its stale lines, so it sees
-    // every value.  This orders like a release/acquire pair without a
-    // per-tile L2 writeback.
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-    __syncthreads();
-    if (tid < kCtrCopies)
-      __hip_atomic_fetch_add(&a.ctr[2 + opi + kCtrStride * tid], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (signal) tile_signal(a, opi);
 }
 
+// The same for a split tile.
+template <bool COH>
+__device__ __forceinline__ void run_split(const Slots &sl, const DevOp &op, const SplitDesc &d, int ti, float *lds) {
+  if (tile_is_split_pb2(U(op.tcfg))) conv_split_tile<2, COH>(sl, op, d, ti, lds);
+  else conv_split_tile<1, COH>(sl, op, d, ti, lds);
+}
+__device__ __forceinline__ void split_body(const StageArgs &a, const Slots &sl, const DevOp *ops, const DevOp &op,
+                                           int opi, int ti, float *lds) {
+  const SplitDesc d = split_desc(op.sp);
+  const int n_deps = U(op.n_deps), signal = U(op.signal);
+  if (n_deps) tile_wait(a, ops, op, n_deps);
+  if (n_deps || signal) run_split<true>(sl, op, d, ti, lds);
+  else run_split<false>(sl, op, d, ti, lds);
+  if (signal) tile_signal(a, opi);
+}
 
 // One tile: find its op, then tile_body.
 // `tab` is the stage table in LDS, `gtab` the same table in global memory.
@@ -1882,8 +2232,15 @@ __device__ __forceinline__ void process_tile(const StageArgs &a, const Slots &sl
   // registers at once (op_scalars); the SEPCONV and full variants, which
   // read many (a v_readlane per word and hundreds of spilled scalars), load
   // each field where it is used with scalar loads from the table in global
-  // memory (read-only while the kernel runs, a uniform address).
-  if constexpr (KV == KV_LIGHT || KV == KV_PIPE) {
+  // memory (read-only while the kernel runs, a uniform address).  The split
+  // tiles have a descriptor of their own.
+  if constexpr (KV == KV_SPLIT || KV == KV_FULL) {
+    if (U(op.kind) == DK_CONV && U(op.tcfg) >= TC_S256x64) {
+      split_body(a, sl, ops, op, opi, ti, lds);
+      return;
+    }
+  }
+  if constexpr (KV == KV_LIGHT || KV == KV_PIPE || KV == KV_SPLIT) {
     const DevOp o = op_scalars(op);
     tile_body<KV>(a, sl, ops, op, o, opi, ti, lds);
   } else {
@@ -1899,15 +2256,13 @@ __device__ __forceinline__ void process_tile(const StageArgs &a, const Slots &sl
 // pointer words from the kernel arguments) is issued before the first wait.
 __device__ __forceinline__ float *stage_prologue(const int4 *__restrict__ table, int table_words,
                                                  const StageArgs &a, int32_t *meta) {
-  const int tid = threadIdx.x, nv = table_words >> 2;
-  const bool ht = tid < nv, hs = tid < kSlotWords;
-  int4 tv{};
-  int sv = 0;
-  if (ht) tv = table[tid];
-  if (hs) sv = ((const int32_t *)a.slot)[tid];
+  // threads past the end copy the last element again: no branch
+  const int tid = threadIdx.x, nv = table_words >> 2, i0 = min(tid, nv - 1), j0 = min(tid, kSlotWords - 1);
+  const int4 tv = table[i0];
+  const int sv = ((const int32_t *)a.slot)[j0];
   int4 *dst = (int4 *)(meta + kSlotWords);
-  if (ht) dst[tid] = tv;
-  if (hs) meta[tid] = sv;
+  dst[i0] = tv;
+  meta[j0] = sv;
   for (int i = tid + kThreads; i < nv; i += kThreads) dst[i] = table[i];   // tables over 8 KB
   __syncthreads();
   return (float *)(meta + kSlotWords + table_words);
@@ -1938,12 +2293,8 @@ __device__ __forceinline__ int xcd_tile(int b, int n, int lg) {
   return ((((local >> lg) << 3) + xcd) << lg) + (local & ((1 << lg) - 1));
 }
 
-// The one-tile-per-workgroup kernels of the light, pipelined and row-SEPCONV
-// variants keep two workgroups per CU (at most 128 VGPRs).
 template <int KV, bool PERSIST>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
-    (!PERSIST && (KV == KV_LIGHT || KV == KV_PIPE || KV == KV_SEPROW)) ? 4 : 1))) void ios_stage_kernel(const int4 *__restrict__ table, int table_words,
-                                                             StageArgs a) {
+__device__ __forceinline__ void stage_body(const int4 *__restrict__ table, int table_words, const StageArgs &a) {
   extern __shared__ int4 lds_base[];
   int32_t *meta = (int32_t *)lds_base;
   float *lds = stage_prologue(table, table_words, a, meta);
@@ -1983,6 +2334,22 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
       __hip_atomic_store(&a.ctr[1], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
+}
+
+// The one-tile-per-workgroup kernels of the light, pipelined and row-SEPCONV
+// variants keep two workgroups per CU (at most 128 VGPRs).
+template <int KV, bool PERSIST>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
+    (!PERSIST && (KV == KV_LIGHT || KV == KV_PIPE || KV == KV_SEPROW)) ? 4 : 1))) void ios_stage_kernel(const int4 *__restrict__ table, int table_words,
+                                                             StageArgs a) {
+  stage_body<KV, PERSIST>(table, table_words, a);
+}
+
+// The split variant: two workgroups per CU.
+template <bool PERSIST>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PERSIST ? 1 : 4))) void ios_split_kernel(
+    const int4 *__restrict__ table, int table_words, StageArgs a) {
+  stage_body<KV_SPLIT, PERSIST>(table, table_words, a);
 }
 
 }  // namespace ios

@@ -22,6 +22,10 @@ void *stage_kernel_fn_pipe();
 hipError_t stage_launch_pipe(const int4 *t, int words, const StageArgs &a, int grid, int lds, hipStream_t s);
 void *stage_kernel_fn_pipe_persist();
 hipError_t stage_launch_pipe_persist(const int4 *t, int words, const StageArgs &a, int grid, int lds, hipStream_t s);
+void *stage_kernel_fn_split();
+hipError_t stage_launch_split(const int4 *t, int words, const StageArgs &a, int grid, int lds, hipStream_t s);
+void *stage_kernel_fn_split_persist();
+hipError_t stage_launch_split_persist(const int4 *t, int words, const StageArgs &a, int grid, int lds, hipStream_t s);
 void *stage_kernel_fn_full();
 hipError_t stage_launch_full(const int4 *t, int words, const StageArgs &a, int grid, int lds, hipStream_t s);
 void *stage_kernel_fn_full_persist();
@@ -29,6 +33,8 @@ hipError_t stage_launch_full_persist(const int4 *t, int words, const StageArgs &
 
 int op_lds_bytes(const DevOp &op) {
   if (op.kind == DK_CONV && tile_is_pipe(op.tcfg)) return pipe_lds_bytes(op.tcfg);
+  if (op.kind == DK_CONV && tile_is_split(op.tcfg))
+    return split_geometry(op.tcfg, op.N, op.Cin, op.Cout, op.H, op.W, op.Ho, op.Wo, op.kh, op.kw, op.sh, op.sw).lds;
   if (op.kind == DK_CONV) {
     TileShape s = tile_shape(op.tcfg);
     return s.wk * tile_bn(op.tcfg) * (tile_bm(op.tcfg) + 1) * (int)sizeof(float);
@@ -58,6 +64,7 @@ static void *kernel_of(int variant, bool persist) {
     case KV_SEP: return persist ? stage_kernel_fn_sep_persist() : stage_kernel_fn_sep();
     case KV_SEPROW: return persist ? stage_kernel_fn_seprow_persist() : stage_kernel_fn_seprow();
     case KV_PIPE: return persist ? stage_kernel_fn_pipe_persist() : stage_kernel_fn_pipe();
+    case KV_SPLIT: return persist ? stage_kernel_fn_split_persist() : stage_kernel_fn_split();
     default: return persist ? stage_kernel_fn_full_persist() : stage_kernel_fn_full();
   }
 }
@@ -98,6 +105,9 @@ hipError_t launch_stage(const int32_t *table, int table_words, const StageArgs &
     case KV_PIPE:
       return persistent ? stage_launch_pipe_persist(t, w, args, grid, lds_bytes, stream)
                         : stage_launch_pipe(t, w, args, grid, lds_bytes, stream);
+    case KV_SPLIT:
+      return persistent ? stage_launch_split_persist(t, w, args, grid, lds_bytes, stream)
+                        : stage_launch_split(t, w, args, grid, lds_bytes, stream);
     default:
       return persistent ? stage_launch_full_persist(t, w, args, grid, lds_bytes, stream)
                         : stage_launch_full(t, w, args, grid, lds_bytes, stream);

@@ -1,0 +1,159 @@
+"""Split conv tiles (shapes 12 .. 19: both operands as three bf16 parts, six
+products summed in fp32) at the sizes where they can go wrong: channel tails,
+tiles that cross rows and images, strides, windows of one row or column,
+padded 1 x 1 windows, merged destinations, an input ReLU, and values outside
+the range in which the parts are exact (computed in fp32 instead).
+
+Tolerance: an operand's three parts leave at most 2^-27 of it, the products
+left out are below 2^-26 of a product, and the fp32 sums of n terms err by at
+most n 2^-24 of the sum of the terms' magnitudes; per output the error is at
+most (K + 8) 2^-24 sum |x| |w|, K the reduction length (the six products of 16
+terms are K 6 / 16 additions)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+I = pytest.importorskip("paper_2011_01302_amd")
+from oracle import evaluator as E          # noqa: E402
+
+DEV = "cuda:0"
+SPLIT = list(range(12, 20))
+
+
+def conv_op(name, cout, k, pad, stride=1, pre=0, post=0):
+    return {"name": name, "kind": "conv", "in": ["x"], "cout": cout, "kh": k[0], "kw": k[1], "sh": stride,
+            "sw": stride, "ph": pad[0], "pw": pad[1], "pre_relu": pre, "post_relu": post}
+
+
+def graph(monkeypatch, batch, c, h, w, ops, ten):
+    monkeypatch.setenv("IOS_CONV_TILE", "1")          # no tile measurement at set-up
+    g = I.Graph({"batch": batch, "inputs": [{"name": "x", "c": c, "h": h, "w": w}], "ops": ops,
+                 "outputs": [o["name"] for o in ops]}, ten)
+    return g
+
+
+def launch(g, stages, strategies, x, ops, h, w):
+    q = I.ios_schedule_from_stages(g.handle, stages, strategies)
+    d = torch.from_numpy(x).to(DEV)
+    outs = []
+    for o in ops:
+        ho, wo = (h + 2 * o["ph"] - o["kh"]) // o["sh"] + 1, (w + 2 * o["pw"] - o["kw"]) // o["sw"] + 1
+        outs.append(torch.full((g.batch, o["cout"], ho, wo), float("nan"), device=DEV))
+    for _ in range(2):
+        I.ios_run(g.handle, q, [d.data_ptr()], [t.data_ptr() for t in outs], 0)
+    torch.cuda.synchronize()
+    assert I.ios_device_status(g.handle) == 0
+    I.ios_schedule_destroy(q)
+    return [t.cpu().numpy().astype(np.float64) for t in outs]
+
+
+def reference(x, wt, b, o):
+    """(exact, bound) of one conv."""
+    s, p = (o["sh"], o["sw"]), (o["ph"], o["pw"])
+    ref = E.conv2d(x, wt, b, s, p, o["pre_relu"], o["post_relu"])
+    xa = np.maximum(x, 0) if o["pre_relu"] else np.abs(x)
+    mag = E.conv2d(xa, np.abs(wt), np.abs(b), s, p)
+    return ref, (wt[0].size + 8) * 2.0 ** -24 * mag
+
+
+CASES = {
+    # batch, c, h, w, cout, window, pad, stride, input ReLU
+    "tails": (3, 5, 7, 9, 33, (3, 3), (1, 1), 1, 0),
+    "one channel past a chunk": (2, 17, 11, 6, 70, (5, 5), (2, 2), 1, 0),
+    "stride over images": (4, 33, 8, 8, 40, (3, 3), (1, 1), 2, 0),
+    "stride past the window": (2, 24, 9, 7, 31, (2, 2), (0, 0), 3, 0),
+    "gather, stride 2": (2, 24, 9, 5, 31, (1, 1), (0, 0), 2, 0),
+    "gather, padded": (2, 16, 5, 5, 32, (1, 1), (1, 1), 1, 0),
+    "column window": (3, 20, 6, 6, 65, (7, 1), (3, 0), 1, 0),
+    "row window": (1, 64, 17, 17, 96, (1, 7), (0, 3), 1, 0),
+    "several rounds": (1, 200, 33, 20, 64, (3, 3), (1, 1), 1, 0),
+    "many chunks, one pixel": (1, 530, 1, 1, 130, (1, 1), (0, 0), 1, 0),
+    "input ReLU": (2, 20, 9, 9, 40, (3, 3), (1, 1), 1, 1),
+    "tile edge": (1, 16, 16, 16, 128, (3, 3), (1, 1), 1, 0),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_split_shapes(name, monkeypatch):
+    n, c, h, w, cout, k, pad, stride, pre = CASES[name]
+    rng = np.random.default_rng(len(name) * 1000 + c)
+    x = rng.standard_normal((n, c, h, w)).astype(np.float32)
+    wt = (rng.standard_normal((cout, c) + k) * (2.0 / (c * k[0] * k[1])) ** 0.5).astype(np.float32)
+    b = rng.standard_normal(cout).astype(np.float32)
+    ops = [conv_op("a", cout, k, pad, stride, pre)]
+    g = graph(monkeypatch, n, c, h, w, ops, {"a.w": wt, "a.b": b})
+    ref, bound = reference(x, wt, b, ops[0])
+    for t in SPLIT:
+        I.ios_set_conv_tile(g.handle, g.tid["a"], t)
+        got, = launch(g, [[g.tid["a"]]], [I.IOS_CONCURRENT], x, ops, h, w)
+        assert np.all(np.abs(got - ref) <= bound), (name, t, float((np.abs(got - ref) / bound).max()))
+    g.close()
+
+
+@pytest.mark.parametrize("tile", [12, 15, 17, 19])
+def test_split_merge_has_every_destination(tile, monkeypatch):
+    """A 1x1 and a 3x3 conv of one input as one merge stage (two routes), and
+    the same pair as one concurrent stage."""
+    rng = np.random.default_rng(7)
+    x = rng.standard_normal((2, 19, 10, 13)).astype(np.float32)
+    ops = [conv_op("a", 37, (1, 1), (0, 0), post=1), conv_op("b", 50, (3, 3), (1, 1), post=1)]
+    ten = {}
+    for o in ops:
+        ten[o["name"] + ".w"] = (rng.standard_normal((o["cout"], 19, o["kh"], o["kw"])) * 0.2).astype(np.float32)
+        ten[o["name"] + ".b"] = rng.standard_normal(o["cout"]).astype(np.float32)
+    g = graph(monkeypatch, 2, 19, 10, 13, ops, ten)
+    u = [g.tid["a"], g.tid["b"]]
+    monkeypatch.setenv("IOS_CONV_TILE", str(tile))
+    for i in u:
+        I.ios_set_conv_tile(g.handle, i, tile)
+    for stages, strat in (([u], [I.IOS_MERGE]), ([u], [I.IOS_CONCURRENT])):
+        got = launch(g, stages, strat, x, ops, 10, 13)
+        for o, y in zip(ops, got):
+            ref, bound = reference(x, ten[o["name"] + ".w"], ten[o["name"] + ".b"], o)
+            bound = bound * (9 * 19 + 8) / (19 * o["kh"] * o["kw"] + 8)     # merged: the larger window's length
+            assert np.all(np.abs(y - ref) <= bound), (tile, strat, o["name"])
+    g.close()
+
+
+@pytest.mark.parametrize("scale", [1e-38, 1e-30, 1e-14, 1e25, 1e30, "inf", "nan"])
+def test_split_values_out_of_range(scale, monkeypatch):
+    """Inputs so small or large that bf16 parts would lose bits or overflow,
+    an infinity and a NaN: as plain fp32 sums give them."""
+    rng = np.random.default_rng(3)
+    n, c, h, w, cout = 2, 20, 9, 9, 40
+    x = rng.standard_normal((n, c, h, w)).astype(np.float32)
+    if scale == "inf":
+        x[1, 7, 4, 4] = np.inf
+    elif scale == "nan":
+        x[0, 3, 0, 8] = np.nan
+    else:
+        x = (x * np.float32(scale)).astype(np.float32)
+    wt = (rng.standard_normal((cout, c, 3, 3)) * 0.1).astype(np.float32)
+    b = np.zeros(cout, np.float32)
+    ops = [conv_op("a", cout, (3, 3), (1, 1))]
+    g = graph(monkeypatch, n, c, h, w, ops, {"a.w": wt, "a.b": b})
+    ref, bound = reference(x, wt, b, ops[0])
+    fine = np.isfinite(ref)
+    for t in SPLIT:
+        I.ios_set_conv_tile(g.handle, g.tid["a"], t)
+        got, = launch(g, [[g.tid["a"]]], [I.IOS_CONCURRENT], x, ops, h, w)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)), (scale, t)
+        assert np.array_equal(got[~fine & ~np.isnan(ref)], ref[~fine & ~np.isnan(ref)]), (scale, t)
+        # 1e-38: products fall below the normal numbers, whose spacing is 2^-149
+        assert np.all(np.abs(got - ref)[fine] <= bound[fine] + c * 9 * 2.0 ** -149), (scale, t)
+    g.close()
+
+
+def test_split_refused_for_weights_out_of_range():
+    """Weights that are not finite, above 2^40 or all below 2^-30: no split shape."""
+    for v in (np.inf, np.nan, 2.0 ** 41, 2.0 ** -31):
+        wt = np.full((8, 16, 3, 3), v, np.float32)
+        g = I.Graph({"batch": 1, "inputs": [{"name": "x", "c": 16, "h": 5, "w": 5}],
+                     "ops": [conv_op("a", 8, (3, 3), (1, 1))], "outputs": ["a"]},
+                    {"a.w": wt, "a.b": np.zeros(8, np.float32)})
+        for t in SPLIT:
+            with pytest.raises(I.IosError):
+                I.ios_set_conv_tile(g.handle, g.tid["a"], t)
+        g.close()
