@@ -193,9 +193,10 @@ int ios_set_conv_tile(ios_graph *g, int32_t unit_id, int32_t shape);
  * choice (0, 1, 2: runs of 16, 32 or 64 consecutive output pixels with
  * every output channel, input rows staged in LDS; 3 .. 6: 16 pixels of one
  * output row with 1 .. 4 blocks of 16 output channels, for at most 256
- * input channels and windows up to 5 x 5; 7, 8: whole output rows in 128
- * or 64 MFMA columns x 64 or 128 output channels, for one input and a
- * 3 x 3 or 5 x 5 window that keeps the plane size; 9, 10: 32 / W whole
+ * input channels and windows up to 5 x 5; 7, 8: 128 or 64 output pixels x
+ * 192 or 384 output channels with the pointwise operands split into three
+ * bf16 parts, for one input and a 3 x 3 or 5 x 5 window that keeps the plane
+ * size, at least two of whose rows fit the pixels; 9, 10: 32 / W whole
  * output rows x 32 or 64 output channels, with 16-byte loads, for a 3 x 3
  * window that keeps the plane size, rows of a multiple of 4 up to 32 floats
  * and at most 96 input channels), 0 for the other kinds;
@@ -249,7 +250,7 @@ void ios_sched_opts_default(ios_sched_opts *opts);
 
 /* Find a schedule (Algorithm 1, block by block).  With fn == NULL each
  * candidate stage is measured with ios_profile_stage (a concurrent stage
- * holding two or more SEPCONVs that admit the GEMM SEPCONV tile is measured
+ * holding two or more SEPCONVs that admit the 128-pixel split tile is measured
  * also with them on it, likewise on the 64-channel line tile, and the fastest
  * figure counts, unless IOS_SEP_TILE fixes the tile choices); otherwise fn(ctx, ...) supplies latencies.  Ties: a stage keeps concurrent execution only if it is
  * strictly faster than merge; among equal-cost endings the smallest

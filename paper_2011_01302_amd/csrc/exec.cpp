@@ -156,7 +156,7 @@ double tile_work(const DevOp &d) {
     }
     case DK_SEP:
       if (d.sep_row == 2)
-        return (double)d.sepg_rout * d.Wo * d.CinP * (d.kh * d.kw + 32.0 * (kWaves / d.sep_nbt)) / kWaves;
+        return (double)d.sp.sc * d.CinP * (d.kh * d.kw + 6.0 / 16.0 * round_up(d.Cout, 32)) / kWaves;
       if (d.sep_row == 3) return 32.0 * d.CinP * (9.0 * d.n_in + 32.0 * d.sep_nbt) / kWaves;
       if (d.sep_row) return 16.0 * d.CinP * (d.row_k * d.row_k * d.n_in + 16.0 * d.sep_nbt) / kWaves;
       return (double)d.sep_bm * d.CinP * (d.kh * d.kw + 16.0 * d.sep_nbt) / kWaves;
@@ -302,6 +302,31 @@ void set_split(DevOp &d, const float *w, const float *w32, bool raw) {
   p.fd_w2 = make_fdiv((uint32_t)g.w2);
   p.fd_hv = make_fdiv((uint32_t)g.hv);
   p.w = w; p.bias = d.bias; p.w32 = w32; p.raw = raw;
+}
+// The same of a SEPCONV's split tile (the pointwise weights and their fp32 pack).
+void set_sep_split(DevOp &d, const SepSplitGeom &g, const float *w, const float *w32) {
+  SplitDesc &p = d.sp;
+  p.sc = g.tp; p.lwm = g.per_img;
+  p.nch = cdiv(d.Cin, kSplitCK); p.pp = g.pp;
+  p.fd_taps = make_fdiv((uint32_t)std::max(1, g.per_img));
+  p.w2 = g.w2; p.hv = g.hv; p.tail = g.tail;
+  p.Ho = d.Ho; p.Wo = d.Wo; p.howo = d.Ho * d.Wo; p.M = d.N * p.howo;
+  p.N = d.N; p.H = d.H; p.W = d.W; p.Cin = d.Cin; p.Cout = d.Cout;
+  p.kh = d.kh; p.kw = d.kw; p.taps = g.rows; p.raw = g.lq;
+  p.fd_pp = make_fdiv((uint32_t)((d.W + 3) / 4));
+  p.sh = p.sw = 1; p.ph = d.ph; p.pw = d.pw;
+  p.in_slot = d.in_slot[0]; p.in_coff = d.in_coff[0]; p.in_ctot = d.in_ctot[0]; p.in_bytes = d.in_bytes[0];
+  p.pre_relu = d.pre_relu; p.post_relu = d.post_relu;
+  p.n_routes = 1; p.route_slot = d.route_slot[0]; p.route_coff = d.route_coff[0]; p.route_ctot = d.route_ctot[0];
+  p.tiles_n = cdiv(d.Cout, g.bn);
+  p.w_bytes = (int32_t)(split_words(d.Cout, d.Cin, 1, 1) * sizeof(float));
+  p.fd_tn = make_fdiv((uint32_t)p.tiles_n);
+  p.fd_wo = make_fdiv((uint32_t)d.Wo);
+  p.fd_ho = make_fdiv((uint32_t)d.Ho);
+  p.fd_howo = make_fdiv((uint32_t)p.howo);
+  p.fd_w2 = make_fdiv((uint32_t)g.w2);
+  p.fd_hv = make_fdiv((uint32_t)g.hv);
+  p.w = w; p.bias = d.bias; p.w32 = w32;
 }
 }  // namespace
 
@@ -452,7 +477,7 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
     const int n_ops = (int)ops.size();
     const int table_bytes = (kSlotWords + ((4 + n_ops + 1 + 3) & ~3) + n_ops * kDevOpWords) * (int)sizeof(int32_t);
     const bool pipe_fits = table_bytes + pipe_lds_bytes(TC_W128x64) <= kMaxLdsBytes;
-    // a split tile runs in the variant without SEPCONV tiles, and its patch
+    // a split conv tile runs in a variant without SEPCONV tiles, and its patch
     // must fit beside the table too
     bool any_sep = false;
     for (int i : ops) any_sep |= g->ops[i].d.kind == IOS_SEPCONV;
@@ -506,33 +531,32 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
             d.dw_bytes = (int32_t)((size_t)d.CinP * sep_kkp(3) * sizeof(float));
             break;
           }
-          if (o.sep_tile >= kSepgFirst) {
-            // GEMM tile (see the stage kernel)
-            const SepgGeom sg = sepg_geometry(o.sep_tile - kSepgFirst, (int)o.in.size(), o.d.kh, o.d.kw,
-                                              o.d.pad_h, o.d.pad_w, o.h, o.wd, o.ho, o.wo);
-            if (sg.bm == 0 || !o.d_pw_pipe) fail(IOS_E_UNSUPPORTED, "SEPCONV GEMM tile does not apply");
+          int sep_tile = o.sep_tile;
+          if (sep_tile >= kSepgFirst && !sep_tile_ok(o, sep_tile)) fail(IOS_E_UNSUPPORTED, "SEPCONV split tile does not apply");
+          SepSplitGeom sg2;
+          if (sep_tile >= kSepgFirst && o.d_wsp) sg2 = sep_split_geometry(sep_tile - kSepgFirst, g->batch, o.d.kh, o.ho, o.wo);
+          if (sg2.tp > 0 && table_bytes + sg2.lds <= kMaxLdsBytes) {
+            // split tile (see the stage kernel)
             d.kind = DK_SEP; d.sep_row = 2;
-            d.CinP = o.CinP; d.Npad = o.Npad;
-            d.sep_nbt = sg.bm / 32;
-            d.sep_nck = o.CinP / 16;
-            d.sep_rows = sg.rows;
-            d.sepg_rout = sg.rout; d.sepg_w2 = sg.w2; d.sepg_strips = sg.strips; d.sepg_ps = sg.ps;
-            d.sepg_xs = sg.xs; d.sepg_ws = sg.ws;
-            d.pipe_ldw = round_up(o.d.cout, 128);
-            d.wpk = o.d_pw_pipe; d.bias = o.d_bias; d.dw = o.d_dw;
-            d.w_bytes = (int32_t)((size_t)o.CinP * d.pipe_ldw * sizeof(float));
-            d.dw_bytes = (int32_t)((size_t)o.CinP * o.d.kh * o.d.kw * sizeof(float));
+            d.CinP = o.CinP; d.Npad = o.Npad; d.NG = o.NG;
+            d.sep_nbt = sg2.bm / 32;
+            d.bias = o.d_bias; d.dw = o.d_dw;
+            set_sep_split(d, sg2, o.d_wsp, o.d_wpk);
             break;
           }
-          if (o.sep_tile >= kSepStagedTiles) {
+          // weights out of the split tiles' range, rows of fewer than four
+          // floats, or a stage of very many operators: the staged tile of 32
+          // pixels, or of 16
+          if (sep_tile >= kSepgFirst) sep_tile = sep_tile_ok(o, 1) ? 1 : 0;
+          if (sep_tile >= kSepStagedTiles) {
             // row tile (see the stage kernel)
-            if (!sep_tile_ok(o, o.sep_tile)) fail(IOS_E_UNSUPPORTED, "SEPCONV row tile does not apply");
+            if (!sep_tile_ok(o, sep_tile)) fail(IOS_E_UNSUPPORTED, "SEPCONV row tile does not apply");
             d.kind = DK_SEP; d.sep_row = 1;
             d.CinP = round_up(o.cin, 4); d.Npad = o.Npad;
             d.wpk = o.d_pw_row; d.bias = o.d_bias; d.dw = o.d_dw_row;
             d.w_bytes = (int32_t)((size_t)d.CinP * o.Npad * sizeof(float));
             d.row_k = sep_row_window(o.d.kh, o.d.kw);
-            d.sep_nbt = o.sep_tile - kSepStagedTiles + 1;
+            d.sep_nbt = sep_tile - kSepStagedTiles + 1;
             d.dw_bytes = (int32_t)((size_t)d.CinP * sep_kkp(d.row_k) * sizeof(float));
             break;
           }
@@ -540,7 +564,7 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
           d.wpk = o.d_wpk; d.bias = o.d_bias; d.dw = o.d_dw;
           d.w_bytes = (int32_t)((size_t)(o.Npad / 16) * o.NG * 256 * sizeof(float));
           d.dw_bytes = (int32_t)((size_t)o.CinP * o.d.kh * o.d.kw * sizeof(float));
-          const SepGeom sg = sep_geometry(o.sep_tile, o.cin, o.d.cout, o.wd, o.ho, o.wo, o.d.kh, o.d.kw);
+          const SepGeom sg = sep_geometry(sep_tile, o.cin, o.d.cout, o.wd, o.ho, o.wo, o.d.kh, o.d.kw);
           if (sg.bm == 0) fail(IOS_E_UNSUPPORTED, "SEPCONV tile does not fit");
           d.sep_bm = sg.bm;
           d.sep_lbm = 31 - __builtin_clz((unsigned)sg.bm);
@@ -579,10 +603,9 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
       d.tiles_m = cdiv(M, tile_bm(d.tcfg));
       d.tiles_n = cdiv(d.Cout, tile_bn(d.tcfg));
     } else if (d.kind == DK_SEP && d.sep_row == 2) {
-      // GEMM tile: (image, block of sepg_rout output rows) x groups of 32 (8 / sep_nbt) channels
-      d.tiles_per_plane = cdiv(d.Ho, d.sepg_rout);
-      d.tiles_m = d.N * d.tiles_per_plane;
-      d.tiles_n = cdiv(d.Cout, 32 * (kWaves / d.sep_nbt));
+      // split tile: runs of sp.sc output pixels of an image or the batch x groups of 96 (8 / sep_nbt) channels
+      d.tiles_m = d.sp.lwm ? d.N * d.sp.lwm : cdiv(M, d.sp.sc);
+      d.tiles_n = d.sp.tiles_n;
     } else if (d.kind == DK_SEP && d.sep_row == 3) {
       // line tile: (image, block of line_r output rows) x groups of 32 sep_nbt channels
       d.tiles_per_plane = cdiv(d.Ho, d.line_r);
@@ -650,9 +673,6 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
     d.fd_spt = fd(d.CinP / 4);
     d.fd_kw = fd(d.kw);
     d.fd_pimg = fd(d.kind == DK_SEP && d.sep_row == 1 ? d.Ho * d.row_bpr : d.tiles_per_plane);
-    d.fd_ps = fd(d.sepg_ps);
-    d.fd_w2 = fd(d.sepg_w2);
-    d.fd_strips = fd(d.sepg_strips);
     d.fd_rbpr = fd(d.row_bpr);
     d.fd_cin = fd(d.Cin);
     d.fd_rw = fd(d.sep_rows * d.W);
@@ -680,7 +700,8 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
   for (int i = 0; i < n; ++i) pos[order[i]] = i;
   std::vector<DevOp> sorted;
   std::vector<int32_t> start{0};
-  bool persistent = false, big_conv = false, has_sep = false, has_row = false, has_pipe = false, has_split = false;
+  bool persistent = false, big_conv = false, has_sep = false, has_row = false, has_pipe = false, has_split = false,
+       has_sepsplit = false;
   for (const DevOp &d : dops) persistent |= d.n_deps > 0;
   int lds = 0;
   for (size_t k = 0; k < order.size(); ++k) {
@@ -699,7 +720,8 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
     big_conv |= d.kind == DK_CONV && !tile_is_light(d.tcfg) && !tile_is_pipe(d.tcfg) && !tile_is_split(d.tcfg);
     has_pipe |= d.kind == DK_CONV && tile_is_pipe(d.tcfg);
     has_split |= d.kind == DK_CONV && tile_is_split(d.tcfg);
-    has_sep |= d.kind == DK_SEP && (d.sep_row == 0 || d.sep_row == 2);
+    has_sepsplit |= d.kind == DK_SEP && d.sep_row == 2;
+    has_sep |= d.kind == DK_SEP && d.sep_row == 0;
     has_row |= d.kind == DK_SEP && (d.sep_row == 1 || d.sep_row == 3);
     lds = std::max(lds, op_lds_bytes(d));
   }
@@ -712,12 +734,13 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
   cs->lds_bytes = (kSlotWords + table_words) * (int)sizeof(int32_t) + lds;
   if (cs->lds_bytes > kMaxLdsBytes) fail(IOS_E_UNSUPPORTED, "stage needs more LDS than a workgroup has");
   cs->persistent = persistent;
-  const int kinds = (int)has_sep + (int)has_row + (int)has_pipe + (int)has_split;
+  const int kinds = (int)has_sep + (int)has_row + (int)has_pipe + (int)has_split + (int)has_sepsplit;
   cs->variant = big_conv || kinds > 1 ? KV_FULL
                 : has_sep            ? KV_SEP
                 : has_row            ? KV_SEPROW
                 : has_pipe           ? KV_PIPE
                 : has_split          ? KV_SPLIT
+                : has_sepsplit       ? KV_SEPSPLIT
                                      : KV_LIGHT;
   cs->grid = start.back();
   if (persistent) {

@@ -354,6 +354,16 @@ static T *upload(const std::vector<T> &v) {
   return p;
 }
 
+// conv weights w as the split tiles read them, in device memory
+static float *upload_split(ios_graph *g, const std::vector<float> &w, int cout, int cin, int kh, int kw) {
+  float *raw = upload(w), *p = nullptr;
+  const hipError_t e = hipMalloc(&p, split_words(cout, cin, kh, kw) * sizeof(float));
+  if (e == hipSuccess) pack_conv_split(raw, cout, cin, kh, kw, p, g->stream);
+  (void)hipFree(raw);
+  hip_check(e, "hipMalloc(weights)");
+  return p;
+}
+
 bool conv_tile_ok(const Op &op, int cfg) {
   if (cfg < 0 || cfg >= TC_COUNT) return false;
   if (tile_is_split(cfg))
@@ -368,8 +378,8 @@ bool sep_tile_ok(const Op &op, int tile) {
     return line_geometry(1 << (tile - kSepLineFirst), op.cin, op.d.cout, op.d.kh, op.d.kw, op.d.pad_h, op.d.pad_w,
                          op.d.stride_h, op.d.stride_w, op.h, op.wd, op.ho, op.wo).r != 0;
   if (tile >= kSepgFirst)
-    return sepg_geometry(tile - kSepgFirst, (int)op.in.size(), op.d.kh, op.d.kw, op.d.pad_h, op.d.pad_w, op.h,
-                         op.wd, op.ho, op.wo).bm != 0;
+    return sep_split_ok(tile - kSepgFirst, (int)op.in.size(), op.d.kh, op.d.kw, op.d.pad_h, op.d.pad_w, op.h, op.wd,
+                        op.ho, op.wo);
   if (tile < kSepStagedTiles)
     return sep_geometry(tile, op.cin, op.d.cout, op.wd, op.ho, op.wo, op.d.kh, op.d.kw).bm == (16 << tile);
   const int K = sep_row_window(op.d.kh, op.d.kw), nbt = tile - kSepStagedTiles + 1;
@@ -431,6 +441,8 @@ void finalize_graph(ios_graph *g) {
     } else if (op.d.kind == IOS_SEPCONV) {
       op.CinP = round_up(op.cin, 16);
       op.Npad = round_up(op.d.cout, 16);
+      const size_t ndw = (size_t)op.cin * op.d.kh * op.d.kw;
+      op.split_ok = split_weights_ok(op.w.data() + ndw, op.w.size() - ndw);
       op.sep_tile = choose_sep_tile(op);
     }
   }
@@ -470,11 +482,7 @@ void ensure_device(ios_graph *g) {
       pack_conv_pipe(op.w.data(), op.d.cout, op.cin, op.d.kh, op.d.kw, wg, &op.pipe_nkb);
       op.d_wg = upload(wg);
       if (op.split_ok) {
-        float *raw = upload(op.w);
-        const hipError_t e = hipMalloc(&op.d_wsp, split_words(op.d.cout, op.cin, op.d.kh, op.d.kw) * sizeof(float));
-        if (e == hipSuccess) pack_conv_split(raw, op.d.cout, op.cin, op.d.kh, op.d.kw, op.d_wsp, g->stream);
-        (void)hipFree(raw);
-        hip_check(e, "hipMalloc(weights)");
+        op.d_wsp = upload_split(g, op.w, op.d.cout, op.cin, op.d.kh, op.d.kw);
       }
     } else if (op.d.kind == IOS_SEPCONV) {
       // depthwise [CinP][kh * kw] (channels past cin zero); pointwise packed
@@ -489,12 +497,10 @@ void ensure_device(ios_graph *g) {
       op.d_dw = upload(dw);
       op.d_wpk = upload(pwk);
       op.d_bias = upload(bias);
-      // the GEMM tile's pointwise layout: [round16(cin)][round128(cout)]
-      if (sep_tile_ok(op, kSepgFirst) || sep_tile_ok(op, kSepgFirst + 1)) {
-        std::vector<float> pwp;
-        int nkb = 0;
-        pack_conv_pipe(op.w.data() + (size_t)op.cin * taps, op.d.cout, op.cin, 1, 1, pwp, &nkb);
-        op.d_pw_pipe = upload(pwp);
+      // the split tile's pointwise parts
+      if (op.split_ok && (sep_tile_ok(op, kSepgFirst) || sep_tile_ok(op, kSepgFirst + 1))) {
+        const std::vector<float> pw(op.w.begin() + (size_t)op.cin * taps, op.w.end());
+        op.d_wsp = upload_split(g, pw, op.d.cout, op.cin, 1, 1);
       }
       // the row tile's layouts, where it applies: depthwise taps at the top
       // left of a K x K window, [CinP4][kkp(K)]; pointwise [CinP4][Npad]

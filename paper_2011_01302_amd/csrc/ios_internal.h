@@ -181,9 +181,8 @@ bool split_weights_ok(const float *w, size_t n);
 // Tile choices: 0 .. kSepStagedTiles - 1 the staged tile (BM = 16 << choice),
 // then kSepRowMaxNB choices of the row tile (16 output pixels of one output
 // row x 1 .. kSepRowMaxNB channel blocks; Cin <= 256, windows up to 5 x 5),
-// then kSepgTiles choices of the GEMM tile (whole output rows in 128 or 64
-// MFMA columns x 64 or 128 output channels; one input, 3 x 3 or 5 x 5
-// windows that keep the size), then kSepLineTiles choices of the line tile
+// then kSepgTiles choices of the split tile (128 or 64 output pixels x 192 or
+// 384 output channels; see sep_split_ok), then kSepLineTiles choices of the line tile
 // (32 / Wo whole output rows x 32 or 64 output channels; 3 x 3 windows that
 // keep the size, rows of a multiple of 4 floats up to 32, Cin <= 96).
 constexpr int kSepStagedTiles = 3;       // BM = 16, 32, 64
@@ -193,40 +192,55 @@ constexpr int kSepgFirst = kSepStagedTiles + kSepRowMaxNB;
 constexpr int kSepLineTiles = 2;
 constexpr int kSepLineFirst = kSepgFirst + kSepgTiles;
 constexpr int kSepTiles = kSepLineFirst + kSepLineTiles;
-constexpr int kSepgStages = 3;           // GEMM tile: ring slots of 16 input channels (two chunks in flight)
-constexpr int kSepgMaxRows = 4;          // GEMM tile: output rows per tile at most
-constexpr int kSepgMaxCopies = 12;       // GEMM tile: 64-float input copies per wave and chunk at most
-constexpr int kSepgMaxLds = 128 * 1024;  // GEMM tile: LDS bytes at most (the stage table comes on top)
-// GEMM tile geometry (bm = 0: the choice does not apply): rout output rows
-// per tile (2 .. kSepgMaxRows), staged input rows (rows), the staged plane's
-// row pitch (w2 = W + 2 pw, a zero halo on both sides) and pitch (ps, odd),
-// the floats per ring slot of the input planes (xs) and of the depthwise
-// weights (ws), and the depthwise strips of 2 output columns per row.
-struct SepgGeom {
-  int bm = 0, bn = 0, rout = 0, rows = 0, w2 = 0, ps = 0, xs = 0, ws = 0, strips = 0, lds = 0;
-};
-// LDS bytes of a GEMM tile: the ring (input planes, pointwise and depthwise
-// weights per slot) and two B operand buffers [16][bm + 1].
-inline int sepg_lds_bytes(int xs, int ws, int bm, int bn) {
-  return (kSepgStages * (xs + 16 * bn + ws) + 2 * 16 * (bm + 1)) * 4;
+// Where choices 7 and 8 apply: one input, a 3 x 3 or 5 x 5 window that keeps
+// the plane size, at least two whole rows in 128 (choice 7) or 64 (choice 8)
+// pixels, and 16 planes of those rows (four at most) and their halo in 6144
+// floats, beside 64 (128) output channels of weights in 128 KB of LDS three
+// times over: the range these choices were given with a tile that staged them
+// so.  Kept as it was, so that a choice is taken or refused as before.
+inline bool sep_split_ok(int choice, int n_in, int kh, int kw, int ph, int pw, int H, int W, int Ho, int Wo) {
+  const int bm = choice == 0 ? 128 : 64, bn = choice == 0 ? 64 : 128;
+  if (n_in != 1 || kh != kw || (kh != 3 && kh != 5) || ph != kh / 2 || pw != kw / 2 || Ho != H || Wo != W || Wo < 1)
+    return false;
+  int rout = std::min(std::min(bm / Wo, Ho), 4);
+  if (rout < 1 || (rout < 2 && Ho >= 2)) return false;
+  rout = std::max(rout, 2);
+  const int xs = (16 * (((rout + kh - 1) * (W + 2 * pw)) | 1) + 63) / 64 * 64, ws = (16 * kh * kw + 63) / 64 * 64;
+  return xs <= 6144 && (3 * (xs + 16 * bn + ws) + 2 * 16 * (bm + 1)) * 4 <= 128 * 1024;
 }
-inline SepgGeom sepg_geometry(int choice, int n_in, int kh, int kw, int ph, int pw, int H, int W, int Ho, int Wo) {
-  SepgGeom g;
-  const int wmw = choice == 0 ? 4 : 2, bm = 32 * wmw, bn = 32 * (8 / wmw);
-  if (n_in != 1 || kh != kw || (kh != 3 && kh != 5) || ph != kh / 2 || pw != kw / 2 || Ho != H || Wo != W ||
-      Wo < 1)
+// Their geometry: tp output pixels per tile; per_img tiles per image, or 0
+// where the pixels of the batch are flattened (images of fewer than bm pixels;
+// a tile that crosses images stages both their halos).  tp is bm, or less
+// where the windows of bm pixels read more than kSepSplitPieces pieces of four
+// columns of the patch: `rows` rows of w2 columns, pp >= rows w2 + 2 floats per
+// channel (an even number), 2^lq >= pieces.  Rows of at least four floats (tp
+// = 0: there is no geometry).
+constexpr int kSepSplitPieces = 128;
+constexpr int kSepSplitBlocks = 3;       // blocks of 32 output channels per wave
+struct SepSplitGeom {
+  int bm = 0, bn = 0, tp = 0, per_img = 0, rows = 0, pp = 0, lq = 0, w2 = 0, hv = 0, tail = 0, lds = 0;
+};
+inline SepSplitGeom sep_split_geometry(int choice, int N, int k, int Ho, int Wo) {
+  SepSplitGeom g;
+  g.bm = choice == 0 ? 128 : 64;
+  g.bn = 32 * kSepSplitBlocks * (kWaves / (g.bm / 32));
+  g.w2 = Wo - 1 + k;
+  g.hv = Ho - 1 + k;
+  if (Wo < 4) return g;
+  const bool flat = Ho * Wo < g.bm;
+  for (g.tp = g.bm; g.tp >= 1; g.tp >>= 1) {
+    const int64_t rows = std::min<int64_t>((int64_t)(flat ? N : 1) * Ho, (Wo - 1 + g.tp - 1) / Wo + 1);
+    const int64_t cross = rows < 2 || !flat ? 0 : std::min<int64_t>(N - 1, 1 + (rows - 2) / Ho);
+    const int64_t v = rows - 1 + k + cross * (k - 1), pieces = v * ((Wo + 3) / 4);
+    if (pieces > kSepSplitPieces) continue;
+    g.per_img = flat ? 0 : (Ho * Wo + g.tp - 1) / g.tp;
+    g.rows = (int)v;
+    g.pp = ((int)v * g.w2 + 2 + 3) / 4 * 4;
+    for (g.lq = 6; (1 << g.lq) < pieces; ++g.lq) {}
+    g.tail = 64 * g.pp + 96 * g.bm + 2 * (g.bn / 32) * kSplitWords * 4;
+    g.lds = g.tail + kSplitTail + g.bn * 4 + 16 * 28 * 4;   // flags, biases, a chunk's filters
     return g;
-  const int rout = std::min(std::min(bm / Wo, Ho), kSepgMaxRows);
-  if (rout < 2 && Ho >= 2) return g;
-  if (rout < 1) return g;
-  const int rows = rout + kh - 1, w2 = W + 2 * pw, ps = (rows * w2) | 1;
-  const int xs = (16 * ps + 63) / 64 * 64, ws = (16 * kh * kw + 63) / 64 * 64;
-  if (xs > kSepgMaxCopies * 8 * 64) return g;
-  if (sepg_lds_bytes(xs, ws, bm, bn) > kSepgMaxLds) return g;
-  g.bm = bm; g.bn = bn; g.rout = std::max(rout, 2); g.rows = g.rout + kh - 1; g.w2 = w2;
-  g.ps = (g.rows * w2) | 1; g.xs = (16 * g.ps + 63) / 64 * 64; g.ws = ws; g.strips = (Wo + 1) / 2;
-  g.lds = sepg_lds_bytes(g.xs, ws, bm, bn);
-  if (g.xs > kSepgMaxCopies * 8 * 64 || g.lds > kSepgMaxLds) return SepgGeom{};
+  }
   return g;
 }
 
@@ -367,6 +381,14 @@ struct SplitDesc {
 };
 static_assert(sizeof(SplitDesc) == 256, "one word per lane");
 
+// (SEP split tile, see SepSplitGeom: sc = tp, lwm = per_img (fd_taps divides by
+// it), taps = rows, raw = lq; fd_pp divides by the pieces of a row.)
+
+// Whether an operator (its kind, tcfg and sep_row) runs on a split tile.
+__host__ __device__ inline bool op_is_split(int kind, int tcfg, int sep_row) {
+  return kind == DK_CONV ? tcfg >= TC_S256x64 : kind == DK_SEP && sep_row == 2;
+}
+
 // One operator of a compiled stage, as the kernel sees it.
 struct alignas(16) DevOp {
   int32_t kind, tcfg;
@@ -396,11 +418,8 @@ struct alignas(16) DevOp {
   int32_t sep_ck, sep_nck;     // SEP: input channels per chunk, chunks
   int32_t sep_rows;            // SEP: input rows staged per chunk
   int32_t sep_nbt;             // SEP: 16-channel output blocks per tile
-  int32_t sep_row;             // SEP: 0 = staged tile, 1 = row tile, 2 = GEMM tile (sep_nbt = its waves along
+  int32_t sep_row;             // SEP: 0 = staged tile, 1 = row tile, 2 = split tile (sep_nbt = its blocks of 32
                                // pixels), 3 = line tile (sep_nbt = its 32-channel output blocks)
-  int32_t sepg_rout, sepg_w2;  // SEP GEMM tile: output rows per tile, staged row pitch (W + 2 pw)
-  int32_t sepg_strips, sepg_ps;// SEP GEMM tile: depthwise strips of 2 columns per row, staged plane pitch
-  int32_t sepg_xs, sepg_ws;    // SEP GEMM tile: floats per ring slot of the input planes and depthwise weights
   int32_t row_k, row_bpr;      // SEP row tile: padded window K, 16-pixel blocks per output row
   int32_t line_r, line_rows;   // SEP line tile: output rows per tile, staged input rows (see LineGeom)
   int32_t line_q, line_chp;    // SEP line tile: 16-byte pieces per staged channel, channels loaded at once
@@ -415,14 +434,13 @@ struct alignas(16) DevOp {
   FDiv fd_pimg, fd_rw, fd_w;   // SEP: pixel tiles (row tile: 16-pixel blocks) per image, staged floats per channel, W
   FDiv fd_rbpr;                // SEP row tile: 16-pixel blocks per row
   FDiv fd_cin;                 // CONV pipelined tile: Cin
-  FDiv fd_ps, fd_w2, fd_strips;// SEP GEMM tile: sepg_ps, sepg_w2, sepg_strips
   FDiv fd_tpp, fd_c;           // POOL / ADD / MEAN: tiles_per_plane, Cout
   FDiv fd_pin;                 // POOL with planes_per_tile > 1: floats staged per plane
   FDiv fd_lq, fd_lw4;          // SEP line tile: line_q, W / 4
   const float *wpk;            // CONV: see pack_conv_weights; SEP: the pointwise weights packed the same way
   const float *bias;           // [Npad]
   const float *dw;             // SEP: depthwise [round16(Cin)][kh * kw], channels past Cin zero
-  SplitDesc sp;                // CONV split tile
+  SplitDesc sp;                // CONV and SEP split tiles
 };
 
 // A compiled stage's table in device memory (int32 words): a header
@@ -448,7 +466,7 @@ struct StageArgs {
 // Launch one stage (defined in the HIP translation unit).
 // Kernel variant of a stage (see the stage kernel): the smallest one that
 // contains every tile kind the stage uses.
-enum KernelVariant { KV_LIGHT = 0, KV_SEP = 1, KV_FULL = 2, KV_SEPROW = 3, KV_PIPE = 4, KV_SPLIT = 5, KV_COUNT = 6 };
+enum KernelVariant { KV_LIGHT = 0, KV_SEP = 1, KV_FULL = 2, KV_SEPROW = 3, KV_PIPE = 4, KV_SPLIT = 5, KV_SEPSPLIT = 6, KV_COUNT = 7 };
 // table / table_words: the compiled stage's table (a multiple of 4 words);
 // lds_bytes: the dynamic LDS, slots and table included.
 hipError_t launch_stage(const int32_t *table, int table_words, const StageArgs &args, bool persistent,
@@ -494,11 +512,10 @@ struct Op {
   int sep_tile = 1;              // SEPCONV: tile choice (16 << sep_tile output pixels per tile)
   int xcd_lg = -1;               // XCD run length 2^xcd_lg of the stage holding it; -1: modelled
   float *d_wpk = nullptr, *d_bias = nullptr, *d_dw = nullptr;
-  float *d_pw_pipe = nullptr;    // SEPCONV GEMM tile: pointwise weights packed like a pipelined 1x1 conv's
   float *d_dw_row = nullptr, *d_pw_row = nullptr;   // SEPCONV row tile: [CinP4][kkp(K)], [CinP4][Npad]
   float *d_pw_line = nullptr;    // SEPCONV line tile: pointwise [ceil(Cout/32)][ceil(Cin/2)][64] (A operands)
-  float *d_wsp = nullptr;        // CONV, split tiles: see pack_conv_split
-  bool split_ok = false;         // CONV: split tiles may run it (split_weights_ok)
+  float *d_wsp = nullptr;        // split tiles: see pack_conv_split (SEPCONV: the pointwise weights)
+  bool split_ok = false;         // split tiles may run it (split_weights_ok)
   float *d_wg = nullptr;         // CONV, pipelined tiles: [nkb * kPipeKB][round128(Cout)]
   int pipe_nkb = 0;
 };

@@ -97,7 +97,7 @@ struct Provider {
   // A stage of several SEPCONVs can be bound by their throughput together,
   // which the isolated tile choice of each (the row or the 32-channel line
   // tile, at batch 1) misjudges; such a stage is also measured with every
-  // SEPCONV that admits it on the GEMM tile, and again on the 64-channel line
+  // SEPCONV that admits it on the 128-pixel split tile, and again on the 64-channel line
   // tile, and the fastest figure is the stage's latency (the per-stage tile
   // tuning of the chosen schedule makes the same choice).  IOS_SEP_TILE in
   // the environment keeps the choices fixed.

@@ -1658,252 +1658,315 @@ __device__ __forceinline__ void sep_line_tile(const Slots &sl, const DevOp &op, 
   }
 }
 
-// The loads of SEPCONV GEMM-tile chunk c into ring slot s: this wave's
-// 64-float pieces of the input planes (per-lane offsets xoff, the chunk's
-// first channel added), of the pointwise weights [16 k][BN] and of the
-// depthwise weights [16][KK].  Offsets that may pass the end of their
-// buffer are per-lane (the range check covers them): the planes of the last
-// chunk past Cin, the copy of the last chunk's depthwise weights rounded up
-// to 64 floats.
-template <int COPIES, int ACOPIES>
-__device__ __forceinline__ void sepg_issue(float *s, const __amdgpu_buffer_rsrc_t &xr, const __amdgpu_buffer_rsrc_t &wr,
-                                           const __amdgpu_buffer_rsrc_t &dr, const int *xoff, const int *aoff, int c,
-                                           int nx, int nw, int XS, int AS, int hw4, int ldw, int KK, int wave,
-                                           int lane) {
-  wave = __builtin_amdgcn_readfirstlane(wave);       // uniform loop bounds around the LDS loads
-#pragma unroll
-  for (int i = 0; i < COPIES; ++i) {
-    const int j = wave + i * kWaves;
-    if (j < nx)                                       // uniform
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void *)(s + j * 64), 4,
-                                               xoff[i] == kOOB ? kOOB : xoff[i] + c * 16 * hw4, 0, 0, 0);
-  }
-#pragma unroll
-  for (int i = 0; i < ACOPIES; ++i)
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_void *)(s + XS + (wave * ACOPIES + i) * 64), 4, aoff[i],
-                                             c * 16 * ldw * 4, 0, 0);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {                       // nw <= 16 (windows up to 5 x 5)
-    const int j = wave + i * kWaves;
-    if (j < nw)                                       // uniform
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(dr, (lds_void *)(s + XS + AS + j * 64), 4,
-                                               (c * 16 * KK + j * 64 + lane) * 4, 0, 0, 0);
-  }
-}
+// Where a split SEPCONV tile keeps pixel px of its B operand: every second run
+// of 16 shifted by one, so that writes of every second pixel spread over twice
+// the LDS banks.
+__device__ __forceinline__ int sep_slot(int px) { return px ^ ((px >> 4) & 1); }
 
-// s_waitcnt vmcnt(n) for a uniform run-time n <= MAX.
-template <int MAX>
-__device__ __forceinline__ void wait_vmcnt_upto(int n) {
-  if constexpr (MAX > 0) {
-    if (n >= MAX) { wait_vmcnt<MAX>(); return; }
-    wait_vmcnt_upto<MAX - 1>(n);
-  } else {
-    wait_vmcnt<0>();
-  }
-}
-
-// Depthwise outputs of one (channel, strip of 2 output columns) for RG
-// output rows, from its staged plane (rows with the window's halo, columns
-// with a zero halo of pw on each side: no column test), the input ReLU
-// applied as each value is read; written to the B operand (row ch, column
-// r Wo + col), zeros for a channel past Cin.
-template <int K, int RG>
-__device__ __forceinline__ void sepg_dw(const float *xp, const float *w, float *brow, int W2, int Wo, int col0, int rt,
-                                        bool relu_in, bool cv) {
-  float d[RG][2];
-#pragma unroll
-  for (int o = 0; o < RG; ++o) d[o][0] = d[o][1] = 0.f;
-#pragma unroll
-  for (int i = 0; i < RG + K - 1; ++i) {             // staged input row i feeds output rows i - K + 1 .. i
-    float x[K + 1];
-#pragma unroll
-    for (int j = 0; j <= K; ++j) {
-      const float v = xp[i * W2 + j];
-      x[j] = relu_in ? relu1(v) : v;
-    }
-#pragma unroll
-    for (int o = 0; o < RG; ++o) {
-      const int u = i - o;
-      if (u < 0 || u >= K) continue;                  // compile time
-#pragma unroll
-      for (int v = 0; v < K; ++v) {
-        d[o][0] = fmaf(w[u * K + v], x[v], d[o][0]);
-        d[o][1] = fmaf(w[u * K + v], x[v + 1], d[o][1]);
-      }
-    }
-  }
-#pragma unroll
-  for (int o = 0; o < RG; ++o)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-      if (o < rt && col0 + j < Wo) brow[o * Wo + col0 + j] = cv ? d[o][j] : 0.f;
-}
-
-// "Relu-SepConv" unit, GEMM tile: RG whole output rows of one image
-// (BM = 32 WMW MFMA columns, RG Wo <= BM) x BN = 32 WNW output channels, 8
-// waves of one 32x32 block each on v_mfma_f32_32x32x2_f32 (output channels
-// as rows, pixels as columns).  The pointwise reduction runs over chunks of
-// 16 input channels; per chunk
-//   stage  direct global -> LDS loads, kSepgStages - 1 chunks in flight, of
-//          the chunk's input planes (the tile's rows with the window's halo,
-//          rows and columns outside the image as 0: one plane of
-//          sepg_w2 = W + 2 pw columns per channel, pitch sepg_ps), its
-//          depthwise weights and its pointwise weights [16 k][BN];
-//   dw     every (channel, strip of 2 output columns) of the chunk over the
-//          tile's rows -> the B operand [16 k][BM] in LDS (two buffers);
-//   mfma   D[32 ch][32 px] += A[32 ch][2 k] B[2 k][32 px], 8 k-pairs, A
-//          from the slot (read into registers a round early), B from the
-//          depthwise results of the round before.
-// One barrier per round: round c runs the depthwise of chunk c and the
-// MFMAs of chunk c - 1; half the waves of each SIMD take the MFMAs first,
-// the other half the depthwise, so that the SIMD's vector ALU works while
-// the matrix core does.  B columns past RG Wo are never stored.
-template <int WMW, int K, int RG, bool COH>
-__device__ __forceinline__ void sep_gemm_tile(const Slots &sl, const DevOp &op, const DevOp &o, int t, float *lds) {
-  constexpr int WNW = kWaves / WMW, BM = 32 * WMW, BN = 32 * WNW, D = kSepgStages, KK = K * K;
-  constexpr int BMP = BM + 1;                        // B row pitch: the 16 channel rows on distinct banks
-  constexpr int AC = 16 * BN / 64 / kWaves;          // 64-float pointwise-weight copies per wave
-  static_assert(D == 3, "slot of chunk c + 2 = slot of chunk c - 1");
-  const int tid = threadIdx.x, lane = tid & 63;
+// "Relu-SepConv" unit, split tile (one input, 3 x 3 or 5 x 5 windows that keep
+// the plane size): up to BM = 32 WM output pixels (of one image, or flattened
+// over the batch where images are small) x BN = 96 (8 / WM) output channels.  The pointwise products run
+// on the bf16 matrix cores in fp32 accuracy like the split conv tiles' (three
+// bf16 parts per operand, six products); per chunk of 16 input channels
+//   stage  the patch of input rows that the windows read (SplitGeom positions),
+//          rectified, to LDS, by 16-byte loads: a thread keeps one piece of a
+//          row and its loads differ by a scalar offset only; the pointwise
+//          weights by direct loads to LDS, shared by the pixel blocks' waves;
+//   dw     the depthwise filter in fp32: a wave has two channels, a lane one
+//          pixel or, of 128, two neighbours that share their windows' reads where no pair of the
+//          wave lies across a row's end; the results' three parts are the B
+//          operand [part][half][px];
+//   mfma   wave (wm, wg) multiplies pixel block wm with the channel blocks wg,
+//          wg + 8 / WM, ... (at most three): every channel of a unit of up to BN
+//          shares one depthwise pass.
+// Two barriers per chunk; the patch and the weights are loaded a chunk ahead
+// (one workgroup per CU).
+// The five small products of a chunk are summed on their own before they are
+// added, so an output is rounded twice per chunk at its full size.  Bound by
+// the depthwise pass (K K multiply-adds and half as many LDS reads per
+// output).  NASNet cell at batch 6, 168 channels at 42 x 42: the
+// stage of four units took 239 us on the tile before this one (fp32 MFMA,
+// planes copied to LDS float by float, the depthwise pass once per 64 output
+// channels).
+template <int WM, int K, bool COH>
+__device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op, const SplitDesc &o, int t, float *lds) {
+  constexpr int BM = 32 * WM, WG = kWaves / WM, KK = K * K, NBW = kSepSplitBlocks;
+  constexpr int XL = 16 * kSepSplitPieces / kThreads;  // 16-byte loads per thread and chunk at most
+  constexpr int AB = NBW * WG;                         // channel blocks of the tile
+  static_assert(kSplitCK == 2 * kWaves, "two channels of a chunk per wave");
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave % WMW, wn = wave / WMW;
+  const int wm = wave % WM, wg = wave / WM;
   const int tm = fdiv(t, o.fd_tn), tn = t - tm * o.tiles_n;
-  const int img = fdiv(tm, o.fd_pimg), rb = tm - img * o.tiles_per_plane;
-  const int Wo = o.Wo, W = o.W, H = o.H, howo = o.Ho * Wo, W2 = o.sepg_w2;
-  const int oh0 = rb * RG, rt = min(RG, o.Ho - oh0);                // rows of this tile
-  const int R = o.sep_rows, PS = o.sepg_ps, ih0 = oh0 - o.ph;       // staged rows, plane pitch
-  const int n0 = tn * BN, nck = o.sep_nck, ldw = o.pipe_ldw;
-  const int XS = o.sepg_xs, AS = 16 * BN, WS = o.sepg_ws;            // floats per slot part
-  const int SLOT = XS + AS + WS;
-  float *ring = lds, *bsm = lds + D * SLOT;
-  const int nx = XS >> 6, nw = WS >> 6;              // 64-float copies per slot part
+  // pixels m0 .. m0 + cnt - 1: of one image where an image has o.lwm tiles, of
+  // the flattened batch (lwm = 0) otherwise
+  const int b0 = tn * (NBW * WG), nblk = (o.Cout + 31) >> 5, nch = o.nch;
+  const int ti = o.lwm ? fdiv(tm, o.fd_taps) : 0;
+  const int m0 = ti * o.howo + (tm - ti * o.lwm) * o.sc, cnt = min(o.sc, (o.lwm ? (ti + 1) * o.howo : o.M) - m0);
+  const int Wo = o.Wo, Ho = o.Ho, howo = o.howo, H = o.H, W = o.W, Cin = o.Cin, W2 = o.w2, hv = o.hv;
+  const int PP = o.pp, hw4 = H * W * 4;
+  float *xs = lds;                                     // [16][PP]
+  char *bop = (char *)lds + 64 * PP;                   // [part][half][BM] x 16 bytes
+  char *aop = bop + 96 * BM;                           // two slots of [block][part][lane] x 16 bytes
+  uint32_t *flags = (uint32_t *)((char *)lds + o.tail);
+  float *biasl = (float *)((char *)lds + o.tail + kSplitTail);
+  const __amdgpu_buffer_rsrc_t xr = rsrc(sl[o.in_slot], o.in_bytes);
+  const __amdgpu_buffer_rsrc_t wr = rsrc(o.w, o.w_bytes);
+  if (tid < 3) flags[tid] = 0;
+  if (tid < 32 * NBW * WG) biasl[tid] = bld(rsrc(o.bias, o.Cout * 4), (b0 * 32 + tid) * 4, 0);
 
-  // per-lane offsets of this wave's copies of the input planes: element
-  // e = 64 j + lane of the slot is channel e / PS, staged row (e % PS) / W2,
-  // plane column (e % PS) % W2 = image column + pw; elements past a plane's
-  // R W2 floats, rows and columns outside the image read 0; the chunk's
-  // first channel is added per chunk
-  const int cbase = img * o.in_ctot[0] + o.in_coff[0];
-  int xoff[kSepgMaxCopies];
-#pragma unroll
-  for (int i = 0; i < kSepgMaxCopies; ++i) {
-    const int e = (wave + i * kWaves) * 64 + lane;
-    const int ch = fdiv(e, o.fd_ps), rem = e - ch * PS, r = fdiv(rem, o.fd_w2), col = rem - r * W2 - o.pw;
-    const int ih = ih0 + r;
-    xoff[i] = rem < R * W2 && ih >= 0 && ih < H && col >= 0 && col < W ? (((cbase + ch) * H + ih) * W + col) * 4
-                                                                        : kOOB;
+  const int g0 = fdiv(m0, o.fd_wo), i0 = fdiv(g0, o.fd_ho), vlo = i0 * hv + g0 - i0 * Ho;
+  // staging: this thread's piece of four columns (the last of a row ends with
+  // it), and the channels cw + j cstep of a chunk; rows outside the image and
+  // the columns around it stay the zeros written here
+  for (int i = tid; i < 4 * PP; i += kThreads) *(floatx4 *)(xs + 4 * i) = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int lq = o.raw, e = tid & ((1 << lq) - 1), cw = __builtin_amdgcn_readfirstlane(tid >> lq);
+  const int cstep = kThreads >> lq, nld = 1 << (lq - 5);
+  int off = kOOB, dst = 0;
+  {
+    const int r = fdiv(e, o.fd_pp), v = vlo + r, img = fdiv(v, o.fd_hv), ih = v - img * hv - o.ph;
+    const int col = min(4 * (e - r * ((W + 3) >> 2)), W - 4);
+    if (r < o.taps && img < o.N && ih >= 0 && ih < H) {
+      off = (((img * o.in_ctot + o.in_coff) * H + ih) * W + col) * 4;
+      dst = r * W2 + o.pw + col;
+    }
   }
-  // pointwise weights of the slot: element f = k BN + col of [16 k][BN]
-  int aoff[AC];
-#pragma unroll
-  for (int i = 0; i < AC; ++i) {
-    const int f = (wave * AC + i) * 64 + lane;
-    aoff[i] = ((f / BN) * ldw + n0 + f % BN) * 4;
-  }
-  const __amdgpu_buffer_rsrc_t xr = rsrc(sl[o.in_slot[0]], o.in_bytes[0]);
-  const __amdgpu_buffer_rsrc_t wr = rsrc(o.wpk, o.w_bytes);
-  const __amdgpu_buffer_rsrc_t dr = rsrc(o.dw, o.dw_bytes);
-  const int hw4 = H * W * 4;
-  const float bl = bias32_load(o.bias, n0 + wn * 32, o.Cout, lane);
-  // loads per wave and chunk (the same for every chunk)
-  int per = AC;
-#pragma unroll
-  for (int i = 0; i < kSepgMaxCopies; ++i) per += wave + i * kWaves < nx;
-  per += (wave < nw) + (wave + kWaves < nw);
-  per = __builtin_amdgcn_readfirstlane(per);
-
-  // depthwise items: (channel ch, strip of columns 2 st, 2 st + 1)
-  const int ch = tid & 15, strips = o.sepg_strips;
   const bool relu_in = o.pre_relu != 0;
-  const bool mfma_first = (wave >> 2) & 1;           // waves w and w + 4 share a SIMD
-
-  floatx16 acc;
+  floatx4 x[XL];
+  auto issue = [&](int c) {
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-  float avc[8];                                      // A of the chunk whose MFMAs run next
-#pragma unroll
-  for (int p = 0; p < 8; ++p) avc[p] = 0.f;
-  sepg_issue<kSepgMaxCopies, AC>(ring, xr, wr, dr, xoff, aoff, 0, nx, nw, XS, AS, hw4, ldw, KK, wave, lane);
-  if (nck > 1)
-    sepg_issue<kSepgMaxCopies, AC>(ring + SLOT, xr, wr, dr, xoff, aoff, 1, nx, nw, XS, AS, hw4, ldw, KK, wave, lane);
-  for (int c = 0; c <= nck; ++c) {
-    // chunk c has landed once only chunk c + 1's loads (if any) are in
-    // flight; the barrier publishes every wave's loads and the depthwise
-    // results of round c - 1, and guarantees that round c - 1 no longer
-    // reads chunk c - 1's slot (its A is in registers) or the B buffer that
-    // round c writes
-    if (c + 1 < nck) wait_vmcnt_upto<kSepgMaxCopies + 4 + 2>(per);
-    else wait_vmcnt<0>();
-    ring_barrier();
-    if (c + 2 < nck)
-      sepg_issue<kSepgMaxCopies, AC>(ring + ((c + 2) % D) * SLOT, xr, wr, dr, xoff, aoff, c + 2, nx, nw, XS, AS, hw4,
-                                     ldw, KK, wave, lane);
-    const float *s = ring + (c % D) * SLOT;
-    float avn[8];
-    if (c < nck) {
-      const float *a = s + XS + (lane >> 5) * BN + wn * 32 + (lane & 31);
-#pragma unroll
-      for (int p = 0; p < 8; ++p) avn[p] = a[2 * p * BN];
+    for (int j = 0; j < XL; ++j) {
+      x[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+      const int ch = c * kSplitCK + cw + j * cstep;    // uniform
+      if (j < nld) x[j] = bld4(xr, ch < Cin ? off : kOOB, ch * hw4);
     }
+  };
+  auto store = [&]() {
+    if (off != kOOB)
 #pragma unroll
-    for (int ph = 0; ph < 2; ++ph) {
-      if ((ph == 0) == mfma_first) {
-        if (c >= 1) {                                 // MFMAs of chunk c - 1
-          const float *b = bsm + ((c - 1) & 1) * 16 * BMP + (lane >> 5) * BMP + wm * 32 + (lane & 31);
-          float bv[8];
+      for (int j = 0; j < XL; ++j)
+        if (j < nld) {
+          float *to = xs + (cw + j * cstep) * PP + dst;
 #pragma unroll
-          for (int p = 0; p < 8; ++p) bv[p] = b[2 * p * BMP];
-#pragma unroll
-          for (int p = 0; p < 8; ++p) acc = mfma32x32x2(avc[p], bv[p], acc);
+          for (int i = 0; i < 4; ++i) to[i] = relu_in ? relu1(x[j][i]) : x[j][i];
         }
-      } else if (c < nck) {                           // depthwise of chunk c
-        const bool cv = c * 16 + ch < o.Cin;          // channels past Cin (last chunk): zeros
-        float *brow = bsm + (c & 1) * 16 * BMP + ch * BMP;
-        float w[KK];
-        const float *wp = s + XS + AS + ch * KK;
+  };
+  // depthwise: this wave's channels of a chunk, 2 wave and 2 wave + 1, at this
+  // lane's pixels: PX = 2 neighbours (BM = 128) or one; their windows' first
+  // positions
+  constexpr int PX = BM / 64;
+  int dpos[PX];
+  const int px0 = min(lane * PX, (cnt - 1) & ~(PX - 1));   // lanes past the tile repeat its last pixel or pair
 #pragma unroll
-        for (int i = 0; i < KK; ++i) w[i] = wp[i];
-        for (int st = tid >> 4; st < strips; st += kThreads / 16)
-          sepg_dw<K, RG>(s + ch * PS + 2 * st, w, brow, W2, Wo, 2 * st, rt, relu_in, cv);
-      }
-    }
-#pragma unroll
-    for (int p = 0; p < 8; ++p) avc[p] = c < nck ? avn[p] : 0.f;
+  for (int i = 0; i < PX; ++i) {
+    const int m = m0 + px0 + i, gr = fdiv(m, o.fd_wo), img = fdiv(gr, o.fd_ho);
+    dpos[i] = (img * hv + gr - img * Ho - vlo) * W2 + m - gr * Wo;
+    if (i && px0 + i >= cnt) dpos[i] = dpos[0] + 1;    // a pair's half past the end: computed, never used
   }
-  // epilogue: element i of lane l is channel n0 + 32 wn + 8 (i/4) + 4 (l/32) + i%4 of tile column 32 wm + l%32
-  const int px = wm * 32 + (lane & 31);
-  float bv16[16];
+  // where no pair of the wave lies across a row's end (and pairs start at even
+  // positions), 8-byte reads serve both windows; 4-byte ones of every second
+  // float would meet in the same LDS banks
+  const bool joined = PX == 2 && !__ballot(dpos[PX - 1] != dpos[0] + 1 || (dpos[0] & 1)) && !(W2 & 1);
+  // a channel's filter: tap i in lane i, a chunk ahead
+  constexpr int KKP = (KK + 3) & ~3;
+  float *wl = biasl + 32 * AB;                         // [16][KKP]
+  const __amdgpu_buffer_rsrc_t dr = rsrc(U(op.dw), nch * kSplitCK * KK * 4);
+  float wv[2];
+  auto filters = [&](int c) {
 #pragma unroll
-  for (int i = 0; i < 16; ++i) bv16[i] = bias32_of(bl, i, lane);
-  if (px < rt * Wo) {
-    const int q = oh0 * Wo + px;
+    for (int q = 0; q < 2; ++q)
+      wv[q] = bld(dr, lane < KK ? lane * 4 : kOOB, (min(c, nch - 1) * kSplitCK + 2 * wave + q) * KK * 4);
+  };
+  int32_t pmax = 0;                                    // largest bits of the depthwise results (see conv_split_tile)
+  uint32_t umax = 0;
+  // the pointwise weights of chunk c straight to LDS slot c % 2: 1 KB (block,
+  // part) pieces, the waves in turn (blocks past the last are not read)
+  auto weights = [&](int c) {
+    const int n = min(AB, nblk - b0) * 3;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int n = n0 + wn * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-      if (n < o.Cout) {
-        float v = acc[i] + bv16[i];
-        if (o.post_relu) v = fmaxf(v, 0.f);
-        st<COH>(route_ptr(sl, op, o, n, img, q, howo), v);
-      }
+    for (int i = 0; i < (3 * AB + kWaves - 1) / kWaves; ++i) {
+      const int f = wave + i * kWaves, bl = f / 3;     // uniform
+      if (f < n)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_void *)(aop + (c & 1) * (AB * 3072) + f * 1024), 16, lane * 16,
+                                                 ((b0 + bl) * nch + c) * (kSplitWords * 4) + (f - 3 * bl) * 1024, 0, 0);
     }
-  }
-}
+  };
 
-// GEMM SEPCONV tile variants: waves along pixels (sep_nbt), window, rows per tile.
-template <int WMW, int K, bool COH>
-__device__ __forceinline__ void sep_gemm_rows(const Slots &sl, const DevOp &op, const DevOp &o, int t, float *lds) {
-  switch (o.sepg_rout) {
-    case 2: sep_gemm_tile<WMW, K, 2, COH>(sl, op, o, t, lds); break;
-    case 3: sep_gemm_tile<WMW, K, 3, COH>(sl, op, o, t, lds); break;
-    default: sep_gemm_tile<WMW, K, 4, COH>(sl, op, o, t, lds); break;
+  floatx16 acc[NBW];
+#pragma unroll
+  for (int i = 0; i < NBW; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+  filters(0);
+  issue(0);
+  weights(0);
+  ring_barrier();                                      // the zeros are written
+  store();
+  if (nch > 1) issue(1);
+  ring_barrier();
+  for (int c = 0; c < nch; ++c) {
+    float d[PX][2];
+    // the filters through this wave's own LDS words: every lane reads every tap
+    float wt[2][KKP];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (lane < KK) wl[(2 * wave + q) * KKP + lane] = wv[q];
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int i = 0; i < KKP; i += 4) {
+        const floatx4 f = *(const floatx4 *)(wl + (2 * wave + q) * KKP + i);
+        wt[q][i] = f.x; wt[q][i + 1] = f.y; wt[q][i + 2] = f.z; wt[q][i + 3] = f.w;
+      }
+    auto tap = [&](int q, int i) { return wt[q][i]; };
+    const float *xp = xs + 2 * wave * PP;
+    if (joined) {
+      // both channels' windows in registers before the first product: one LDS round trip
+      float2 r[2][K][(K + 1) / 2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int u = 0; u < K; ++u)
+#pragma unroll
+          for (int v = 0; v < (K + 1) / 2; ++v) r[q][u][v] = *(const float2 *)(xp + q * PP + dpos[0] + u * W2 + 2 * v);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        d[0][q] = d[PX - 1][q] = 0.f;
+#pragma unroll
+        for (int u = 0; u < K; ++u)
+#pragma unroll
+          for (int v = 0; v < K; ++v) {
+            const float w = tap(q, u * K + v);
+            const float2 f = r[q][u][v / 2], g = r[q][u][(v + 1) / 2];
+            d[0][q] = fmaf(w, v & 1 ? f.y : f.x, d[0][q]);
+            d[PX - 1][q] = fmaf(w, v & 1 ? g.x : g.y, d[PX - 1][q]);
+          }
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        float r[PX][K][K];
+#pragma unroll
+        for (int i = 0; i < PX; ++i)
+#pragma unroll
+          for (int u = 0; u < K; ++u)
+#pragma unroll
+            for (int v = 0; v < K; ++v) r[i][u][v] = xp[q * PP + dpos[i] + u * W2 + v];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < PX; ++i) d[i][q] = 0.f;
+#pragma unroll
+        for (int u = 0; u < K; ++u)
+#pragma unroll
+          for (int v = 0; v < K; ++v)
+#pragma unroll
+            for (int i = 0; i < PX; ++i) d[i][q] = fmaf(tap(q, u * K + v), r[i][u][v], d[i][q]);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int i = 0; i < PX; ++i)
+        if (px0 + i < cnt) {
+          pmax = max(pmax, __builtin_bit_cast(int32_t, d[i][q]));
+          umax = max(umax, __builtin_bit_cast(uint32_t, d[i][q]));
+        }
+    filters(c + 1);
+    // the three parts: two bf16 of the 16 bytes of (part, half, px)
+#pragma unroll
+    for (int i = 0; i < PX; ++i) {
+      char *to = bop + (((wave >> 2) * BM + sep_slot(lane * PX + i)) * 16 + (wave & 3) * 4);
+      float v0 = d[i][0], v1 = d[i][1];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const uint32_t h = bf16_pair(v0, v1);
+        *(uint32_t *)(to + k * 32 * BM) = h;
+        v0 -= __builtin_bit_cast(float, h << 16);
+        v1 -= __builtin_bit_cast(float, h & 0xFFFF0000u);
+      }
+    }
+    wait_vmcnt<0>();                                   // this wave's weights of the chunk (and the next patch) have landed
+    ring_barrier();                                    // the patch is no longer read, both operands are there
+    if (c + 1 < nch) {
+      store();
+      weights(c + 1);                                  // in flight during the products and the next depthwise pass
+    }
+    if (c + 2 < nch) issue(c + 2);
+    uintx4 b[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) b[k] = *(const uintx4 *)(bop + ((k * 2 + half) * BM + sep_slot(wm * 32 + l32)) * 16);
+#pragma unroll
+    for (int i = 0; i < NBW; ++i) {
+      if (b0 + wg + i * WG < nblk) {                   // uniform
+        const char *al = aop + (c & 1) * (AB * 3072) + (wg + i * WG) * 3072 + lane * 16;
+        const uintx4 a[3] = {*(const uintx4 *)al, *(const uintx4 *)(al + 1024), *(const uintx4 *)(al + 2048)};
+        floatx16 sm;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sm[r] = 0.f;
+        acc[i] = mfma32x32x16(a[0], b[0], acc[i]);
+        sm = mfma32x32x16(a[0], b[1], sm);
+        sm = mfma32x32x16(a[1], b[0], sm);
+        sm = mfma32x32x16(a[1], b[1], sm);
+        sm = mfma32x32x16(a[0], b[2], sm);
+        sm = mfma32x32x16(a[2], b[0], sm);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] += sm[r];
+      }
+    }
+    ring_barrier();                                    // the next patch is there, the B operand is no longer read
   }
-}
-template <bool COH>
-__device__ __forceinline__ void sep_gemm_dispatch(const Slots &sl, const DevOp &op, const DevOp &o, int t, float *lds) {
-  if (o.sep_nbt == 4) {
-    if (o.kh == 3) sep_gemm_rows<4, 3, COH>(sl, op, o, t, lds); else sep_gemm_rows<4, 5, COH>(sl, op, o, t, lds);
-  } else {
-    if (o.kh == 3) sep_gemm_rows<2, 3, COH>(sl, op, o, t, lds); else sep_gemm_rows<2, 5, COH>(sl, op, o, t, lds);
+  // the tile's range check
+  const uint32_t vmax = max((uint32_t)pmax, umax & 0x7FFFFFFFu);
+  if (__ballot(vmax >= kSplitHi) && lane == 0) atomicOr(&flags[0], 1u);
+  if (__ballot(vmax >= kSplitLo) && lane == 0) atomicOr(&flags[1], 1u);
+  if (__ballot(vmax != 0) && lane == 0) atomicOr(&flags[2], 1u);
+  ring_barrier();
+  const bool post = o.post_relu != 0;
+  float *const out0 = sl[o.route_slot];
+  const int rctot = o.route_ctot, rcoff = o.route_coff;
+  if (__builtin_amdgcn_readfirstlane((int)(flags[0] | (flags[2] & ~flags[1])))) {
+    // out of range: plain fp32, one thread per output
+    const float *xp = sl[o.in_slot], *dwp = U(op.dw);
+    const int NG = U(op.NG);
+    for (int idx = tid; idx < BM * 32 * NBW * WG; idx += kThreads) {
+      const int p = idx & (BM - 1), nl = idx / BM, n = b0 * 32 + nl, m = m0 + p;
+      if (p >= cnt || n >= o.Cout) continue;
+      const int gr = fdiv(m, o.fd_wo), ow = m - gr * Wo, img = fdiv(gr, o.fd_ho), oh = gr - img * Ho;
+      float v = biasl[nl];
+      for (int c = 0; c < Cin; ++c) {
+        const float *pl = xp + (size_t)(img * o.in_ctot + o.in_coff + c) * H * W;
+        float s = 0.f;
+        for (int u = 0; u < K; ++u)
+          for (int q = 0; q < K; ++q) {
+            const int ih = oh - o.ph + u, iw = ow - o.pw + q;
+            if (ih < 0 || ih >= H || iw < 0 || iw >= W) continue;
+            const float xv = pl[(size_t)ih * W + iw];
+            s = fmaf(dwp[c * KK + u * K + q], relu_in ? relu1(xv) : xv, s);
+          }
+        v = fmaf(s, o.w32[(((size_t)(n >> 4) * NG + (c >> 4)) * 64 + (c & 3) * 16 + (n & 15)) * 4 + ((c >> 2) & 3)], v);
+      }
+      if (post) v = fmaxf(v, 0.f);
+      st<COH>(out0 + ((size_t)img * rctot + rcoff + n) * howo + m - img * howo, v);
+    }
+    return;
+  }
+  const int p = wm * 32 + l32, m = m0 + p;
+  if (p < cnt) {
+    const int img = fdiv(m, o.fd_howo), pix = m - img * howo;
+    float *const out = out0 + ((size_t)img * rctot + rcoff) * howo + pix;
+#pragma unroll
+    for (int i = 0; i < NBW; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int nl = (wg + i * WG) * 32 + 8 * (r >> 2) + 4 * half + (r & 3), n = b0 * 32 + nl;
+        if (n < o.Cout) {
+          float v = acc[i][r] + biasl[nl];
+          if (post) v = fmaxf(v, 0.f);
+          st<COH>(out + (size_t)n * howo, v);
+        }
+      }
   }
 }
 
@@ -2065,6 +2128,7 @@ __device__ __forceinline__ void sum_tile(const Slots &sl, const DevOp &op, const
 //   KV_SEPROW  KV_LIGHT + row SEPCONV tiles
 //   KV_PIPE    KV_LIGHT + pipelined conv tiles
 //   KV_SPLIT   KV_LIGHT + split conv tiles
+//   KV_SEPSPLIT KV_LIGHT + split SEPCONV tiles
 //   KV_FULL    every tile kind and conv tile shape
 // A conv tile with the input ReLU and the channel check resolved at compile
 // time (no branch between its loads and MFMAs).
@@ -2114,9 +2178,7 @@ __device__ __forceinline__ void run_tile(const Slots &sl, const DevOp &op, const
       }
     case DK_SEP:
       if constexpr (KV == KV_SEP || KV == KV_SEPROW || KV == KV_FULL) {
-        if (o.sep_row == 2) {
-          if constexpr (KV != KV_SEPROW) sep_gemm_dispatch<COH>(sl, op, o, ti, lds);
-        } else if (!o.sep_row) {
+        if (!o.sep_row) {
           if constexpr (KV != KV_SEPROW) sep_tile<COH>(sl, op, o, ti, lds);
         } else if constexpr (KV != KV_SEP) {
           if (o.sep_row == 3) {
@@ -2192,19 +2254,33 @@ __device__ __forceinline__ void tile_body(const StageArgs &a, const Slots &sl, c
   if (signal) tile_signal(a, opi);
 }
 
-// The same for a split tile.
-template <bool COH>
+// The same for a split tile (the variants hold the conv's, the SEPCONV's or both).
+template <bool COH, int KV>
 __device__ __forceinline__ void run_split(const Slots &sl, const DevOp &op, const SplitDesc &d, int ti, float *lds) {
-  if (tile_is_split_pb2(U(op.tcfg))) conv_split_tile<2, COH>(sl, op, d, ti, lds);
-  else conv_split_tile<1, COH>(sl, op, d, ti, lds);
+  if constexpr (KV != KV_SPLIT) {
+    if (KV == KV_SEPSPLIT || U(op.kind) == DK_SEP) {
+      const bool wide = U(op.sep_nbt) == 4, k3 = d.kh == 3;   // 32 sep_nbt pixels
+      if (wide) {
+        if (k3) sep_split_tile<4, 3, COH>(sl, op, d, ti, lds); else sep_split_tile<4, 5, COH>(sl, op, d, ti, lds);
+      } else {
+        if (k3) sep_split_tile<2, 3, COH>(sl, op, d, ti, lds); else sep_split_tile<2, 5, COH>(sl, op, d, ti, lds);
+      }
+      return;
+    }
+  }
+  if constexpr (KV != KV_SEPSPLIT) {
+    if (tile_is_split_pb2(U(op.tcfg))) conv_split_tile<2, COH>(sl, op, d, ti, lds);
+    else conv_split_tile<1, COH>(sl, op, d, ti, lds);
+  }
 }
+template <int KV>
 __device__ __forceinline__ void split_body(const StageArgs &a, const Slots &sl, const DevOp *ops, const DevOp &op,
                                            int opi, int ti, float *lds) {
   const SplitDesc d = split_desc(op.sp);
   const int n_deps = U(op.n_deps), signal = U(op.signal);
   if (n_deps) tile_wait(a, ops, op, n_deps);
-  if (n_deps || signal) run_split<true>(sl, op, d, ti, lds);
-  else run_split<false>(sl, op, d, ti, lds);
+  if (n_deps || signal) run_split<true, KV>(sl, op, d, ti, lds);
+  else run_split<false, KV>(sl, op, d, ti, lds);
   if (signal) tile_signal(a, opi);
 }
 
@@ -2234,13 +2310,13 @@ __device__ __forceinline__ void process_tile(const StageArgs &a, const Slots &sl
   // each field where it is used with scalar loads from the table in global
   // memory (read-only while the kernel runs, a uniform address).  The split
   // tiles have a descriptor of their own.
-  if constexpr (KV == KV_SPLIT || KV == KV_FULL) {
-    if (U(op.kind) == DK_CONV && U(op.tcfg) >= TC_S256x64) {
-      split_body(a, sl, ops, op, opi, ti, lds);
+  if constexpr (KV == KV_SPLIT || KV == KV_SEPSPLIT || KV == KV_FULL) {
+    if (op_is_split(U(op.kind), U(op.tcfg), U(op.sep_row))) {
+      split_body<KV>(a, sl, ops, op, opi, ti, lds);
       return;
     }
   }
-  if constexpr (KV == KV_LIGHT || KV == KV_PIPE || KV == KV_SPLIT) {
+  if constexpr (KV == KV_LIGHT || KV == KV_PIPE || KV == KV_SPLIT || KV == KV_SEPSPLIT) {
     const DevOp o = op_scalars(op);
     tile_body<KV>(a, sl, ops, op, o, opi, ti, lds);
   } else {
@@ -2345,11 +2421,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
   stage_body<KV, PERSIST>(table, table_words, a);
 }
 
-// The split variant: two workgroups per CU.
-template <bool PERSIST>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PERSIST ? 1 : 4))) void ios_split_kernel(
+// The split variants (KV_SPLIT, KV_SEPSPLIT): two workgroups per CU.
+template <int KV, bool PERSIST>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PERSIST ? 1 : KV == KV_SEPSPLIT ? 2 : 4))) void ios_split_kernel(
     const int4 *__restrict__ table, int table_words, StageArgs a) {
-  stage_body<KV_SPLIT, PERSIST>(table, table_words, a);
+  stage_body<KV, PERSIST>(table, table_words, a);
 }
 
 }  // namespace ios

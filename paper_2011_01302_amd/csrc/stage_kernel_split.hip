@@ -5,10 +5,10 @@
 
 namespace ios {
 
-void *stage_kernel_fn_split() { return (void *)ios_split_kernel<false>; }
+void *stage_kernel_fn_split() { return (void *)ios_split_kernel<KV_SPLIT, false>; }
 
 hipError_t stage_launch_split(const int4 *t, int words, const StageArgs &a, int grid, int lds, hipStream_t s) {
-  hipLaunchKernelGGL((ios_split_kernel<false>), dim3(grid), dim3(kThreads), lds, s, t, words, a);
+  hipLaunchKernelGGL((ios_split_kernel<KV_SPLIT, false>), dim3(grid), dim3(kThreads), lds, s, t, words, a);
   return hipGetLastError();
 }
 

@@ -5,10 +5,10 @@
 
 namespace ios {
 
-void *stage_kernel_fn_split_persist() { return (void *)ios_split_kernel<true>; }
+void *stage_kernel_fn_split_persist() { return (void *)ios_split_kernel<KV_SPLIT, true>; }
 
 hipError_t stage_launch_split_persist(const int4 *t, int words, const StageArgs &a, int grid, int lds, hipStream_t s) {
-  hipLaunchKernelGGL((ios_split_kernel<true>), dim3(grid), dim3(kThreads), lds, s, t, words, a);
+  hipLaunchKernelGGL((ios_split_kernel<KV_SPLIT, true>), dim3(grid), dim3(kThreads), lds, s, t, words, a);
   return hipGetLastError();
 }
 

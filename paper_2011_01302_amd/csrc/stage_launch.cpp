@@ -26,6 +26,10 @@ void *stage_kernel_fn_split();
 hipError_t stage_launch_split(const int4 *t, int words, const StageArgs &a, int grid, int lds, hipStream_t s);
 void *stage_kernel_fn_split_persist();
 hipError_t stage_launch_split_persist(const int4 *t, int words, const StageArgs &a, int grid, int lds, hipStream_t s);
+void *stage_kernel_fn_sepsplit();
+hipError_t stage_launch_sepsplit(const int4 *t, int words, const StageArgs &a, int grid, int lds, hipStream_t s);
+void *stage_kernel_fn_sepsplit_persist();
+hipError_t stage_launch_sepsplit_persist(const int4 *t, int words, const StageArgs &a, int grid, int lds, hipStream_t s);
 void *stage_kernel_fn_full();
 hipError_t stage_launch_full(const int4 *t, int words, const StageArgs &a, int grid, int lds, hipStream_t s);
 void *stage_kernel_fn_full_persist();
@@ -39,8 +43,7 @@ int op_lds_bytes(const DevOp &op) {
     TileShape s = tile_shape(op.tcfg);
     return s.wk * tile_bn(op.tcfg) * (tile_bm(op.tcfg) + 1) * (int)sizeof(float);
   }
-  if (op.kind == DK_SEP && op.sep_row == 2)
-    return sepg_lds_bytes(op.sepg_xs, op.sepg_ws, 32 * op.sep_nbt, 32 * (kWaves / op.sep_nbt));
+  if (op.kind == DK_SEP && op.sep_row == 2) return sep_split_geometry(op.sep_nbt == 4 ? 0 : 1, op.N, op.kh, op.Ho, op.Wo).lds;
   if (op.kind == DK_SEP && op.sep_row == 3) {
     LineGeom g;
     g.r = op.line_r; g.rows = op.line_rows; g.q = op.line_q; g.chp = op.line_chp; g.nks = op.line_nks;
@@ -65,6 +68,7 @@ static void *kernel_of(int variant, bool persist) {
     case KV_SEPROW: return persist ? stage_kernel_fn_seprow_persist() : stage_kernel_fn_seprow();
     case KV_PIPE: return persist ? stage_kernel_fn_pipe_persist() : stage_kernel_fn_pipe();
     case KV_SPLIT: return persist ? stage_kernel_fn_split_persist() : stage_kernel_fn_split();
+    case KV_SEPSPLIT: return persist ? stage_kernel_fn_sepsplit_persist() : stage_kernel_fn_sepsplit();
     default: return persist ? stage_kernel_fn_full_persist() : stage_kernel_fn_full();
   }
 }
@@ -108,6 +112,9 @@ hipError_t launch_stage(const int32_t *table, int table_words, const StageArgs &
     case KV_SPLIT:
       return persistent ? stage_launch_split_persist(t, w, args, grid, lds_bytes, stream)
                         : stage_launch_split(t, w, args, grid, lds_bytes, stream);
+    case KV_SEPSPLIT:
+      return persistent ? stage_launch_sepsplit_persist(t, w, args, grid, lds_bytes, stream)
+                        : stage_launch_sepsplit(t, w, args, grid, lds_bytes, stream);
     default:
       return persistent ? stage_launch_full_persist(t, w, args, grid, lds_bytes, stream)
                         : stage_launch_full(t, w, args, grid, lds_bytes, stream);

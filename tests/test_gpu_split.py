@@ -146,6 +146,70 @@ def test_split_values_out_of_range(scale, monkeypatch):
     g.close()
 
 
+SEP_CASES = {
+    # batch, c, h, w, cout, window: rows odd and even, tiles within and across images, tails, several channel groups
+    "even rows, last tile short": (1, 20, 6, 42, 40, 5),
+    "odd rows": (2, 17, 11, 13, 70, 3),
+    "tiles across images": (5, 33, 5, 6, 31, 5),
+    "one row per image": (3, 16, 1, 8, 32, 3),
+    "more than 192 channels": (1, 40, 8, 12, 400, 3),
+    "rows of four": (2, 18, 9, 4, 33, 5),
+    "rows of three": (2, 18, 9, 3, 33, 3),
+    "odd pixel count": (1, 48, 13, 13, 64, 5),
+}
+
+
+@pytest.mark.parametrize("name", list(SEP_CASES))
+def test_sep_split(name, monkeypatch):
+    """SEPCONV choices 7 and 8.  A depthwise value errs by at most (k k + 1)
+    2^-24 of its terms' magnitudes, the pointwise sum as a conv's."""
+    n, c, h, w, cout, k = SEP_CASES[name]
+    rng = np.random.default_rng(c * 100 + k)
+    x = rng.standard_normal((n, c, h, w)).astype(np.float32)
+    dw = (rng.standard_normal((c, 1, k, k)) / k).astype(np.float32)
+    pw = (rng.standard_normal((cout, c, 1, 1)) / c ** 0.5).astype(np.float32)
+    b = rng.standard_normal(cout).astype(np.float32)
+    check_sep(monkeypatch, x, dw, pw, b, k)
+
+
+@pytest.mark.parametrize("scale", [1e-38, 1e-20, 1e25, "inf", "nan"])
+def test_sep_split_values_out_of_range(scale, monkeypatch):
+    rng = np.random.default_rng(5)
+    x = rng.standard_normal((2, 20, 9, 10)).astype(np.float32)
+    if scale == "inf":
+        x[1, 7, 4, 4] = np.inf
+    elif scale == "nan":
+        x[0, 3, 0, 8] = np.nan          # the input ReLU takes a NaN to 0
+    else:
+        x = (x * np.float32(scale)).astype(np.float32)
+    dw = (rng.standard_normal((20, 1, 3, 3)) / 3).astype(np.float32)
+    pw = (rng.standard_normal((33, 20, 1, 1)) / 5).astype(np.float32)
+    check_sep(monkeypatch, x, dw, pw, np.zeros(33, np.float32), 3)
+
+
+def check_sep(monkeypatch, x, dw, pw, b, k):
+    n, c, h, w = x.shape
+    cout = pw.shape[0]
+    op = {"name": "a", "kind": "sepconv", "in": ["x"], "cout": cout, "kh": k, "kw": k, "sh": 1, "sw": 1, "ph": k // 2,
+          "pw": k // 2, "pre_relu": 1, "post_relu": 0}
+    monkeypatch.setenv("IOS_SEP_TILE", "0")
+    g = graph(monkeypatch, n, c, h, w, [op], {"a.dw": dw, "a.pw": pw, "a.b": b})
+    r = np.where(np.isnan(x), 0, np.maximum(x, 0)).astype(np.float64)
+    d = E.depthwise(r, dw, (k // 2, k // 2))
+    da = E.depthwise(np.where(np.isinf(r), 0, r), np.abs(dw), (k // 2, k // 2))
+    with np.errstate(invalid="ignore"):
+        ref = E.conv2d(d, pw, b)
+    bound = (c + k * k + 9) * 2.0 ** -24 * E.conv2d(da, np.abs(pw), np.abs(b)) + c * k * k * 2.0 ** -149
+    fine = np.isfinite(ref)
+    for t in (7, 8)[:1 if 2 * w > 64 else 2]:          # choice 8 holds two rows in 64 pixels
+        I.ios_set_unit_tiling(g.handle, g.tid["a"], t, -1)
+        got, = launch(g, [[g.tid["a"]]], [I.IOS_CONCURRENT], x, [op], h, w)
+        assert np.array_equal(np.isnan(got), np.isnan(ref)), t
+        assert np.array_equal(got[~fine & ~np.isnan(ref)], ref[~fine & ~np.isnan(ref)]), t
+        assert np.all(np.abs(got - ref)[fine] <= bound[fine]), (t, float((np.abs(got - ref)[fine] / bound[fine]).max()))
+    g.close()
+
+
 def test_split_refused_for_weights_out_of_range():
     """Weights that are not finite, above 2^40 or all below 2^-30: no split shape."""
     for v in (np.inf, np.nan, 2.0 ** 41, 2.0 ** -31):
