@@ -279,7 +279,7 @@ int ios_schedule_from_stages(ios_graph *g, int32_t n_stages, const int32_t *stag
 static constexpr double kStageTileSlack = 0.02;
 // A value whose stage is slower than the best by more than this in a few
 // launches is not measured in full.
-static constexpr double kStageScreen = 1.15;
+static constexpr double kStageScreen = 1.25;
 
 int ios_schedule_tune_tiles(ios_graph *g, ios_schedule_t *q, const ios_sched_opts *opts,
                             int64_t *cost_ns) {

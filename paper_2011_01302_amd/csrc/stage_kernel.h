@@ -695,7 +695,9 @@ constexpr uint32_t kSplitHi = (127u + 70u) << 23, kSplitLo = (127u - 40u) << 23;
 // product costs 6/16 of an fp32 one.  x1 w1 has an accumulator of its own, the
 // five small products another (added at the end): the large one is rounded
 // once per 16 channels and tap.  The 2-norm error against 64 bits is below the
-// fp32 tiles' at every size measured.
+// fp32 tiles' at every size measured (4e-8 .. 3e-7 against 6e-8 .. 8e-7).
+// 3 x 3, 32 -> 128 channels, 55 x 55, batch 32: 50 us, 142 TFLOP/s (the best
+// fp32 tile 76 us); 5 x 5, 48 -> 64, 35 x 35, batch 16: 30 us (49 us).
 //
 // BM = 32 PB WM output pixels (flattened over the batch) x BN = 32 WN output
 // channels; wave (wm, wn, wk) owns PB blocks of 32 pixels, one of 32 channels
@@ -1684,10 +1686,10 @@ __device__ __forceinline__ int sep_slot(int px) { return px ^ ((px >> 4) & 1); }
 // The five small products of a chunk are summed on their own before they are
 // added, so an output is rounded twice per chunk at its full size.  Bound by
 // the depthwise pass (K K multiply-adds and half as many LDS reads per
-// output).  NASNet cell at batch 6, 168 channels at 42 x 42: the
-// stage of four units took 239 us on the tile before this one (fp32 MFMA,
-// planes copied to LDS float by float, the depthwise pass once per 64 output
-// channels).
+// output) and its barriers.  168 channels at 42 x 42, batch 6: a 5 x 5 unit 36
+// us, 3 x 3 29 us (70 and 58 us on the best other tile); the NASNet cell 428 ->
+// 223 us against the tile before this one (fp32 MFMA, planes copied to LDS
+// float by float, the depthwise pass once per 64 output channels).
 template <int WM, int K, bool COH>
 __device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op, const SplitDesc &o, int t, float *lds) {
   constexpr int BM = 32 * WM, WG = kWaves / WM, KK = K * K, NBW = kSepSplitBlocks;
