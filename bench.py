@@ -227,6 +227,11 @@ def load_trace(workload, sha):
     return {k: d.get(k) for k in ("mean_ns", "mean_period_ns", "median_gap_ns", "frac_from_trace")}
 
 
+def _is_stage(kernel):
+    """A stage launch: the stage kernel, or its variants that hold split tiles."""
+    return "ios_stage_kernel" in kernel or "ios_split_kernel" in kernel
+
+
 def _pmc_rows(d, counter):
     import csv
     import glob
@@ -248,8 +253,8 @@ def write_traffic(args, fetch_dir, write_dir, out_dir=None):
     res = {}
     for counter, d in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
         rows = _pmc_rows(d, counter)
-        copy = [v for _, k, v in rows if "ios_stage_kernel" not in k][-1]
-        stage = [v for _, k, v in rows if "ios_stage_kernel" in k]
+        copy = [v for _, k, v in rows if not _is_stage(k)][-1]
+        stage = [v for _, k, v in rows if _is_stage(k)]
         meta = json.load(open(os.path.join(d, "bench.json")))
         n = meta["steps"] * meta["stages"]
         timed = stage[-n:]
@@ -281,12 +286,13 @@ def write_mfma(args, d, out_dir=None):
     MFMA flops (2 x MAC of the convolutions as defined).  The excess is the
     padding the kernel multiplies by zero: output channels to multiples of 16,
     input channels to multiples of 4 and the reduction to multiples of 16,
-    pixel rows of the last M-tile, and the zero taps of merged kernels."""
+    pixel rows of the last M-tile, and the zero taps of merged kernels.
+    Products of split tiles run on bf16 and are not in these counters."""
     import workloads as W
     meta = json.load(open(os.path.join(d, "bench.json")))
     ns, steps = meta["stages"], meta["steps"]
-    mops = [v for _, k, v in _pmc_rows(d, "SQ_INSTS_VALU_MFMA_MOPS_F32") if "ios_stage_kernel" in k][-steps * ns:]
-    inst = [v for _, k, v in _pmc_rows(d, "SQ_INSTS_VALU_MFMA_F32") if "ios_stage_kernel" in k][-steps * ns:]
+    mops = [v for _, k, v in _pmc_rows(d, "SQ_INSTS_VALU_MFMA_MOPS_F32") if _is_stage(k)][-steps * ns:]
+    inst = [v for _, k, v in _pmc_rows(d, "SQ_INSTS_VALU_MFMA_F32") if _is_stage(k)][-steps * ns:]
     spec, _ = W.make(args.config, args.batch, args.seed)
     work = unit_work(spec, args.batch)
     rows = []
@@ -325,7 +331,7 @@ def write_occupancy(args, ios_dir, seq_dir, out_dir=None):
         info = _pmc_info(d)
         meta = json.load(open(os.path.join(d, "bench.json")))
         ns = meta["stages"]
-        timed = [(i, v) for i, k, v in occ if "ios_stage_kernel" in k][-meta["steps"] * ns:]
+        timed = [(i, v) for i, k, v in occ if _is_stage(k)][-meta["steps"] * ns:]
         w = sum(act[i] for i, _ in timed)
         stages = []
         for k in range(ns):
@@ -371,7 +377,7 @@ def trace_summary(args, trace_dir, out_dir=None):
     rows = []
     for f in glob.glob(os.path.join(trace_dir, "**", "*kernel_trace.csv"), recursive=True):
         for r in csv.DictReader(open(f)):
-            if "ios_stage_kernel" in r["Kernel_Name"]:
+            if _is_stage(r["Kernel_Name"]):
                 rows.append((int(r["Start_Timestamp"]), int(r["End_Timestamp"]), int(r.get("Grid_Size_X") or r.get("Grid_Size")) // 512))
     rows.sort()
     meta = json.load(open(os.path.join(trace_dir, "bench.json")))
