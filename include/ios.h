@@ -176,7 +176,7 @@ int ios_profile_stage(ios_graph *g, const int32_t *unit_ids, int32_t n, int32_t 
  * merged window has more taps falls back to 16x32; then 256x64, 128x128,
  * 128x64, 64x64, 128x32, 64x32, 32x64 and 32x32 with both operands split into
  * three bf16 parts whose products are summed in fp32, for convs whose weights
- * are finite, at most 2^40 and not all below 2^-30 in magnitude, and whose
+ * are 0 or 2^-110 .. 2^40 in magnitude and not all below 2^-30, and whose
  * input rows fit a workgroup's LDS).  A new shape applies to stages compiled
  * afterwards (ios_profile_stage, ios_schedule, ios_schedule_from_stages),
  * not to schedules that already exist.  Both calls set up the device first

@@ -211,12 +211,14 @@ void pack_conv_pipe(const float *w, int cout, int cin, int kh, int kw, std::vect
 }
 
 bool split_weights_ok(const float *w, size_t n) {
-  float m = 0.f;
+  float hi = 0.f, lo = 1.f;      // largest and smallest magnitude, zeros aside
   for (size_t i = 0; i < n; ++i) {
     if (!std::isfinite(w[i])) return false;
-    m = std::max(m, std::fabs(w[i]));
+    const float a = std::fabs(w[i]);
+    hi = std::max(hi, a);
+    if (a > 0.f) lo = std::min(lo, a);
   }
-  return m == 0.f || (m <= 0x1p40f && m >= 0x1p-30f);
+  return hi == 0.f || (hi <= 0x1p40f && hi >= 0x1p-30f && lo >= 0x1p-110f);
 }
 
 SplitGeom split_geometry(int cfg, int N, int cin, int cout, int H, int W, int Ho, int Wo, int kh, int kw, int sh,

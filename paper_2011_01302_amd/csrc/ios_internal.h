@@ -158,7 +158,7 @@ inline bool pipe_conv_ok(int cin, int taps, int pre_relu) {
 // pixel (gather).  ok = false: the patch does not fit.
 constexpr int kSplitCK = 16;
 constexpr int kSplitPosBytes = 96;
-constexpr int kSplitTail = 256;              // LDS bytes of the range flags, before the biases
+constexpr int kSplitTail = 256;              // LDS bytes of the range flag, before the biases
 constexpr int kSplitLdsShared = 74 * 1024;   // two workgroups per CU, the stage tables included
 constexpr int kSplitLdsAlone = 140 * 1024;   // one workgroup per CU (the stage table comes on top)
 constexpr int kSplitWords = 768;             // words of packed weights per (32 channels, 16 input channels, tap)
@@ -168,9 +168,10 @@ struct SplitGeom {
 };
 SplitGeom split_geometry(int cfg, int N, int cin, int cout, int H, int W, int Ho, int Wo, int kh, int kw, int sh,
                          int sw);
-// Whether every weight is finite and in the range where the three bf16 parts
-// of both operands and the partial sums keep every bit that matters (see the
-// stage kernel's range check of the activations).
+// Whether the split tiles take these weights: every one is 0 or at least 2^-110
+// (its three parts add up to it, see the stage kernel's range check of the
+// activations) and at most 2^40 (no sum passes the largest number), and not
+// all are below 2^-30.
 bool split_weights_ok(const float *w, size_t n);
 
 // SEPCONV tile: BM = 16 << tile consecutive output pixels of one image x

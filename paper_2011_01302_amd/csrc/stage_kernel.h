@@ -664,8 +664,9 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{a, b}, bf16x2));
 }
 
-// Eight values as three bf16 parts each, v = p[0] + p[1] + p[2] but for at
-// most 2^-27 of it (every part is the nearest bf16 to what is left of v).
+// Eight values as three bf16 parts each, v = p[0] + p[1] + p[2] exactly (every
+// part is the nearest bf16 to what is left of v: 8 of its 24 bits) where v is 0
+// or at least kSplitLo.
 __device__ __forceinline__ void split3(const float (&v)[8], uintx4 (&p)[3]) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -680,12 +681,28 @@ __device__ __forceinline__ void split3(const float (&v)[8], uintx4 (&p)[3]) {
   }
 }
 
-// The range of magnitudes in which the products of the bf16 parts and their
-// sums lose nothing (with the weights' range, see split_weights_ok: no part
-// below the smallest normal number that matters, no sum past the largest), as
-// magnitude bits.  A tile whose largest input lies outside, or that holds an
-// infinity or a NaN, is computed in fp32 instead.
-constexpr uint32_t kSplitHi = (127u + 70u) << 23, kSplitLo = (127u - 40u) << 23;
+// The magnitudes that the split tiles take, as bits: 0, and 2^-110 <= |v| <
+// 2^70.  The last bit of such a value is at least 2^-133, the spacing of the
+// smallest bf16 numbers (which the conversion and the matrix cores keep), so
+// its three parts add up to it; and no sum of products with weights up to 2^40
+// passes the largest number.  Every value is checked: in a tile that holds
+// one other value, an infinity or a NaN, the sums are computed from the fp32
+// values instead.  The weights' range is checked once (split_weights_ok).
+constexpr uint32_t kSplitHi = (127u + 70u) << 23, kSplitLo = (127u - 110u) << 23;
+struct SplitRange {
+  int32_t pos = 0;                                     // largest bits as signed and as unsigned numbers: of the
+  uint32_t any = 0;                                    // positive values, and of the negative ones if there are any
+  uint32_t low = ~0u;                                  // smallest of 2 |bits| - 1, which takes 0 to the top
+  __device__ __forceinline__ void add(float v) {
+    const uint32_t b = __builtin_bit_cast(uint32_t, v);
+    pos = max(pos, (int32_t)b);
+    any = max(any, b);
+    low = min(low, 2 * b - 1);
+  }
+  __device__ __forceinline__ bool out() const {
+    return max((uint32_t)pos, any & 0x7FFFFFFFu) >= kSplitHi || low < 2 * kSplitLo - 1;
+  }
+};
 
 // Implicit-GEMM convolution tile on the bf16 matrix cores, in fp32 accuracy:
 // every operand is split into three bf16 parts (x = x1 + x2 + x3, 24 bits),
@@ -733,7 +750,7 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
   const __amdgpu_buffer_rsrc_t xr = rsrc(sl[o.in_slot], o.in_bytes);
   const __amdgpu_buffer_rsrc_t wr = rsrc(o.w, o.w_bytes);
 
-  if (tid < 3) flags[tid] = 0;
+  if (tid == 0) *flags = 0;
   const float bias = tid < BN ? bld(rsrc(o.bias, o.Cout * 4), (n0 + tid) * 4, 0) : 0.f;
 
   // this wave's weights: block nb of 32 channels (clamped: columns past Cout
@@ -779,8 +796,7 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
   // e / PP.  A wave takes elements 64 (wave + 8 i) + lane, SB such items at
   // once.
   const bool relu_in = o.pre_relu != 0;
-  int32_t pmax = 0;                                    // largest bits of the values staged by this thread, as
-  uint32_t umax = 0;                                   // signed and as unsigned numbers
+  SplitRange range;                                    // of the values staged by this thread
   auto stage = [&](int c0) {
     const int n64 = min(SC, nch - c0) * 2 * PP, cb = c0 * kSplitCK;
 #pragma unroll 1
@@ -809,8 +825,7 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
           if (relu_in) x[i][j] = relu1(x[i][j]);
-          pmax = max(pmax, __builtin_bit_cast(int32_t, x[i][j]));
-          umax = max(umax, __builtin_bit_cast(uint32_t, x[i][j]));
+          range.add(x[i][j]);
         }
         uintx4 q[3];
         split3(x[i], q);
@@ -881,10 +896,7 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
   }
 
   // the tile's range check
-  const uint32_t vmax = max((uint32_t)pmax, umax & 0x7FFFFFFFu);
-  if (__ballot(vmax >= kSplitHi) && lane == 0) atomicOr(&flags[0], 1u);
-  if (__ballot(vmax >= kSplitLo) && lane == 0) atomicOr(&flags[1], 1u);
-  if (__ballot(vmax != 0) && lane == 0) atomicOr(&flags[2], 1u);
+  if (__ballot(range.out()) && lane == 0) *flags = 1;
   float *red = lds;                                   // [wk][block][16][64]
   const int nblk = (PB << lwm) << lwn;
   if (WK > 1) {
@@ -907,7 +919,7 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
     return sl.p[op.route_slot[r]] +
            ((size_t)img * op.route_ctot[r] + op.route_coff[r] + (n - op.route_n0[r])) * howo + pix;
   };
-  if (__builtin_amdgcn_readfirstlane((int)(flags[0] | (flags[2] & ~flags[1])))) {
+  if (__builtin_amdgcn_readfirstlane((int)*flags)) {
     // out of range: plain fp32, one thread per output
     const int spt = U(op.CinP) >> 2, lbm = 31 - __builtin_clz(BM), NG = U(op.NG);
     const float *xp = sl[o.in_slot];
@@ -1714,7 +1726,7 @@ __device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op,
   float *biasl = (float *)((char *)lds + o.tail + kSplitTail);
   const __amdgpu_buffer_rsrc_t xr = rsrc(sl[o.in_slot], o.in_bytes);
   const __amdgpu_buffer_rsrc_t wr = rsrc(o.w, o.w_bytes);
-  if (tid < 3) flags[tid] = 0;
+  if (tid == 0) *flags = 0;
   if (tid < 32 * NBW * WG) biasl[tid] = bld(rsrc(o.bias, o.Cout * 4), (b0 * 32 + tid) * 4, 0);
 
   const int g0 = fdiv(m0, o.fd_wo), i0 = fdiv(g0, o.fd_ho), vlo = i0 * hv + g0 - i0 * Ho;
@@ -1779,8 +1791,7 @@ __device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op,
     for (int q = 0; q < 2; ++q)
       wv[q] = bld(dr, lane < KK ? lane * 4 : kOOB, (min(c, nch - 1) * kSplitCK + 2 * wave + q) * KK * 4);
   };
-  int32_t pmax = 0;                                    // largest bits of the depthwise results (see conv_split_tile)
-  uint32_t umax = 0;
+  SplitRange range;                                    // of this thread's depthwise results
   // the pointwise weights of chunk c straight to LDS slot c % 2: 1 KB (block,
   // part) pieces, the waves in turn (blocks past the last are not read)
   auto weights = [&](int c) {
@@ -1871,10 +1882,7 @@ __device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op,
     for (int q = 0; q < 2; ++q)
 #pragma unroll
       for (int i = 0; i < PX; ++i)
-        if (px0 + i < cnt) {
-          pmax = max(pmax, __builtin_bit_cast(int32_t, d[i][q]));
-          umax = max(umax, __builtin_bit_cast(uint32_t, d[i][q]));
-        }
+        if (px0 + i < cnt) range.add(d[i][q]);
     filters(c + 1);
     // the three parts: two bf16 of the 16 bytes of (part, half, px)
 #pragma unroll
@@ -1920,15 +1928,12 @@ __device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op,
     ring_barrier();                                    // the next patch is there, the B operand is no longer read
   }
   // the tile's range check
-  const uint32_t vmax = max((uint32_t)pmax, umax & 0x7FFFFFFFu);
-  if (__ballot(vmax >= kSplitHi) && lane == 0) atomicOr(&flags[0], 1u);
-  if (__ballot(vmax >= kSplitLo) && lane == 0) atomicOr(&flags[1], 1u);
-  if (__ballot(vmax != 0) && lane == 0) atomicOr(&flags[2], 1u);
+  if (__ballot(range.out()) && lane == 0) *flags = 1;
   ring_barrier();
   const bool post = o.post_relu != 0;
   float *const out0 = sl[o.route_slot];
   const int rctot = o.route_ctot, rcoff = o.route_coff;
-  if (__builtin_amdgcn_readfirstlane((int)(flags[0] | (flags[2] & ~flags[1])))) {
+  if (__builtin_amdgcn_readfirstlane((int)*flags)) {
     // out of range: plain fp32, one thread per output
     const float *xp = sl[o.in_slot], *dwp = U(op.dw);
     const int NG = U(op.NG);

@@ -146,6 +146,35 @@ def test_split_values_out_of_range(scale, monkeypatch):
     g.close()
 
 
+def mixed(rng, shape, scale):
+    """Ordinary values, the first rows of the first image scaled: tiles that
+    hold both, and windows that hold the scaled ones only."""
+    x = rng.standard_normal(shape).astype(np.float32)
+    x[0, :, :5] *= np.float32(scale)
+    return x
+
+
+@pytest.mark.parametrize("scale", [1e-31, 1e-36, 1e-40, 1e22])
+def test_split_mixed_magnitudes(scale, monkeypatch):
+    """A region of tiny (or huge) values beside ordinary ones in one tile: its
+    outputs keep the bound of their own terms, a few steps of 2^-149 apart (six
+    products a term, each rounded there)."""
+    rng = np.random.default_rng(11)
+    x = mixed(rng, (2, 20, 9, 9), scale)
+    wt = (rng.standard_normal((40, 20, 3, 3)) * 0.1).astype(np.float32)
+    wt[3, 5] = 0
+    b = np.zeros(40, np.float32)
+    ops = [conv_op("a", 40, (3, 3), (1, 1))]
+    g = graph(monkeypatch, 2, 20, 9, 9, ops, {"a.w": wt, "a.b": b})
+    ref, bound = reference(x, wt, b, ops[0])
+    bound = bound + 6 * 180 * 2.0 ** -149
+    for t in SPLIT:
+        I.ios_set_conv_tile(g.handle, g.tid["a"], t)
+        got, = launch(g, [[g.tid["a"]]], [I.IOS_CONCURRENT], x, ops, 9, 9)
+        assert np.all(np.abs(got - ref) <= bound), (scale, t, float((np.abs(got - ref) / bound).max()))
+    g.close()
+
+
 SEP_CASES = {
     # batch, c, h, w, cout, window: rows odd and even, tiles within and across images, tails, several channel groups
     "even rows, last tile short": (1, 20, 6, 42, 40, 5),
@@ -187,6 +216,25 @@ def test_sep_split_values_out_of_range(scale, monkeypatch):
     check_sep(monkeypatch, x, dw, pw, np.zeros(33, np.float32), 3)
 
 
+@pytest.mark.parametrize("scale", [1e-31, 1e-36, 1e22])
+def test_sep_split_mixed_magnitudes(scale, monkeypatch):
+    rng = np.random.default_rng(13)
+    x = mixed(rng, (2, 20, 9, 10), scale)
+    dw = (rng.standard_normal((20, 1, 3, 3)) / 3).astype(np.float32)
+    pw = (rng.standard_normal((33, 20, 1, 1)) / 5).astype(np.float32)
+    check_sep(monkeypatch, x, dw, pw, np.zeros(33, np.float32), 3)
+
+
+def test_sep_split_tiny_output_channel(monkeypatch):
+    """Pointwise weights out of the parts' range: another tile runs the choice."""
+    rng = np.random.default_rng(17)
+    x = rng.standard_normal((1, 20, 9, 10)).astype(np.float32)
+    dw = (rng.standard_normal((20, 1, 3, 3)) / 3).astype(np.float32)
+    pw = (rng.standard_normal((33, 20, 1, 1)) / 5).astype(np.float32)
+    pw[4] *= np.float32(1e-36)
+    check_sep(monkeypatch, x, dw, pw, np.zeros(33, np.float32), 3)
+
+
 def check_sep(monkeypatch, x, dw, pw, b, k):
     n, c, h, w = x.shape
     cout = pw.shape[0]
@@ -211,9 +259,12 @@ def check_sep(monkeypatch, x, dw, pw, b, k):
 
 
 def test_split_refused_for_weights_out_of_range():
-    """Weights that are not finite, above 2^40 or all below 2^-30: no split shape."""
-    for v in (np.inf, np.nan, 2.0 ** 41, 2.0 ** -31):
+    """Weights that are not finite, above 2^40 or all below 2^-30, and one below
+    2^-110 among ordinary ones: no split shape."""
+    for v in (np.inf, np.nan, 2.0 ** 41, 2.0 ** -31, 2.0 ** -111):
         wt = np.full((8, 16, 3, 3), v, np.float32)
+        if v == 2.0 ** -111:
+            wt[:7] = 0.5
         g = I.Graph({"batch": 1, "inputs": [{"name": "x", "c": 16, "h": 5, "w": 5}],
                      "ops": [conv_op("a", 8, (3, 3), (1, 1))], "outputs": ["a"]},
                     {"a.w": wt, "a.b": np.zeros(8, np.float32)})
