@@ -177,7 +177,9 @@ int ios_profile_stage(ios_graph *g, const int32_t *unit_ids, int32_t n, int32_t 
  * 128x64, 64x64, 128x32, 64x32, 32x64 and 32x32 with both operands split into
  * three bf16 parts whose products are summed in fp32, for convs whose weights
  * are 0 or 2^-110 .. 2^40 in magnitude and not all below 2^-30, and whose
- * input rows fit a workgroup's LDS).  A new shape applies to stages compiled
+ * input rows fit a workgroup's LDS; a tile one of whose inputs is an
+ * infinity, a NaN, at least 2^70 or non-zero below 2^-110 in magnitude runs a
+ * second time with fp32 products).  A new shape applies to stages compiled
  * afterwards (ios_profile_stage, ios_schedule, ios_schedule_from_stages),
  * not to schedules that already exist.  Both calls set up the device first
  * (hence the measurement) if no earlier call has.

@@ -165,18 +165,23 @@ double tile_work(const DevOp &d) {
   }
 }
 
-// `n_copy` > 0: only that many elements are copied.
 template <class T>
-void grow_upload(T **dptr, size_t *cap, const std::vector<T> &v, bool reuse, size_t n_copy = 0) {
-  size_t n = std::max<size_t>(v.size(), 1);
+void grow(T **dptr, size_t *cap, size_t n, bool reuse) {
+  n = std::max<size_t>(n, 1);
   if (!reuse || *cap < n) {
     if (reuse && *dptr) (void)hipFree(*dptr);
+    *dptr = nullptr;
+    *cap = 0;
     hip_check(hipMalloc(dptr, sizeof(T) * n), "hipMalloc(stage)");
     if (reuse) *cap = n;
   }
+}
+
+template <class T>
+void grow_upload(T **dptr, size_t *cap, const std::vector<T> &v, bool reuse) {
+  grow(dptr, cap, v.size(), reuse);
   if (!v.empty())
-    hip_check(hipMemcpy(*dptr, v.data(), sizeof(T) * (n_copy ? n_copy : v.size()), hipMemcpyHostToDevice),
-              "hipMemcpy(stage)");
+    hip_check(hipMemcpy(*dptr, v.data(), sizeof(T) * v.size(), hipMemcpyHostToDevice), "hipMemcpy(stage)");
 }
 
 }  // namespace
@@ -274,14 +279,14 @@ SplitGeom split_geometry(int cfg, int N, int cin, int cout, int H, int W, int Ho
 
 namespace {
 // The split tile's descriptor, from the operator's final fields and sizes.
-void set_split(DevOp &d, const float *w, const float *w32, bool raw) {
+void set_split(DevOp &d, const float *w) {
   const SplitShape s = split_shape(d.tcfg);
   const SplitGeom g = split_geometry(d.tcfg, d.N, d.Cin, d.Cout, d.H, d.W, d.Ho, d.Wo, d.kh, d.kw, d.sh, d.sw);
   if (!g.ok) fail(IOS_E_UNSUPPORTED, "conv split tile does not apply");
   SplitDesc &p = d.sp;
   p.lwm = 31 - __builtin_clz((unsigned)s.wm);
   p.lwn = 31 - __builtin_clz((unsigned)s.wn);
-  p.wk = s.wk;
+  p.wk = s.wk; p.pb = s.pb;
   p.sc = g.sc; p.nch = g.nch; p.np = g.np; p.pp = g.pp;
   p.w2 = g.w2; p.hv = g.hv; p.gather = g.gather; p.tail = g.body;
   p.Ho = d.Ho; p.Wo = d.Wo; p.howo = d.Ho * d.Wo; p.M = d.N * p.howo;
@@ -303,10 +308,10 @@ void set_split(DevOp &d, const float *w, const float *w32, bool raw) {
   p.fd_kw = make_fdiv((uint32_t)d.kw);
   p.fd_w2 = make_fdiv((uint32_t)g.w2);
   p.fd_hv = make_fdiv((uint32_t)g.hv);
-  p.w = w; p.bias = d.bias; p.w32 = w32; p.raw = raw;
+  p.w = w; p.bias = d.bias;
 }
-// The same of a SEPCONV's split tile (the pointwise weights and their fp32 pack).
-void set_sep_split(DevOp &d, const SepSplitGeom &g, const float *w, const float *w32) {
+// The same of a SEPCONV's split tile (w: the pointwise weights).
+void set_sep_split(DevOp &d, const SepSplitGeom &g, const float *w) {
   SplitDesc &p = d.sp;
   p.sc = g.tp; p.lwm = g.per_img;
   p.nch = cdiv(d.Cin, kSplitCK); p.pp = g.pp;
@@ -314,7 +319,7 @@ void set_sep_split(DevOp &d, const SepSplitGeom &g, const float *w, const float 
   p.w2 = g.w2; p.hv = g.hv; p.tail = g.tail;
   p.Ho = d.Ho; p.Wo = d.Wo; p.howo = d.Ho * d.Wo; p.M = d.N * p.howo;
   p.N = d.N; p.H = d.H; p.W = d.W; p.Cin = d.Cin; p.Cout = d.Cout;
-  p.kh = d.kh; p.kw = d.kw; p.taps = g.rows; p.raw = g.lq;
+  p.kh = d.kh; p.kw = d.kw; p.taps = g.rows; p.lq = g.lq;
   p.fd_pp = make_fdiv((uint32_t)((d.W + 3) / 4));
   p.sh = p.sw = 1; p.ph = d.ph; p.pw = d.pw;
   p.in_slot = d.in_slot[0]; p.in_coff = d.in_coff[0]; p.in_ctot = d.in_ctot[0]; p.in_bytes = d.in_bytes[0];
@@ -328,7 +333,7 @@ void set_sep_split(DevOp &d, const SepSplitGeom &g, const float *w, const float 
   p.fd_howo = make_fdiv((uint32_t)p.howo);
   p.fd_w2 = make_fdiv((uint32_t)g.w2);
   p.fd_hv = make_fdiv((uint32_t)g.hv);
-  p.w = w; p.bias = d.bias; p.w32 = w32;
+  p.w = w; p.bias = d.bias;
 }
 }  // namespace
 
@@ -382,7 +387,7 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
   SlotMap sm;
   std::vector<DevOp> dops;
   std::vector<float> mw, mb;
-  size_t wsp_off = 0;            // merge on a split tile: the place of the bf16 parts in mw
+  bool merge_split = false;      // mw holds the raw weights: the split tiles' packing is done on the device
   bool merge_held = false;       // the profiler's stage holds this merge's packed weights already
   if (strategy == IOS_MERGE) {
     if (!stage_mergeable(g, ops)) fail(IOS_E_NOT_MERGEABLE, "stage cannot be merged");
@@ -429,7 +434,6 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
     if (merge_held) {
       d.NG = g->prof_merge_ng;
       nb = g->prof_merge_nb;
-      wsp_off = g->prof_merge_wsp;
     } else {
       // merged kernel [total][cin][KH][KW]: each op's kernel centred, stacked
       // along output channels
@@ -448,10 +452,8 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
         }
       }
       if (layout == 2) {
-        // the fp32 weights as they are, room for the bf16 parts behind them
-        wsp_off = (wm.size() + 63) & ~(size_t)63;
         mw = std::move(wm);
-        mw.resize(wsp_off + split_words(total, o0.cin, KH, KW));
+        merge_split = true;
         nb = round_up(total, 16) / 16;
       } else if (layout == 1) {
         pack_conv_pipe(wm.data(), total, o0.cin, KH, KW, mw, &d.NG);
@@ -468,7 +470,6 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
       g->prof_merge_layout = layout;
       g->prof_merge_ng = d.NG;
       g->prof_merge_nb = nb;
-      g->prof_merge_wsp = wsp_off;
     }
     set_inputs(g, o0, d, sm);
     d.route_n0[d.n_routes] = total;
@@ -502,8 +503,7 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
             if (any_sep || !sg.ok || table_bytes + sg.lds > kMaxLdsBytes) d.tcfg = TC_16x32_K8;
           }
           if (tile_is_split(d.tcfg)) {
-            d.NG = o.NG;
-            set_split(d, o.d_wsp, o.d_wpk, false);
+            set_split(d, o.d_wsp);
           } else if (tile_is_pipe(d.tcfg)) {
             d.NG = o.pipe_nkb;
             d.pipe_ldw = round_up(o.d.cout, 128);
@@ -540,10 +540,10 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
           if (sg2.tp > 0 && table_bytes + sg2.lds <= kMaxLdsBytes) {
             // split tile (see the stage kernel)
             d.kind = DK_SEP; d.sep_row = 2;
-            d.CinP = o.CinP; d.Npad = o.Npad; d.NG = o.NG;
+            d.CinP = o.CinP; d.Npad = o.Npad;
             d.sep_nbt = sg2.bm / 32;
             d.bias = o.d_bias; d.dw = o.d_dw;
-            set_sep_split(d, sg2, o.d_wsp, o.d_wpk);
+            set_sep_split(d, sg2, o.d_wsp);
             break;
           }
           // weights out of the split tiles' range, rows of fewer than four
@@ -756,16 +756,20 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
     size_t *wc = reuse ? &g->prof_w_cap : nullptr, *bc = reuse ? &g->prof_b_cap : nullptr;
     size_t dummy_w = 0, dummy_b = 0;
     if (reuse) g->prof_merge_ops.clear();              // until both are uploaded
-    grow_upload(&cs->d_mw, wc ? wc : &dummy_w, mw, reuse, wsp_off);
-    if (wsp_off)
-      pack_conv_split(cs->d_mw, cs->ops[0].Cout, cs->ops[0].Cin, cs->ops[0].kh, cs->ops[0].kw, cs->d_mw + wsp_off, g->stream);
+    if (merge_split) {
+      const DevOp &d = cs->ops[0];
+      grow(&cs->d_mw, wc ? wc : &dummy_w, split_words(d.Cout, d.Cin, d.kh, d.kw), reuse);
+      pack_conv_split(mw.data(), d.Cout, d.Cin, d.kh, d.kw, cs->d_mw, g->stream);
+    } else {
+      grow_upload(&cs->d_mw, wc ? wc : &dummy_w, mw, reuse);
+    }
     grow_upload(&cs->d_mb, bc ? bc : &dummy_b, mb, reuse);
     if (reuse) g->prof_merge_ops = ops;
   }
   if (!mw.empty() || merge_held) {
     cs->ops[0].wpk = cs->d_mw;
     cs->ops[0].bias = cs->d_mb;
-    if (tile_is_split(cs->ops[0].tcfg)) set_split(cs->ops[0], cs->d_mw + wsp_off, cs->d_mw, true);
+    if (tile_is_split(cs->ops[0].tcfg)) set_split(cs->ops[0], cs->d_mw);
   }
   cs->table.assign(table_words, 0);
   cs->table[0] = n;

@@ -354,14 +354,10 @@ static T *upload(const std::vector<T> &v) {
   return p;
 }
 
-// conv weights w as the split tiles read them, in device memory
-static float *upload_split(ios_graph *g, const std::vector<float> &w, int cout, int cin, int kh, int kw) {
-  float *raw = upload(w), *p = nullptr;
-  const hipError_t e = hipMalloc(&p, split_words(cout, cin, kh, kw) * sizeof(float));
-  if (e == hipSuccess) pack_conv_split(raw, cout, cin, kh, kw, p, g->stream);
-  (void)hipFree(raw);
-  hip_check(e, "hipMalloc(weights)");
-  return p;
+// conv weights w as the split tiles read them, in device memory at *out
+static void upload_split(ios_graph *g, const float *w, int cout, int cin, int kh, int kw, float **out) {
+  hip_check(hipMalloc(out, split_words(cout, cin, kh, kw) * sizeof(float)), "hipMalloc(weights)");
+  pack_conv_split(w, cout, cin, kh, kw, *out, g->stream);
 }
 
 bool conv_tile_ok(const Op &op, int cfg) {
@@ -481,9 +477,7 @@ void ensure_device(ios_graph *g) {
       std::vector<float> wg;
       pack_conv_pipe(op.w.data(), op.d.cout, op.cin, op.d.kh, op.d.kw, wg, &op.pipe_nkb);
       op.d_wg = upload(wg);
-      if (op.split_ok) {
-        op.d_wsp = upload_split(g, op.w, op.d.cout, op.cin, op.d.kh, op.d.kw);
-      }
+      if (op.split_ok) upload_split(g, op.w.data(), op.d.cout, op.cin, op.d.kh, op.d.kw, &op.d_wsp);
     } else if (op.d.kind == IOS_SEPCONV) {
       // depthwise [CinP][kh * kw] (channels past cin zero); pointwise packed
       // like a 1x1 conv's weights (groups of 4 k-steps = 16 input channels)
@@ -498,10 +492,8 @@ void ensure_device(ios_graph *g) {
       op.d_wpk = upload(pwk);
       op.d_bias = upload(bias);
       // the split tile's pointwise parts
-      if (op.split_ok && (sep_tile_ok(op, kSepgFirst) || sep_tile_ok(op, kSepgFirst + 1))) {
-        const std::vector<float> pw(op.w.begin() + (size_t)op.cin * taps, op.w.end());
-        op.d_wsp = upload_split(g, pw, op.d.cout, op.cin, 1, 1);
-      }
+      if (op.split_ok && (sep_tile_ok(op, kSepgFirst) || sep_tile_ok(op, kSepgFirst + 1)))
+        upload_split(g, op.w.data() + (size_t)op.cin * taps, op.d.cout, op.cin, 1, 1, &op.d_wsp);
       // the row tile's layouts, where it applies: depthwise taps at the top
       // left of a K x K window, [CinP4][kkp(K)]; pointwise [CinP4][Npad]
       const int K = sep_row_window(op.d.kh, op.d.kw);

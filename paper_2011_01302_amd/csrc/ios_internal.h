@@ -92,7 +92,6 @@ inline bool tile_is_light(int cfg) { return cfg == TC_16x16_K8 || cfg == TC_16x3
 inline bool tile_is_pipe(int cfg) { return cfg >= TC_P128x64 && cfg < TC_S256x64; }
 inline bool tile_is_wave_ring(int cfg) { return cfg >= TC_W128x64 && cfg < TC_S256x64; }
 inline bool tile_is_split(int cfg) { return cfg >= TC_S256x64 && cfg < TC_COUNT; }
-__host__ __device__ inline bool tile_is_split_pb2(int cfg) { return cfg >= TC_S256x64 && cfg <= TC_S128x32; }
 // split tiles: 8 waves arranged wm (pixels) x wn (channels) x wk (reduction),
 // each with pb blocks of 32 pixels x one block of 32 channels
 struct SplitShape { int pb, wm, wn, wk; };
@@ -108,7 +107,6 @@ inline SplitShape split_shape(int cfg) {
     default: return {1, 1, 1, 8};
   }
 }
-static_assert(TC_S128x32 == TC_S64x64 + 1 && TC_S64x32 == TC_S128x32 + 1, "the tiles with two pixel blocks per wave come first");
 // pipelined tiles: waves along pixels (and kWaves / that along channels)
 inline int pipe_wm(int cfg) {
   const int k = tile_is_wave_ring(cfg) ? cfg - TC_W128x64 : cfg - TC_P128x64;
@@ -359,9 +357,9 @@ inline FDiv make_fdiv(uint32_t d) {
 
 // What a split tile reads of its operator, one word for each lane of a wave
 // (the fields as in DevOp and SplitGeom).
-struct SplitDesc {
+struct alignas(16) SplitDesc {
   int32_t lwm, lwn, wk, sc;    // SplitShape (wm, wn as log2), sub-chunks per round
-  int32_t nch, np, pp, raw;    // sub-chunks in all, positions, rounded up to 32; layout of w32
+  int32_t nch, np, pp, lq;     // sub-chunks in all, positions, rounded up to 32; lq: see SepSplitGeom
   int32_t w2, hv, gather, tail;// patch row length, virtual rows per image, LDS byte offset of flags and biases
   int32_t M, Ho, Wo, howo;     // output pixels of the batch
   int32_t N, H, W, Cin;
@@ -375,15 +373,14 @@ struct SplitDesc {
   FDiv fd_pp, fd_taps;
   FDiv fd_kw, fd_w2;
   FDiv fd_hv;
+  int32_t pb, pad;             // SplitShape: blocks of 32 pixels per wave
   const void *w;               // pack_conv_split
   const float *bias;           // [Npad], at least Cout floats
-  const float *w32;            // the weights in fp32, for values out of range: raw [cout][cin][kh][kw], else
-                               // packed (pack_conv_weights; CinP, NG)
 };
-static_assert(sizeof(SplitDesc) == 256, "one word per lane");
+static_assert(sizeof(SplitDesc) == 256, "one word per lane (some unused)");
 
 // (SEP split tile, see SepSplitGeom: sc = tp, lwm = per_img (fd_taps divides by
-// it), taps = rows, raw = lq; fd_pp divides by the pieces of a row.)
+// it), taps = rows; fd_pp divides by the pieces of a row.)
 
 // Whether an operator (its kind, tcfg and sep_row) runs on a split tile.
 __host__ __device__ inline bool op_is_split(int kind, int tcfg, int sep_row) {
@@ -568,7 +565,6 @@ struct ios_graph {
   // layout (0 direct, 1 pipelined, 2 split) and what packing them returned
   std::vector<int> prof_merge_ops;
   int prof_merge_layout = -1, prof_merge_ng = 0, prof_merge_nb = 0;
-  size_t prof_merge_wsp = 0;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   // ios_run_noalloc: byte offset of each intermediate buffer in the scratch
   // array (counters first), and the bytes the graph needs there
@@ -604,14 +600,14 @@ void noalloc_setup(int device);
 size_t noalloc_counter_bytes();
 
 // pack.hip: conv weights for the split tiles, from w[cout][cin][kh][kw] in
-// device memory: per block of 32 output channels, chunk of 16 input channels
+// host memory: per block of 32 output channels, chunk of 16 input channels
 // and tap, three parts (w = w1 + w2 + w3, each the bf16 nearest to what the
 // parts before it leave) of 64 lanes x 8 bf16, lane l holding output channel
 // l % 32, input channels 8 (l / 32) .. + 7: the A operands of
 // v_mfma_f32_32x32x16_bf16.  Zero past cin and cout; split_words floats.
 // Returns when the packing is done.
 size_t split_words(int cout, int cin, int kh, int kw);
-void pack_conv_split(const float *d_w, int cout, int cin, int kh, int kw, float *d_out, hipStream_t stream);
+void pack_conv_split(const float *w, int cout, int cin, int kh, int kw, float *d_out, hipStream_t stream);
 
 // graph.cpp
 int unit_op_of_tensor(const ios_graph *g, int tensor_id);   // op index or throws

@@ -38,12 +38,21 @@ size_t split_words(int cout, int cin, int kh, int kw) {
   return (size_t)((cout + 31) / 32) * ((cin + kSplitCK - 1) / kSplitCK) * kh * kw * kSplitWords;
 }
 
-void pack_conv_split(const float *d_w, int cout, int cin, int kh, int kw, float *d_out, hipStream_t stream) {
+void pack_conv_split(const float *w, int cout, int cin, int kh, int kw, float *d_out, hipStream_t stream) {
   const int taps = kh * kw, nch = (cin + kSplitCK - 1) / kSplitCK, groups = (cout + 31) / 32 * nch * taps;
-  hipLaunchKernelGGL(pack_split_kernel, dim3((groups + 3) / 4), dim3(256), 0, stream, d_w, cout, cin, taps, nch, groups,
-                     (uintx4 *)d_out);
-  hip_check(hipGetLastError(), "pack_split_kernel");
-  hip_check(hipStreamSynchronize(stream), "hipStreamSynchronize(pack)");
+  const size_t bytes = (size_t)cout * cin * taps * sizeof(float);
+  float *raw = nullptr;
+  hip_check(hipMalloc(&raw, bytes), "hipMalloc(weights)");
+  hipError_t e = hipMemcpy(raw, w, bytes, hipMemcpyHostToDevice);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(pack_split_kernel, dim3((groups + 3) / 4), dim3(256), 0, stream, raw, cout, cin, taps, nch, groups,
+                       (uintx4 *)d_out);
+    e = hipGetLastError();
+    const hipError_t s = hipStreamSynchronize(stream);
+    if (e == hipSuccess) e = s;
+  }
+  (void)hipFree(raw);
+  hip_check(e, "pack_conv_split");
 }
 
 }  // namespace ios

@@ -16,6 +16,7 @@
 // sequentially): a consumer tile waits until every tile of its producers has
 // finished (see stage_body for why the waits always end).
 #pragma once
+#include <type_traits>
 #include <utility>
 
 #include "ios_internal.h"
@@ -681,13 +682,33 @@ __device__ __forceinline__ void split3(const float (&v)[8], uintx4 (&p)[3]) {
   }
 }
 
+// The eight values of which p holds the parts (exact: see split3).
+__device__ __forceinline__ void join3(const uintx4 (&p)[3], float (&v)[8]) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    float t[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      t[k] = __builtin_bit_cast(float, j & 1 ? p[k][j >> 1] & 0xFFFF0000u : p[k][j >> 1] << 16);
+    v[j] = (t[0] + t[1]) + t[2];
+  }
+}
+
+// D += A B as mfma32x32x16, of the fp32 values: lane l holds 8 channels 8 (l / 32) .. + 7 of each operand.
+__device__ __forceinline__ floatx16 mfma32x32x16_f32(const float (&a)[8], floatx4 b0, floatx4 b1, floatx16 c) {
+#pragma unroll
+  for (int j = 0; j < 8; ++j) c = mfma32x32x2(a[j], j < 4 ? b0[j & 3] : b1[j & 3], c);
+  return c;
+}
+
 // The magnitudes that the split tiles take, as bits: 0, and 2^-110 <= |v| <
 // 2^70.  The last bit of such a value is at least 2^-133, the spacing of the
 // smallest bf16 numbers (which the conversion and the matrix cores keep), so
 // its three parts add up to it; and no sum of products with weights up to 2^40
-// passes the largest number.  Every value is checked: in a tile that holds
-// one other value, an infinity or a NaN, the sums are computed from the fp32
-// values instead.  The weights' range is checked once (split_weights_ok).
+// passes the largest number.  Every value is checked: a tile that holds one
+// other value, an infinity or a NaN runs again, with the fp32 values in LDS
+// and products on v_mfma_f32_32x32x2_f32 (the weights put together from their
+// parts).  The weights' range is checked once (split_weights_ok).
 constexpr uint32_t kSplitHi = (127u + 70u) << 23, kSplitLo = (127u - 110u) << 23;
 struct SplitRange {
   int32_t pos = 0;                                     // largest bits as signed and as unsigned numbers: of the
@@ -732,8 +753,8 @@ struct SplitRange {
 // channel's, which the range check does not cover: channels past Cin take
 // kOOB.
 template <int PB, bool COH>
-__device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op, const SplitDesc &o, int t, float *lds) {
-  constexpr int SB = PB == 1 ? 3 : 2;                  // staging items loaded at once
+__device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op, const SplitDesc &o, const float *in, int t,
+                                                float *lds) {
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lwm = o.lwm, lwn = o.lwn, WK = o.wk, WN = 1 << lwn;
@@ -747,7 +768,7 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
   char *lb = (char *)lds;
   uint32_t *flags = (uint32_t *)(lb + o.tail);
   float *biasl = (float *)(lb + o.tail + kSplitTail);
-  const __amdgpu_buffer_rsrc_t xr = rsrc(sl[o.in_slot], o.in_bytes);
+  const __amdgpu_buffer_rsrc_t xr = rsrc(in, o.in_bytes);
   const __amdgpu_buffer_rsrc_t wr = rsrc(o.w, o.w_bytes);
 
   if (tid == 0) *flags = 0;
@@ -797,7 +818,8 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
   // once.
   const bool relu_in = o.pre_relu != 0;
   SplitRange range;                                    // of the values staged by this thread
-  auto stage = [&](int c0) {
+  auto stage = [&](int c0, auto fp32) {
+    constexpr int SB = fp32 ? 1 : PB == 1 ? 3 : 2;     // staging items loaded at once
     const int n64 = min(SC, nch - c0) * 2 * PP, cb = c0 * kSplitCK;
 #pragma unroll 1
     for (int e0 = wave * 64; e0 < n64; e0 += SB * kThreads) {   // uniform
@@ -825,15 +847,20 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
           if (relu_in) x[i][j] = relu1(x[i][j]);
-          range.add(x[i][j]);
+          if constexpr (!fp32) range.add(x[i][j]);
         }
-        uintx4 q[3];
-        split3(x[i], q);
-        // part k of sub-chunk hg / 2, half hg % 2: 16 bytes per position
+        // part k of sub-chunk hg / 2, half hg % 2: 16 bytes per position (fp32: four values in each of two)
         char *d = lb + (e + 4 * (hg[i] >> 1) * PP) * 16;
+        uintx4 q[3];
+        if constexpr (fp32) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) q[j >> 2][j & 3] = __builtin_bit_cast(uint32_t, x[i][j]);
+        } else {
+          split3(x[i], q);
+        }
         if (e < n64)
 #pragma unroll
-          for (int k = 0; k < 3; ++k) *(uintx4 *)(d + k * 2 * PP * 16) = q[k];
+          for (int k = 0; k < (fp32 ? 2 : 3); ++k) *(uintx4 *)(d + k * 2 * PP * 16) = q[k];
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -852,51 +879,65 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
     bpos[pb] = (pos + half * PP) * 16;
   }
   floatx16 big[PB], sml[PB];
-#pragma unroll
-  for (int pb = 0; pb < PB; ++pb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) big[pb][i] = sml[pb][i] = 0.f;
-  auto step = [&](int ks, const uintx4 (&a)[3]) {
+  auto step = [&](int ks, const uintx4 (&a)[3], auto fp32) {
     const int sc = fdiv(ks, o.fd_taps), tap = ks - sc * taps, u = fdiv(tap, o.fd_kw), v = tap - u * kw;
     const char *b0 = lb + (sc * 6 * PP + u * W2 + v) * 16;
+    if constexpr (fp32) {
+      float w[8];
+      join3(a, w);
 #pragma unroll
-    for (int pb = 0; pb < PB; ++pb) {
-      uintx4 b[3];
+      for (int pb = 0; pb < PB; ++pb)
+        big[pb] = mfma32x32x16_f32(w, *(const floatx4 *)(b0 + bpos[pb]), *(const floatx4 *)(b0 + bpos[pb] + 2 * PP * 16),
+                                   big[pb]);
+    } else {
 #pragma unroll
-      for (int k = 0; k < 3; ++k) b[k] = *(const uintx4 *)(b0 + bpos[pb] + k * 2 * PP * 16);
-      big[pb] = mfma32x32x16(a[0], b[0], big[pb]);
-      sml[pb] = mfma32x32x16(a[0], b[1], sml[pb]);
-      sml[pb] = mfma32x32x16(a[1], b[0], sml[pb]);
-      sml[pb] = mfma32x32x16(a[1], b[1], sml[pb]);
-      sml[pb] = mfma32x32x16(a[0], b[2], sml[pb]);
-      sml[pb] = mfma32x32x16(a[2], b[0], sml[pb]);
+      for (int pb = 0; pb < PB; ++pb) {
+        uintx4 b[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) b[k] = *(const uintx4 *)(b0 + bpos[pb] + k * 2 * PP * 16);
+        big[pb] = mfma32x32x16(a[0], b[0], big[pb]);
+        sml[pb] = mfma32x32x16(a[0], b[1], sml[pb]);
+        sml[pb] = mfma32x32x16(a[1], b[0], sml[pb]);
+        sml[pb] = mfma32x32x16(a[1], b[1], sml[pb]);
+        sml[pb] = mfma32x32x16(a[0], b[2], sml[pb]);
+        sml[pb] = mfma32x32x16(a[2], b[0], sml[pb]);
+      }
     }
   };
 
-  for (int c0 = 0;;) {
-    if constexpr (PB == 1) weights(c0, wk, a0);        // the first weights in flight beside the patch
-    stage(c0);
-    if constexpr (PB != 1) weights(c0, wk, a0);
-    if (c0 == 0 && tid < BN) biasl[tid] = bias;
-    ring_barrier();
-    const int nks = min(SC, nch - c0) * taps;
-    for (int ks = wk; ks < nks;) {                     // one k-step of weights in flight
-      weights(c0, ks + WK, a1);
-      __builtin_amdgcn_sched_barrier(0);
-      step(ks, a0);
-      ks += WK;
-      if (ks >= nks) break;
-      weights(c0, ks + WK, a0);
-      __builtin_amdgcn_sched_barrier(0);
-      step(ks, a1);
-      ks += WK;
+  auto rounds = [&](auto fp32) {
+#pragma unroll
+    for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) big[pb][i] = sml[pb][i] = 0.f;
+    for (int c0 = 0;;) {
+      if constexpr (PB == 1 && !fp32) weights(c0, wk, a0);   // the first weights in flight beside the patch
+      stage(c0, fp32);
+      if constexpr (PB != 1 || fp32) weights(c0, wk, a0);
+      if constexpr (!fp32)
+        if (c0 == 0 && tid < BN) biasl[tid] = bias;
+      ring_barrier();
+      const int nks = min(SC, nch - c0) * taps;
+      for (int ks = wk; ks < nks;) {                   // one k-step of weights in flight
+        weights(c0, ks + WK, a1);
+        __builtin_amdgcn_sched_barrier(0);
+        step(ks, a0, fp32);
+        ks += WK;
+        if (ks >= nks) break;
+        weights(c0, ks + WK, a0);
+        __builtin_amdgcn_sched_barrier(0);
+        step(ks, a1, fp32);
+        ks += WK;
+      }
+      ring_barrier();                                  // the patch is no longer read
+      if ((c0 += SC) >= nch) break;
     }
-    ring_barrier();                                    // the patch is no longer read
-    if ((c0 += SC) >= nch) break;
-  }
-
+  };
+  rounds(std::false_type{});
   // the tile's range check
   if (__ballot(range.out()) && lane == 0) *flags = 1;
+  ring_barrier();
+  if (__builtin_amdgcn_readfirstlane((int)*flags)) rounds(std::true_type{});
   float *red = lds;                                   // [wk][block][16][64]
   const int nblk = (PB << lwm) << lwn;
   if (WK > 1) {
@@ -906,8 +947,8 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
 #pragma unroll
       for (int i = 0; i < 16; ++i) red[((wk * nblk + blk) * 16 + i) * 64 + lane] = big[pb][i] + sml[pb][i];
     }
+    ring_barrier();
   }
-  ring_barrier();
   const bool post = o.post_relu != 0;
   // output n of image img, pixel pix (a merged conv has several destinations)
   float *const out0 = sl[o.route_slot];
@@ -919,33 +960,6 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
     return sl.p[op.route_slot[r]] +
            ((size_t)img * op.route_ctot[r] + op.route_coff[r] + (n - op.route_n0[r])) * howo + pix;
   };
-  if (__builtin_amdgcn_readfirstlane((int)*flags)) {
-    // out of range: plain fp32, one thread per output
-    const int spt = U(op.CinP) >> 2, lbm = 31 - __builtin_clz(BM), NG = U(op.NG);
-    const float *xp = sl[o.in_slot];
-    for (int idx = tid; idx < BM * BN; idx += kThreads) {
-      const int m = m0 + (idx & (BM - 1)), nl = idx >> lbm, n = n0 + nl;
-      if (m >= M || n >= o.Cout) continue;
-      const int gr = fdiv(m, o.fd_wo), ow = m - gr * Wo, img = fdiv(gr, o.fd_ho), oh = gr - img * Ho;
-      float v = biasl[nl];
-      for (int u = 0; u < o.kh; ++u)
-        for (int q = 0; q < kw; ++q) {
-          const int ih = oh * o.sh - o.ph + u, iw = ow * o.sw - o.pw + q;
-          if (ih < 0 || ih >= H || iw < 0 || iw >= W) continue;
-          const float *px = xp + ((size_t)(img * o.in_ctot + o.in_coff) * H + ih) * W + iw;
-          for (int c = 0; c < Cin; ++c) {
-            const int tap = u * kw + q, ks = tap * spt + (c >> 2);
-            const float w = o.w32[o.raw ? ((size_t)n * Cin + c) * taps + tap
-                                        : (((size_t)(n >> 4) * NG + (ks >> 2)) * 64 + (c & 3) * 16 + (n & 15)) * 4 + (ks & 3)];
-            const float xv = px[(size_t)c * H * W];
-            v = fmaf(relu_in ? relu1(xv) : xv, w, v);
-          }
-        }
-      if (post) v = fmaxf(v, 0.f);
-      st<COH>(dest(n, img, m - img * howo), v);
-    }
-    return;
-  }
   if (WK == 1) {
     // element r of lane l is channel 8 (r/4) + 4 (l/32) + r%4 of its block, pixel l%32
 #pragma unroll
@@ -983,7 +997,7 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
 // The descriptor of a split tile in scalar registers: word i from lane i (one
 // LDS read), as op_scalars.
 __device__ __forceinline__ SplitDesc split_desc(const SplitDesc &g) {
-  static_assert(sizeof(SplitDesc) == 256, "one word per lane");
+  static_assert(sizeof(SplitDesc) == 256, "one word per lane (some unused)");
   const int v = ((const int *)&g)[threadIdx.x & 63];
   int w[64];
 #pragma unroll
@@ -1703,7 +1717,8 @@ __device__ __forceinline__ int sep_slot(int px) { return px ^ ((px >> 4) & 1); }
 // 223 us against the tile before this one (fp32 MFMA, planes copied to LDS
 // float by float, the depthwise pass once per 64 output channels).
 template <int WM, int K, bool COH>
-__device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op, const SplitDesc &o, int t, float *lds) {
+__device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op, const SplitDesc &o, const float *in, int t,
+                                               float *lds) {
   constexpr int BM = 32 * WM, WG = kWaves / WM, KK = K * K, NBW = kSepSplitBlocks;
   constexpr int XL = 16 * kSepSplitPieces / kThreads;  // 16-byte loads per thread and chunk at most
   constexpr int AB = NBW * WG;                         // channel blocks of the tile
@@ -1724,7 +1739,7 @@ __device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op,
   char *aop = bop + 96 * BM;                           // two slots of [block][part][lane] x 16 bytes
   uint32_t *flags = (uint32_t *)((char *)lds + o.tail);
   float *biasl = (float *)((char *)lds + o.tail + kSplitTail);
-  const __amdgpu_buffer_rsrc_t xr = rsrc(sl[o.in_slot], o.in_bytes);
+  const __amdgpu_buffer_rsrc_t xr = rsrc(in, o.in_bytes);
   const __amdgpu_buffer_rsrc_t wr = rsrc(o.w, o.w_bytes);
   if (tid == 0) *flags = 0;
   if (tid < 32 * NBW * WG) biasl[tid] = bld(rsrc(o.bias, o.Cout * 4), (b0 * 32 + tid) * 4, 0);
@@ -1734,7 +1749,7 @@ __device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op,
   // it), and the channels cw + j cstep of a chunk; rows outside the image and
   // the columns around it stay the zeros written here
   for (int i = tid; i < 4 * PP; i += kThreads) *(floatx4 *)(xs + 4 * i) = floatx4{0.f, 0.f, 0.f, 0.f};
-  const int lq = o.raw, e = tid & ((1 << lq) - 1), cw = __builtin_amdgcn_readfirstlane(tid >> lq);
+  const int lq = o.lq, e = tid & ((1 << lq) - 1), cw = __builtin_amdgcn_readfirstlane(tid >> lq);
   const int cstep = kThreads >> lq, nld = 1 << (lq - 5);
   int off = kOOB, dst = 0;
   {
@@ -1806,159 +1821,150 @@ __device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op,
   };
 
   floatx16 acc[NBW];
+  auto chunks = [&](auto fp32) {
 #pragma unroll
-  for (int i = 0; i < NBW; ++i)
+    for (int i = 0; i < NBW; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
-  filters(0);
-  issue(0);
-  weights(0);
-  ring_barrier();                                      // the zeros are written
-  store();
-  if (nch > 1) issue(1);
-  ring_barrier();
-  for (int c = 0; c < nch; ++c) {
-    float d[PX][2];
-    // the filters through this wave's own LDS words: every lane reads every tap
-    float wt[2][KKP];
+      for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+    filters(0);
+    issue(0);
+    weights(0);
+    ring_barrier();                                      // the zeros are written
+    store();
+    if (nch > 1) issue(1);
+    ring_barrier();
+    for (int c = 0; c < nch; ++c) {
+      float d[PX][2];
+      // the filters through this wave's own LDS words: every lane reads every tap
+      float wt[2][KKP];
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
-      if (lane < KK) wl[(2 * wave + q) * KKP + lane] = wv[q];
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-#pragma unroll
-      for (int i = 0; i < KKP; i += 4) {
-        const floatx4 f = *(const floatx4 *)(wl + (2 * wave + q) * KKP + i);
-        wt[q][i] = f.x; wt[q][i + 1] = f.y; wt[q][i + 2] = f.z; wt[q][i + 3] = f.w;
-      }
-    auto tap = [&](int q, int i) { return wt[q][i]; };
-    const float *xp = xs + 2 * wave * PP;
-    if (joined) {
-      // both channels' windows in registers before the first product: one LDS round trip
-      float2 r[2][K][(K + 1) / 2];
+      for (int q = 0; q < 2; ++q)
+        if (lane < KK) wl[(2 * wave + q) * KKP + lane] = wv[q];
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int u = 0; u < K; ++u)
+        for (int i = 0; i < KKP; i += 4) {
+          const floatx4 f = *(const floatx4 *)(wl + (2 * wave + q) * KKP + i);
+          wt[q][i] = f.x; wt[q][i + 1] = f.y; wt[q][i + 2] = f.z; wt[q][i + 3] = f.w;
+        }
+      auto tap = [&](int q, int i) { return wt[q][i]; };
+      const float *xp = xs + 2 * wave * PP;
+      if (joined) {
+        // both channels' windows in registers before the first product: one LDS round trip
+        float2 r[2][K][(K + 1) / 2];
 #pragma unroll
-          for (int v = 0; v < (K + 1) / 2; ++v) r[q][u][v] = *(const float2 *)(xp + q * PP + dpos[0] + u * W2 + 2 * v);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        d[0][q] = d[PX - 1][q] = 0.f;
-#pragma unroll
-        for (int u = 0; u < K; ++u)
-#pragma unroll
-          for (int v = 0; v < K; ++v) {
-            const float w = tap(q, u * K + v);
-            const float2 f = r[q][u][v / 2], g = r[q][u][(v + 1) / 2];
-            d[0][q] = fmaf(w, v & 1 ? f.y : f.x, d[0][q]);
-            d[PX - 1][q] = fmaf(w, v & 1 ? g.x : g.y, d[PX - 1][q]);
-          }
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        float r[PX][K][K];
-#pragma unroll
-        for (int i = 0; i < PX; ++i)
+        for (int q = 0; q < 2; ++q)
 #pragma unroll
           for (int u = 0; u < K; ++u)
 #pragma unroll
-            for (int v = 0; v < K; ++v) r[i][u][v] = xp[q * PP + dpos[i] + u * W2 + v];
+            for (int v = 0; v < (K + 1) / 2; ++v) r[q][u][v] = *(const float2 *)(xp + q * PP + dpos[0] + u * W2 + 2 * v);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < PX; ++i) d[i][q] = 0.f;
+        for (int q = 0; q < 2; ++q) {
+          d[0][q] = d[PX - 1][q] = 0.f;
 #pragma unroll
-        for (int u = 0; u < K; ++u)
+          for (int u = 0; u < K; ++u)
 #pragma unroll
-          for (int v = 0; v < K; ++v)
+            for (int v = 0; v < K; ++v) {
+              const float w = tap(q, u * K + v);
+              const float2 f = r[q][u][v / 2], g = r[q][u][(v + 1) / 2];
+              d[0][q] = fmaf(w, v & 1 ? f.y : f.x, d[0][q]);
+              d[PX - 1][q] = fmaf(w, v & 1 ? g.x : g.y, d[PX - 1][q]);
+            }
+        }
+      } else {
 #pragma unroll
-            for (int i = 0; i < PX; ++i) d[i][q] = fmaf(tap(q, u * K + v), r[i][u][v], d[i][q]);
+        for (int q = 0; q < 2; ++q) {
+          float r[PX][K][K];
+#pragma unroll
+          for (int i = 0; i < PX; ++i)
+#pragma unroll
+            for (int u = 0; u < K; ++u)
+#pragma unroll
+              for (int v = 0; v < K; ++v) r[i][u][v] = xp[q * PP + dpos[i] + u * W2 + v];
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < PX; ++i) d[i][q] = 0.f;
+#pragma unroll
+          for (int u = 0; u < K; ++u)
+#pragma unroll
+            for (int v = 0; v < K; ++v)
+#pragma unroll
+              for (int i = 0; i < PX; ++i) d[i][q] = fmaf(tap(q, u * K + v), r[i][u][v], d[i][q]);
+        }
       }
-    }
+      if constexpr (!fp32) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
+        for (int q = 0; q < 2; ++q)
 #pragma unroll
-      for (int i = 0; i < PX; ++i)
-        if (px0 + i < cnt) range.add(d[i][q]);
-    filters(c + 1);
-    // the three parts: two bf16 of the 16 bytes of (part, half, px)
-#pragma unroll
-    for (int i = 0; i < PX; ++i) {
-      char *to = bop + (((wave >> 2) * BM + sep_slot(lane * PX + i)) * 16 + (wave & 3) * 4);
-      float v0 = d[i][0], v1 = d[i][1];
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const uint32_t h = bf16_pair(v0, v1);
-        *(uint32_t *)(to + k * 32 * BM) = h;
-        v0 -= __builtin_bit_cast(float, h << 16);
-        v1 -= __builtin_bit_cast(float, h & 0xFFFF0000u);
+          for (int i = 0; i < PX; ++i)
+            if (px0 + i < cnt) range.add(d[i][q]);
       }
-    }
-    wait_vmcnt<0>();                                   // this wave's weights of the chunk (and the next patch) have landed
-    ring_barrier();                                    // the patch is no longer read, both operands are there
-    if (c + 1 < nch) {
-      store();
-      weights(c + 1);                                  // in flight during the products and the next depthwise pass
-    }
-    if (c + 2 < nch) issue(c + 2);
-    uintx4 b[3];
+      filters(c + 1);
+      // the three parts: two bf16 of the 16 bytes of (part, half, px)
 #pragma unroll
-    for (int k = 0; k < 3; ++k) b[k] = *(const uintx4 *)(bop + ((k * 2 + half) * BM + sep_slot(wm * 32 + l32)) * 16);
+      for (int i = 0; i < PX; ++i) {
+        if constexpr (fp32) {                            // four channels in each of two times 16 bytes
+          *(float2 *)(bop + ((((wave & 2) + (wave >> 2)) * BM + sep_slot(lane * PX + i)) * 16 + (wave & 1) * 8)) =
+              float2{d[i][0], d[i][1]};
+          continue;
+        }
+        char *to = bop + (((wave >> 2) * BM + sep_slot(lane * PX + i)) * 16 + (wave & 3) * 4);
+        float v0 = d[i][0], v1 = d[i][1];
 #pragma unroll
-    for (int i = 0; i < NBW; ++i) {
-      if (b0 + wg + i * WG < nblk) {                   // uniform
-        const char *al = aop + (c & 1) * (AB * 3072) + (wg + i * WG) * 3072 + lane * 16;
-        const uintx4 a[3] = {*(const uintx4 *)al, *(const uintx4 *)(al + 1024), *(const uintx4 *)(al + 2048)};
-        floatx16 sm;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sm[r] = 0.f;
-        acc[i] = mfma32x32x16(a[0], b[0], acc[i]);
-        sm = mfma32x32x16(a[0], b[1], sm);
-        sm = mfma32x32x16(a[1], b[0], sm);
-        sm = mfma32x32x16(a[1], b[1], sm);
-        sm = mfma32x32x16(a[0], b[2], sm);
-        sm = mfma32x32x16(a[2], b[0], sm);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] += sm[r];
+        for (int k = 0; k < 3; ++k) {
+          const uint32_t h = bf16_pair(v0, v1);
+          *(uint32_t *)(to + k * 32 * BM) = h;
+          v0 -= __builtin_bit_cast(float, h << 16);
+          v1 -= __builtin_bit_cast(float, h & 0xFFFF0000u);
+        }
       }
+      wait_vmcnt<0>();                                   // this wave's weights of the chunk (and the next patch) have landed
+      ring_barrier();                                    // the patch is no longer read, both operands are there
+      if (c + 1 < nch) {
+        store();
+        weights(c + 1);                                  // in flight during the products and the next depthwise pass
+      }
+      if (c + 2 < nch) issue(c + 2);
+      uintx4 b[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) b[k] = *(const uintx4 *)(bop + ((k * 2 + half) * BM + sep_slot(wm * 32 + l32)) * 16);
+#pragma unroll
+      for (int i = 0; i < NBW; ++i) {
+        if (b0 + wg + i * WG < nblk) {                   // uniform
+          const char *al = aop + (c & 1) * (AB * 3072) + (wg + i * WG) * 3072 + lane * 16;
+          const uintx4 a[3] = {*(const uintx4 *)al, *(const uintx4 *)(al + 1024), *(const uintx4 *)(al + 2048)};
+          if constexpr (fp32) {
+            float w[8];
+            join3(a, w);
+            acc[i] = mfma32x32x16_f32(w, __builtin_bit_cast(floatx4, b[0]), __builtin_bit_cast(floatx4, b[1]), acc[i]);
+            continue;
+          }
+          floatx16 sm;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sm[r] = 0.f;
+          acc[i] = mfma32x32x16(a[0], b[0], acc[i]);
+          sm = mfma32x32x16(a[0], b[1], sm);
+          sm = mfma32x32x16(a[1], b[0], sm);
+          sm = mfma32x32x16(a[1], b[1], sm);
+          sm = mfma32x32x16(a[0], b[2], sm);
+          sm = mfma32x32x16(a[2], b[0], sm);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][r] += sm[r];
+        }
+      }
+      ring_barrier();                                    // the next patch is there, the B operand is no longer read
     }
-    ring_barrier();                                    // the next patch is there, the B operand is no longer read
-  }
+  };
+  chunks(std::false_type{});
   // the tile's range check
   if (__ballot(range.out()) && lane == 0) *flags = 1;
   ring_barrier();
+  if (__builtin_amdgcn_readfirstlane((int)*flags)) chunks(std::true_type{});
   const bool post = o.post_relu != 0;
   float *const out0 = sl[o.route_slot];
   const int rctot = o.route_ctot, rcoff = o.route_coff;
-  if (__builtin_amdgcn_readfirstlane((int)*flags)) {
-    // out of range: plain fp32, one thread per output
-    const float *xp = sl[o.in_slot], *dwp = U(op.dw);
-    const int NG = U(op.NG);
-    for (int idx = tid; idx < BM * 32 * NBW * WG; idx += kThreads) {
-      const int p = idx & (BM - 1), nl = idx / BM, n = b0 * 32 + nl, m = m0 + p;
-      if (p >= cnt || n >= o.Cout) continue;
-      const int gr = fdiv(m, o.fd_wo), ow = m - gr * Wo, img = fdiv(gr, o.fd_ho), oh = gr - img * Ho;
-      float v = biasl[nl];
-      for (int c = 0; c < Cin; ++c) {
-        const float *pl = xp + (size_t)(img * o.in_ctot + o.in_coff + c) * H * W;
-        float s = 0.f;
-        for (int u = 0; u < K; ++u)
-          for (int q = 0; q < K; ++q) {
-            const int ih = oh - o.ph + u, iw = ow - o.pw + q;
-            if (ih < 0 || ih >= H || iw < 0 || iw >= W) continue;
-            const float xv = pl[(size_t)ih * W + iw];
-            s = fmaf(dwp[c * KK + u * K + q], relu_in ? relu1(xv) : xv, s);
-          }
-        v = fmaf(s, o.w32[(((size_t)(n >> 4) * NG + (c >> 4)) * 64 + (c & 3) * 16 + (n & 15)) * 4 + ((c >> 2) & 3)], v);
-      }
-      if (post) v = fmaxf(v, 0.f);
-      st<COH>(out0 + ((size_t)img * rctot + rcoff + n) * howo + m - img * howo, v);
-    }
-    return;
-  }
   const int p = wm * 32 + l32, m = m0 + p;
   if (p < cnt) {
     const int img = fdiv(m, o.fd_howo), pix = m - img * howo;
@@ -2261,33 +2267,36 @@ __device__ __forceinline__ void tile_body(const StageArgs &a, const Slots &sl, c
   if (signal) tile_signal(a, opi);
 }
 
-// The same for a split tile (the variants hold the conv's, the SEPCONV's or both).
+// The same for a split tile (the variants hold the conv's, the SEPCONV's or
+// both; `in`: its input, in scalar registers before the branches).
 template <bool COH, int KV>
-__device__ __forceinline__ void run_split(const Slots &sl, const DevOp &op, const SplitDesc &d, int ti, float *lds) {
+__device__ __forceinline__ void run_split(const Slots &sl, const DevOp &op, const SplitDesc &d, const float *in, int ti,
+                                          float *lds) {
   if constexpr (KV != KV_SPLIT) {
     if (KV == KV_SEPSPLIT || U(op.kind) == DK_SEP) {
       const bool wide = U(op.sep_nbt) == 4, k3 = d.kh == 3;   // 32 sep_nbt pixels
       if (wide) {
-        if (k3) sep_split_tile<4, 3, COH>(sl, op, d, ti, lds); else sep_split_tile<4, 5, COH>(sl, op, d, ti, lds);
+        if (k3) sep_split_tile<4, 3, COH>(sl, op, d, in, ti, lds); else sep_split_tile<4, 5, COH>(sl, op, d, in, ti, lds);
       } else {
-        if (k3) sep_split_tile<2, 3, COH>(sl, op, d, ti, lds); else sep_split_tile<2, 5, COH>(sl, op, d, ti, lds);
+        if (k3) sep_split_tile<2, 3, COH>(sl, op, d, in, ti, lds); else sep_split_tile<2, 5, COH>(sl, op, d, in, ti, lds);
       }
       return;
     }
   }
   if constexpr (KV != KV_SEPSPLIT) {
-    if (tile_is_split_pb2(U(op.tcfg))) conv_split_tile<2, COH>(sl, op, d, ti, lds);
-    else conv_split_tile<1, COH>(sl, op, d, ti, lds);
+    if (d.pb == 2) conv_split_tile<2, COH>(sl, op, d, in, ti, lds);
+    else conv_split_tile<1, COH>(sl, op, d, in, ti, lds);
   }
 }
 template <int KV>
 __device__ __forceinline__ void split_body(const StageArgs &a, const Slots &sl, const DevOp *ops, const DevOp &op,
                                            int opi, int ti, float *lds) {
   const SplitDesc d = split_desc(op.sp);
+  const float *in = sl[d.in_slot];
   const int n_deps = U(op.n_deps), signal = U(op.signal);
   if (n_deps) tile_wait(a, ops, op, n_deps);
-  if (n_deps || signal) run_split<true, KV>(sl, op, d, ti, lds);
-  else run_split<false, KV>(sl, op, d, ti, lds);
+  if (n_deps || signal) run_split<true, KV>(sl, op, d, in, ti, lds);
+  else run_split<false, KV>(sl, op, d, in, ti, lds);
   if (signal) tile_signal(a, opi);
 }
 

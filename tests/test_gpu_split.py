@@ -175,6 +175,42 @@ def test_split_mixed_magnitudes(scale, monkeypatch):
     g.close()
 
 
+@pytest.mark.parametrize("scale", [1e-36, 1e24, "inf"])
+def test_split_merge_values_out_of_range(scale, monkeypatch):
+    """The fp32 path of a merge stage with two destinations."""
+    rng = np.random.default_rng(19)
+    x = mixed(rng, (2, 19, 10, 13), 1.0 if scale == "inf" else scale)
+    if scale == "inf":
+        x[1, 7, 6, 4] = np.inf
+    ops = [conv_op("a", 37, (1, 1), (0, 0), post=1), conv_op("b", 50, (3, 3), (1, 1), post=1)]
+    ten = {}
+    for o in ops:
+        ten[o["name"] + ".w"] = (rng.standard_normal((o["cout"], 19, o["kh"], o["kw"])) * 0.2).astype(np.float32)
+        ten[o["name"] + ".b"] = np.zeros(o["cout"], np.float32)
+    g = graph(monkeypatch, 2, 19, 10, 13, ops, ten)
+    u = [g.tid["a"], g.tid["b"]]
+    for tile in SPLIT:
+        monkeypatch.setenv("IOS_CONV_TILE", str(tile))
+        got = launch(g, [u], [I.IOS_MERGE], x, ops, 10, 13)
+        for o, y in zip(ops, got):
+            # the merged conv is the 3 x 3 window of both: an infinity beside a 1 x 1 window meets its zero taps
+            w3 = np.zeros((o["cout"], 19, 3, 3), np.float32)
+            w3[:, :, (3 - o["kh"]) // 2:(3 + o["kh"]) // 2, (3 - o["kw"]) // 2:(3 + o["kw"]) // 2] = ten[o["name"] + ".w"]
+            o3 = conv_op(o["name"], o["cout"], (3, 3), (1, 1))
+            with np.errstate(invalid="ignore"):
+                ref, bound = reference(x, w3, ten[o["name"] + ".b"], o3)
+            if o["post_relu"]:
+                ref = np.fmax(ref, 0)                    # the kernels' ReLU takes a NaN to 0
+            fine = np.isfinite(ref)
+            assert np.array_equal(np.isnan(y), np.isnan(ref)), (tile, o["name"])
+            assert np.array_equal(y[~fine & ~np.isnan(ref)], ref[~fine & ~np.isnan(ref)]), (tile, o["name"])
+            # (no bound where a NaN became 0: the values are the same there)
+            bound = np.where(np.isnan(bound), 0, bound) + 6 * 171 * 2.0 ** -149
+            with np.errstate(invalid="ignore"):
+                assert np.all((np.abs(y - ref) <= bound)[fine]), (tile, o["name"])
+    g.close()
+
+
 SEP_CASES = {
     # batch, c, h, w, cout, window: rows odd and even, tiles within and across images, tails, several channel groups
     "even rows, last tile short": (1, 20, 6, 42, 40, 5),
