@@ -144,6 +144,12 @@ static int choose_xcd_runs(const std::vector<DevOp> &ops, const std::vector<int3
 }
 
 // Per-tile work estimate (MACs or elementwise ops), for ordering tiles.
+SepSplitGeom sep_split_geom_of(const DevOp &d) {
+  return sep_split_geometry(d.sep_nbt == 4 ? 0 : 1, d.N, d.kh, d.Ho, d.Wo);
+}
+
+bool op_is_split(const DevOp &d) { return d.kind == DK_CONV ? tile_is_split(d.tcfg) : d.kind == DK_SEP && d.sep_row == 2; }
+
 double tile_work(const DevOp &d) {
   switch (d.kind) {
     case DK_CONV: {
@@ -156,7 +162,7 @@ double tile_work(const DevOp &d) {
     }
     case DK_SEP:
       if (d.sep_row == 2)
-        return (double)d.sp.sc * d.CinP * (d.kh * d.kw + 6.0 / 16.0 * round_up(d.Cout, 32)) / kWaves;
+        return (double)sep_split_geom_of(d).tp * d.CinP * (d.kh * d.kw + 6.0 / 16.0 * round_up(d.Cout, 32)) / kWaves;
       if (d.sep_row == 3) return 32.0 * d.CinP * (9.0 * d.n_in + 32.0 * d.sep_nbt) / kWaves;
       if (d.sep_row) return 16.0 * d.CinP * (d.row_k * d.row_k * d.n_in + 16.0 * d.sep_nbt) / kWaves;
       return (double)d.sep_bm * d.CinP * (d.kh * d.kw + 16.0 * d.sep_nbt) / kWaves;
@@ -279,11 +285,11 @@ SplitGeom split_geometry(int cfg, int N, int cin, int cout, int H, int W, int Ho
 
 namespace {
 // The split tile's descriptor, from the operator's final fields and sizes.
-void set_split(DevOp &d, const float *w) {
+SplitDesc split_desc(const DevOp &d) {
   const SplitShape s = split_shape(d.tcfg);
   const SplitGeom g = split_geometry(d.tcfg, d.N, d.Cin, d.Cout, d.H, d.W, d.Ho, d.Wo, d.kh, d.kw, d.sh, d.sw);
   if (!g.ok) fail(IOS_E_UNSUPPORTED, "conv split tile does not apply");
-  SplitDesc &p = d.sp;
+  SplitDesc p{};
   p.lwm = 31 - __builtin_clz((unsigned)s.wm);
   p.lwn = 31 - __builtin_clz((unsigned)s.wn);
   p.wk = s.wk; p.pb = s.pb;
@@ -308,32 +314,32 @@ void set_split(DevOp &d, const float *w) {
   p.fd_kw = make_fdiv((uint32_t)d.kw);
   p.fd_w2 = make_fdiv((uint32_t)g.w2);
   p.fd_hv = make_fdiv((uint32_t)g.hv);
-  p.w = w; p.bias = d.bias;
+  p.w = d.wpk; p.bias = d.bias;
+  return p;
 }
-// The same of a SEPCONV's split tile (w: the pointwise weights).
-void set_sep_split(DevOp &d, const SepSplitGeom &g, const float *w) {
-  SplitDesc &p = d.sp;
-  p.sc = g.tp; p.lwm = g.per_img;
-  p.nch = cdiv(d.Cin, kSplitCK); p.pp = g.pp;
-  p.fd_taps = make_fdiv((uint32_t)std::max(1, g.per_img));
-  p.w2 = g.w2; p.hv = g.hv; p.tail = g.tail;
+// The same of a SEPCONV.
+SepSplitDesc sep_split_desc(const DevOp &d) {
+  const SepSplitGeom g = sep_split_geom_of(d);
+  SepSplitDesc p{};
+  p.bm = g.bm; p.k = d.kh;
+  p.tp = g.tp; p.per_img = g.per_img; p.rows = g.rows; p.lq = g.lq;
+  p.nch = cdiv(d.Cin, kSplitCK); p.pp = g.pp; p.w2 = g.w2; p.hv = g.hv; p.tail = g.tail;
   p.Ho = d.Ho; p.Wo = d.Wo; p.howo = d.Ho * d.Wo; p.M = d.N * p.howo;
-  p.N = d.N; p.H = d.H; p.W = d.W; p.Cin = d.Cin; p.Cout = d.Cout;
-  p.kh = d.kh; p.kw = d.kw; p.taps = g.rows; p.lq = g.lq;
-  p.fd_pp = make_fdiv((uint32_t)((d.W + 3) / 4));
-  p.sh = p.sw = 1; p.ph = d.ph; p.pw = d.pw;
+  p.N = d.N; p.H = d.H; p.W = d.W; p.Cin = d.Cin; p.Cout = d.Cout; p.ph = d.ph; p.pw = d.pw;
   p.in_slot = d.in_slot[0]; p.in_coff = d.in_coff[0]; p.in_ctot = d.in_ctot[0]; p.in_bytes = d.in_bytes[0];
   p.pre_relu = d.pre_relu; p.post_relu = d.post_relu;
-  p.n_routes = 1; p.route_slot = d.route_slot[0]; p.route_coff = d.route_coff[0]; p.route_ctot = d.route_ctot[0];
+  p.route_slot = d.route_slot[0]; p.route_coff = d.route_coff[0]; p.route_ctot = d.route_ctot[0];
   p.tiles_n = cdiv(d.Cout, g.bn);
   p.w_bytes = (int32_t)(split_words(d.Cout, d.Cin, 1, 1) * sizeof(float));
   p.fd_tn = make_fdiv((uint32_t)p.tiles_n);
   p.fd_wo = make_fdiv((uint32_t)d.Wo);
   p.fd_ho = make_fdiv((uint32_t)d.Ho);
   p.fd_howo = make_fdiv((uint32_t)p.howo);
-  p.fd_w2 = make_fdiv((uint32_t)g.w2);
+  p.fd_img = make_fdiv((uint32_t)std::max(1, g.per_img));
+  p.fd_pieces = make_fdiv((uint32_t)((d.W + 3) / 4));
   p.fd_hv = make_fdiv((uint32_t)g.hv);
-  p.w = w; p.bias = d.bias;
+  p.w = d.wpk; p.bias = d.bias; p.dw = d.dw;
+  return p;
 }
 }  // namespace
 
@@ -478,7 +484,14 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
     // a pipelined conv tile's LDS rings beside the stage table must fit a
     // workgroup; in a stage of very many operators such a conv takes 16x32
     const int n_ops = (int)ops.size();
-    const int table_bytes = (kSlotWords + ((4 + n_ops + 1 + 3) & ~3) + n_ops * kDevOpWords) * (int)sizeof(int32_t);
+    int n_split = 0;             // at most
+    for (int i : ops) {
+      const Op &o = g->ops[i];
+      n_split += o.d.kind == IOS_CONV ? tile_is_split(o.tcfg)
+                                      : o.d.kind == IOS_SEPCONV && o.sep_tile >= kSepgFirst && o.sep_tile < kSepLineFirst;
+    }
+    const int table_bytes = (kSlotWords + ((4 + n_ops + 1 + 3) & ~3) + n_ops * kDevOpWords + n_split * kSplitDescWords) *
+                            (int)sizeof(int32_t);
     const bool pipe_fits = table_bytes + pipe_lds_bytes(TC_W128x64) <= kMaxLdsBytes;
     // a split conv tile runs in a variant without SEPCONV tiles, and its patch
     // must fit beside the table too
@@ -503,7 +516,7 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
             if (any_sep || !sg.ok || table_bytes + sg.lds > kMaxLdsBytes) d.tcfg = TC_16x32_K8;
           }
           if (tile_is_split(d.tcfg)) {
-            set_split(d, o.d_wsp);
+            d.wpk = o.d_wsp;
           } else if (tile_is_pipe(d.tcfg)) {
             d.NG = o.pipe_nkb;
             d.pipe_ldw = round_up(o.d.cout, 128);
@@ -542,8 +555,7 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
             d.kind = DK_SEP; d.sep_row = 2;
             d.CinP = o.CinP; d.Npad = o.Npad;
             d.sep_nbt = sg2.bm / 32;
-            d.bias = o.d_bias; d.dw = o.d_dw;
-            set_sep_split(d, sg2, o.d_wsp);
+            d.wpk = o.d_wsp; d.bias = o.d_bias; d.dw = o.d_dw;
             break;
           }
           // weights out of the split tiles' range, rows of fewer than four
@@ -605,9 +617,10 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
       d.tiles_m = cdiv(M, tile_bm(d.tcfg));
       d.tiles_n = cdiv(d.Cout, tile_bn(d.tcfg));
     } else if (d.kind == DK_SEP && d.sep_row == 2) {
-      // split tile: runs of sp.sc output pixels of an image or the batch x groups of 96 (8 / sep_nbt) channels
-      d.tiles_m = d.sp.lwm ? d.N * d.sp.lwm : cdiv(M, d.sp.sc);
-      d.tiles_n = d.sp.tiles_n;
+      // split tile: runs of tp output pixels of an image or the batch x groups of bn channels
+      const SepSplitGeom sg = sep_split_geom_of(d);
+      d.tiles_m = sg.per_img ? d.N * sg.per_img : cdiv(M, sg.tp);
+      d.tiles_n = cdiv(d.Cout, sg.bn);
     } else if (d.kind == DK_SEP && d.sep_row == 3) {
       // line tile: (image, block of line_r output rows) x groups of 32 sep_nbt channels
       d.tiles_per_plane = cdiv(d.Ho, d.line_r);
@@ -732,7 +745,12 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
   cs->slot_buf = sm.bufs;
   // table: header, op_start, DevOps (the kernel copies it to LDS)
   const int devop_off = (4 + n + 1 + 3) & ~3;
-  const int table_words = devop_off + n * kDevOpWords;
+  int table_words = devop_off + n * kDevOpWords;
+  for (DevOp &d : cs->ops)
+    if (op_is_split(d)) {
+      d.split_off = table_words;
+      table_words += kSplitDescWords;
+    }
   cs->lds_bytes = (kSlotWords + table_words) * (int)sizeof(int32_t) + lds;
   if (cs->lds_bytes > kMaxLdsBytes) fail(IOS_E_UNSUPPORTED, "stage needs more LDS than a workgroup has");
   cs->persistent = persistent;
@@ -769,7 +787,6 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
   if (!mw.empty() || merge_held) {
     cs->ops[0].wpk = cs->d_mw;
     cs->ops[0].bias = cs->d_mb;
-    if (tile_is_split(cs->ops[0].tcfg)) set_split(cs->ops[0], cs->d_mw);
   }
   cs->table.assign(table_words, 0);
   cs->table[0] = n;
@@ -789,6 +806,16 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
   cs->table[3] = lg >= 0 ? lg : choose_xcd_runs(sorted, start, cs->grid);
   for (int i = 0; i <= n; ++i) cs->table[4 + i] = start[i];
   std::memcpy(&cs->table[devop_off], cs->ops.data(), sizeof(DevOp) * n);
+  for (const DevOp &d : cs->ops) {
+    if (!d.split_off) continue;
+    if (d.kind == DK_CONV) {
+      const SplitDesc p = split_desc(d);
+      std::memcpy(&cs->table[d.split_off], &p, sizeof(p));
+    } else {
+      const SepSplitDesc p = sep_split_desc(d);
+      std::memcpy(&cs->table[d.split_off], &p, sizeof(p));
+    }
+  }
   size_t d0 = 0, d2 = 0;
   grow_upload(&cs->d_table, reuse ? &g->prof_ops_cap : &d0, cs->table, reuse);
   std::vector<int32_t> ctr(2 + kCtrStride * kCtrCopies, 0);

@@ -355,11 +355,14 @@ inline FDiv make_fdiv(uint32_t d) {
   return {(uint32_t)(((1ull << 32) * ((1ull << l) - d)) / d + 1), l};
 }
 
-// What a split tile reads of its operator, one word for each lane of a wave
-// (the fields as in DevOp and SplitGeom).
-struct alignas(16) SplitDesc {
-  int32_t lwm, lwn, wk, sc;    // SplitShape (wm, wn as log2), sub-chunks per round
-  int32_t nch, np, pp, lq;     // sub-chunks in all, positions, rounded up to 32; lq: see SepSplitGeom
+// What a split tile reads of its operator, at most one word for each lane of a
+// wave (the fields as in DevOp, SplitGeom and SepSplitGeom).  In the stage
+// table after the operators' descriptors, kSplitDescWords apart, and only for
+// the operators that run on one.
+constexpr int kSplitDescWords = 64;
+struct SplitDesc {             // conv
+  int32_t lwm, lwn, wk, pb;    // SplitShape (wm, wn as log2)
+  int32_t sc, nch, np, pp;     // sub-chunks per round and in all, positions, rounded up to 32
   int32_t w2, hv, gather, tail;// patch row length, virtual rows per image, LDS byte offset of flags and biases
   int32_t M, Ho, Wo, howo;     // output pixels of the batch
   int32_t N, H, W, Cin;
@@ -368,24 +371,28 @@ struct alignas(16) SplitDesc {
   int32_t in_slot, in_coff, in_ctot, in_bytes;
   int32_t pre_relu, post_relu, n_routes, route_slot;
   int32_t route_coff, route_ctot, tiles_n, w_bytes;
-  FDiv fd_tn, fd_wo;
-  FDiv fd_ho, fd_howo;
-  FDiv fd_pp, fd_taps;
-  FDiv fd_kw, fd_w2;
-  FDiv fd_hv;
-  int32_t pb, pad;             // SplitShape: blocks of 32 pixels per wave
+  FDiv fd_tn, fd_wo, fd_ho, fd_howo;
+  FDiv fd_pp, fd_taps, fd_kw, fd_w2, fd_hv;
   const void *w;               // pack_conv_split
   const float *bias;           // [Npad], at least Cout floats
 };
-static_assert(sizeof(SplitDesc) == 256, "one word per lane (some unused)");
-
-// (SEP split tile, see SepSplitGeom: sc = tp, lwm = per_img (fd_taps divides by
-// it), taps = rows; fd_pp divides by the pieces of a row.)
-
-// Whether an operator (its kind, tcfg and sep_row) runs on a split tile.
-__host__ __device__ inline bool op_is_split(int kind, int tcfg, int sep_row) {
-  return kind == DK_CONV ? tcfg >= TC_S256x64 : kind == DK_SEP && sep_row == 2;
-}
+struct SepSplitDesc {
+  int32_t bm, k;               // pixels of the choice, window
+  int32_t tp, per_img, rows, lq;
+  int32_t nch, pp, w2, hv, tail;   // nch: chunks of kSplitCK input channels
+  int32_t M, Ho, Wo, howo;
+  int32_t N, H, W, Cin, Cout, ph, pw;
+  int32_t in_slot, in_coff, in_ctot, in_bytes;
+  int32_t pre_relu, post_relu, route_slot, route_coff, route_ctot;
+  int32_t tiles_n, w_bytes;
+  int32_t pad;
+  FDiv fd_tn, fd_wo, fd_ho, fd_howo;
+  FDiv fd_img, fd_pieces, fd_hv;   // max(1, per_img), pieces of four columns in a row
+  const void *w;               // pack_conv_split of the pointwise weights
+  const float *bias, *dw;      // as DevOp
+};
+static_assert(sizeof(SplitDesc) <= 4 * kSplitDescWords && sizeof(SepSplitDesc) <= 4 * kSplitDescWords,
+              "one word per lane");
 
 // One operator of a compiled stage, as the kernel sees it.
 struct alignas(16) DevOp {
@@ -425,6 +432,7 @@ struct alignas(16) DevOp {
   int32_t pipe_ldw;            // CONV pipelined tile: row length of the packed weights (NG = k-blocks)
   int32_t w_bytes;             // size of wpk in bytes
   int32_t dw_bytes;            // SEP: size of dw in bytes
+  int32_t split_off;           // split tiles: word of the table where their SplitDesc or SepSplitDesc starts; else 0
   // divisors of the tile and pixel decompositions (see FDiv)
   FDiv fd_tn;                  // tiles_n
   FDiv fd_howo, fd_wo;         // Ho * Wo, Wo
@@ -438,13 +446,13 @@ struct alignas(16) DevOp {
   const float *wpk;            // CONV: see pack_conv_weights; SEP: the pointwise weights packed the same way
   const float *bias;           // [Npad]
   const float *dw;             // SEP: depthwise [round16(Cin)][kh * kw], channels past Cin zero
-  SplitDesc sp;                // CONV and SEP split tiles
 };
 
 // A compiled stage's table in device memory (int32 words): a header
 // {n_ops, n_tiles, devop_off, 0}, op_start[n_ops + 1] (op i owns tiles
 // [op_start[i], op_start[i+1]) in tile order), zero padding to a multiple of
-// 4 words, then DevOp[n_ops] from word devop_off.  Every workgroup copies the
+// 4 words, DevOp[n_ops] from word devop_off, then the split tiles'
+// descriptors (DevOp::split_off).  Every workgroup copies the
 // table and the launch's buffer pointers to LDS when it starts (one memory
 // round trip for all of its metadata).
 constexpr int kDevOpWords = (int)(sizeof(DevOp) / 4);
@@ -532,7 +540,7 @@ struct CompiledStage {
   bool persistent = false;       // some op waits for another: persistent launch
   int grid = 0;                  // workgroups launched
   int variant = 0;               // KernelVariant
-  std::vector<int32_t> table;    // header, op_start, DevOps (see kDevOpWords)
+  std::vector<int32_t> table;    // header, op_start, descriptors (see kDevOpWords)
   // device copies (owned unless reused by the profiler)
   int32_t *d_table = nullptr;
   int32_t *d_ctr = nullptr;

@@ -996,13 +996,14 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
 
 // The descriptor of a split tile in scalar registers: word i from lane i (one
 // LDS read), as op_scalars.
-__device__ __forceinline__ SplitDesc split_desc(const SplitDesc &g) {
-  static_assert(sizeof(SplitDesc) == 256, "one word per lane (some unused)");
-  const int v = ((const int *)&g)[threadIdx.x & 63];
-  int w[64];
+template <class D>
+__device__ __forceinline__ D split_desc(const int32_t *words) {
+  const int v = words[threadIdx.x & 63];
+  D d;
+  int *w = (int *)&d;
 #pragma unroll
-  for (int i = 0; i < 64; ++i) w[i] = __builtin_amdgcn_readlane(v, i);
-  return __builtin_bit_cast(SplitDesc, w);
+  for (int i = 0; i < (int)(sizeof(D) / 4); ++i) w[i] = __builtin_amdgcn_readlane(v, i);
+  return d;
 }
 
 // ------------------------------------------------------------------ sepconv
@@ -1717,8 +1718,7 @@ __device__ __forceinline__ int sep_slot(int px) { return px ^ ((px >> 4) & 1); }
 // 223 us against the tile before this one (fp32 MFMA, planes copied to LDS
 // float by float, the depthwise pass once per 64 output channels).
 template <int WM, int K, bool COH>
-__device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op, const SplitDesc &o, const float *in, int t,
-                                               float *lds) {
+__device__ __forceinline__ void sep_split_tile(const Slots &sl, const SepSplitDesc &o, const float *in, int t, float *lds) {
   constexpr int BM = 32 * WM, WG = kWaves / WM, KK = K * K, NBW = kSepSplitBlocks;
   constexpr int XL = 16 * kSepSplitPieces / kThreads;  // 16-byte loads per thread and chunk at most
   constexpr int AB = NBW * WG;                         // channel blocks of the tile
@@ -1727,11 +1727,11 @@ __device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op,
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave % WM, wg = wave / WM;
   const int tm = fdiv(t, o.fd_tn), tn = t - tm * o.tiles_n;
-  // pixels m0 .. m0 + cnt - 1: of one image where an image has o.lwm tiles, of
-  // the flattened batch (lwm = 0) otherwise
+  // pixels m0 .. m0 + cnt - 1: of one image where an image has o.per_img tiles, of
+  // the flattened batch (per_img = 0) otherwise
   const int b0 = tn * (NBW * WG), nblk = (o.Cout + 31) >> 5, nch = o.nch;
-  const int ti = o.lwm ? fdiv(tm, o.fd_taps) : 0;
-  const int m0 = ti * o.howo + (tm - ti * o.lwm) * o.sc, cnt = min(o.sc, (o.lwm ? (ti + 1) * o.howo : o.M) - m0);
+  const int ti = o.per_img ? fdiv(tm, o.fd_img) : 0;
+  const int m0 = ti * o.howo + (tm - ti * o.per_img) * o.tp, cnt = min(o.tp, (o.per_img ? (ti + 1) * o.howo : o.M) - m0);
   const int Wo = o.Wo, Ho = o.Ho, howo = o.howo, H = o.H, W = o.W, Cin = o.Cin, W2 = o.w2, hv = o.hv;
   const int PP = o.pp, hw4 = H * W * 4;
   float *xs = lds;                                     // [16][PP]
@@ -1753,9 +1753,9 @@ __device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op,
   const int cstep = kThreads >> lq, nld = 1 << (lq - 5);
   int off = kOOB, dst = 0;
   {
-    const int r = fdiv(e, o.fd_pp), v = vlo + r, img = fdiv(v, o.fd_hv), ih = v - img * hv - o.ph;
+    const int r = fdiv(e, o.fd_pieces), v = vlo + r, img = fdiv(v, o.fd_hv), ih = v - img * hv - o.ph;
     const int col = min(4 * (e - r * ((W + 3) >> 2)), W - 4);
-    if (r < o.taps && img < o.N && ih >= 0 && ih < H) {
+    if (r < o.rows && img < o.N && ih >= 0 && ih < H) {
       off = (((img * o.in_ctot + o.in_coff) * H + ih) * W + col) * 4;
       dst = r * W2 + o.pw + col;
     }
@@ -1799,7 +1799,7 @@ __device__ __forceinline__ void sep_split_tile(const Slots &sl, const DevOp &op,
   // a channel's filter: tap i in lane i, a chunk ahead
   constexpr int KKP = (KK + 3) & ~3;
   float *wl = biasl + 32 * AB;                         // [16][KKP]
-  const __amdgpu_buffer_rsrc_t dr = rsrc(U(op.dw), nch * kSplitCK * KK * 4);
+  const __amdgpu_buffer_rsrc_t dr = rsrc(o.dw, nch * kSplitCK * KK * 4);
   float wv[2];
   auto filters = [&](int c) {
 #pragma unroll
@@ -2269,34 +2269,30 @@ __device__ __forceinline__ void tile_body(const StageArgs &a, const Slots &sl, c
 
 // The same for a split tile (the variants hold the conv's, the SEPCONV's or
 // both; `in`: its input, in scalar registers before the branches).
-template <bool COH, int KV>
+template <bool COH>
 __device__ __forceinline__ void run_split(const Slots &sl, const DevOp &op, const SplitDesc &d, const float *in, int ti,
                                           float *lds) {
-  if constexpr (KV != KV_SPLIT) {
-    if (KV == KV_SEPSPLIT || U(op.kind) == DK_SEP) {
-      const bool wide = U(op.sep_nbt) == 4, k3 = d.kh == 3;   // 32 sep_nbt pixels
-      if (wide) {
-        if (k3) sep_split_tile<4, 3, COH>(sl, op, d, in, ti, lds); else sep_split_tile<4, 5, COH>(sl, op, d, in, ti, lds);
-      } else {
-        if (k3) sep_split_tile<2, 3, COH>(sl, op, d, in, ti, lds); else sep_split_tile<2, 5, COH>(sl, op, d, in, ti, lds);
-      }
-      return;
-    }
-  }
-  if constexpr (KV != KV_SEPSPLIT) {
-    if (d.pb == 2) conv_split_tile<2, COH>(sl, op, d, in, ti, lds);
-    else conv_split_tile<1, COH>(sl, op, d, in, ti, lds);
+  if (d.pb == 2) conv_split_tile<2, COH>(sl, op, d, in, ti, lds);
+  else conv_split_tile<1, COH>(sl, op, d, in, ti, lds);
+}
+template <bool COH>
+__device__ __forceinline__ void run_split(const Slots &sl, const DevOp &, const SepSplitDesc &d, const float *in, int ti,
+                                          float *lds) {
+  if (d.bm == 128) {
+    if (d.k == 3) sep_split_tile<4, 3, COH>(sl, d, in, ti, lds); else sep_split_tile<4, 5, COH>(sl, d, in, ti, lds);
+  } else {
+    if (d.k == 3) sep_split_tile<2, 3, COH>(sl, d, in, ti, lds); else sep_split_tile<2, 5, COH>(sl, d, in, ti, lds);
   }
 }
-template <int KV>
+template <class D>
 __device__ __forceinline__ void split_body(const StageArgs &a, const Slots &sl, const DevOp *ops, const DevOp &op,
-                                           int opi, int ti, float *lds) {
-  const SplitDesc d = split_desc(op.sp);
+                                           const int32_t *words, int opi, int ti, float *lds) {
+  const D d = split_desc<D>(words);
   const float *in = sl[d.in_slot];
   const int n_deps = U(op.n_deps), signal = U(op.signal);
   if (n_deps) tile_wait(a, ops, op, n_deps);
-  if (n_deps || signal) run_split<true, KV>(sl, op, d, in, ti, lds);
-  else run_split<false, KV>(sl, op, d, in, ti, lds);
+  if (n_deps || signal) run_split<true>(sl, op, d, in, ti, lds);
+  else run_split<false>(sl, op, d, in, ti, lds);
   if (signal) tile_signal(a, opi);
 }
 
@@ -2327,8 +2323,12 @@ __device__ __forceinline__ void process_tile(const StageArgs &a, const Slots &sl
   // memory (read-only while the kernel runs, a uniform address).  The split
   // tiles have a descriptor of their own.
   if constexpr (KV == KV_SPLIT || KV == KV_SEPSPLIT || KV == KV_FULL) {
-    if (op_is_split(U(op.kind), U(op.tcfg), U(op.sep_row))) {
-      split_body<KV>(a, sl, ops, op, opi, ti, lds);
+    const int off = U(op.split_off);
+    if (off) {
+      if constexpr (KV == KV_SPLIT) split_body<SplitDesc>(a, sl, ops, op, tab + off, opi, ti, lds);
+      else if constexpr (KV == KV_SEPSPLIT) split_body<SepSplitDesc>(a, sl, ops, op, tab + off, opi, ti, lds);
+      else if (U(op.kind) == DK_CONV) split_body<SplitDesc>(a, sl, ops, op, tab + off, opi, ti, lds);
+      else split_body<SepSplitDesc>(a, sl, ops, op, tab + off, opi, ti, lds);
       return;
     }
   }
