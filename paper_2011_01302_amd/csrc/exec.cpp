@@ -493,10 +493,6 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
     const int table_bytes = (kSlotWords + ((4 + n_ops + 1 + 3) & ~3) + n_ops * kDevOpWords + n_split * kSplitDescWords) *
                             (int)sizeof(int32_t);
     const bool pipe_fits = table_bytes + pipe_lds_bytes(TC_W128x64) <= kMaxLdsBytes;
-    // a split conv tile runs in a variant without SEPCONV tiles, and its patch
-    // must fit beside the table too
-    bool any_sep = false;
-    for (int i : ops) any_sep |= g->ops[i].d.kind == IOS_SEPCONV;
     for (size_t i = 0; i < ops.size(); ++i) {
       const Op &o = g->ops[ops[i]];
       DevOp d{};
@@ -511,9 +507,9 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
           d.kind = DK_CONV; d.tcfg = o.tcfg; d.CinP = o.CinP; d.Npad = o.Npad;
           d.bias = o.d_bias;
           if (tile_is_pipe(d.tcfg) && !pipe_fits) d.tcfg = TC_16x32_K8;
-          if (tile_is_split(d.tcfg)) {
+          if (tile_is_split(d.tcfg)) {                 // its patch must fit beside the table too
             const SplitGeom sg = split_geometry(d.tcfg, d.N, d.Cin, d.Cout, d.H, d.W, d.Ho, d.Wo, d.kh, d.kw, d.sh, d.sw);
-            if (any_sep || !sg.ok || table_bytes + sg.lds > kMaxLdsBytes) d.tcfg = TC_16x32_K8;
+            if (!sg.ok || table_bytes + sg.lds > kMaxLdsBytes) d.tcfg = TC_16x32_K8;
           }
           if (tile_is_split(d.tcfg)) {
             d.wpk = o.d_wsp;

@@ -146,6 +146,49 @@ def test_split_values_out_of_range(scale, monkeypatch):
     g.close()
 
 
+def profiled(g, ids, strategy, tiles):
+    """Stage times with the first unit on each of the tile shapes."""
+    out = []
+    for t in tiles:
+        I.ios_set_conv_tile(g.handle, ids[0], t)
+        out.append(I.ios_profile_stage(g.handle, ids, strategy, 5, 20, 5))
+    return out
+
+
+def test_split_beside_sepconv(monkeypatch):
+    """A large conv on a split shape beside SEPCONVs of each kind of tile: right,
+    and that shape runs (16 x 32, shape 1, takes more than twice its time)."""
+    rng = np.random.default_rng(23)
+    n, c, h, w = 16, 96, 35, 36
+    x = rng.standard_normal((n, c, h, w)).astype(np.float32)
+    ops = [conv_op("a", 96, (3, 3), (1, 1)),
+           {"name": "s", "kind": "sepconv", "in": ["x"], "cout": 40, "kh": 3, "kw": 3, "sh": 1, "sw": 1, "ph": 1,
+            "pw": 1, "pre_relu": 1, "post_relu": 0}]
+    ten = {"a.w": (rng.standard_normal((96, c, 3, 3)) / 30).astype(np.float32),
+           "a.b": rng.standard_normal(96).astype(np.float32),
+           "s.dw": (rng.standard_normal((c, 1, 3, 3)) / 3).astype(np.float32),
+           "s.pw": (rng.standard_normal((40, c, 1, 1)) / 10).astype(np.float32),
+           "s.b": rng.standard_normal(40).astype(np.float32)}
+    monkeypatch.setenv("IOS_SEP_TILE", "0")
+    g = graph(monkeypatch, n, c, h, w, ops, ten)
+    u = [g.tid["a"], g.tid["s"]]
+    ref, bound = reference(x, ten["a.w"], ten["a.b"], ops[0])
+    r = np.maximum(x, 0).astype(np.float64)
+    sref = E.conv2d(E.depthwise(r, ten["s.dw"], (1, 1)), ten["s.pw"], ten["s.b"])
+    mag = E.conv2d(E.depthwise(r, np.abs(ten["s.dw"]), (1, 1)), np.abs(ten["s.pw"]), np.abs(ten["s.b"]))
+    for sep in (0, 3, 7):
+        I.ios_set_unit_tiling(g.handle, u[1], sep, -1)
+        for t in (13, 17):
+            I.ios_set_conv_tile(g.handle, u[0], t)
+            y, z = launch(g, [u], [I.IOS_CONCURRENT], x, ops, h, w)
+            assert np.all(np.abs(y - ref) <= bound), (sep, t)
+            assert np.all(np.abs(z - sref) <= (c + 18) * 2.0 ** -24 * mag), (sep, t)
+    I.ios_set_unit_tiling(g.handle, u[1], 7, -1)
+    split, small = profiled(g, u, I.IOS_CONCURRENT, (14, 1))
+    assert split < 0.75 * small, (split, small)
+    g.close()
+
+
 def mixed(rng, shape, scale):
     """Ordinary values, the first rows of the first image scaled: tiles that
     hold both, and windows that hold the scaled ones only."""
