@@ -433,7 +433,9 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
     };
     d.tcfg = std::getenv("IOS_CONV_TILE") ? choose_conv_tile((int64_t)g->batch * o0.ho * o0.wo, total, merged_ok)
                                            : g->ops[largest].tcfg;
-    if (!merged_ok(d.tcfg)) d.tcfg = TC_16x32_K8;   // the merged window has more than 32 taps, or does not fit
+    // the merged window may not fit a split tile, or have more than 32 taps
+    if (tile_is_split(d.tcfg) && !merged_ok(d.tcfg)) d.tcfg = g->ops[largest].tcfg_fp32;
+    if (!merged_ok(d.tcfg)) d.tcfg = TC_16x32_K8;
     const int layout = tile_is_split(d.tcfg) ? 2 : tile_is_pipe(d.tcfg) ? 1 : 0;
     int nb = 0;
     merge_held = reuse && g->prof_merge_ops == ops && g->prof_merge_layout == layout;
@@ -506,11 +508,11 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
         case IOS_CONV:
           d.kind = DK_CONV; d.tcfg = o.tcfg; d.CinP = o.CinP; d.Npad = o.Npad;
           d.bias = o.d_bias;
-          if (tile_is_pipe(d.tcfg) && !pipe_fits) d.tcfg = TC_16x32_K8;
           if (tile_is_split(d.tcfg)) {                 // its patch must fit beside the table too
             const SplitGeom sg = split_geometry(d.tcfg, d.N, d.Cin, d.Cout, d.H, d.W, d.Ho, d.Wo, d.kh, d.kw, d.sh, d.sw);
-            if (!sg.ok || table_bytes + sg.lds > kMaxLdsBytes) d.tcfg = TC_16x32_K8;
+            if (!sg.ok || table_bytes + sg.lds > kMaxLdsBytes) d.tcfg = o.tcfg_fp32;
           }
+          if (tile_is_pipe(d.tcfg) && !pipe_fits) d.tcfg = TC_16x32_K8;
           if (tile_is_split(d.tcfg)) {
             d.wpk = o.d_wsp;
           } else if (tile_is_pipe(d.tcfg)) {

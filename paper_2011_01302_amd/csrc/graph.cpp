@@ -393,10 +393,6 @@ static int choose_sep_tile(const Op &op) {
   return sep_tile_ok(op, v) ? v : 0;
 }
 
-// Conv tile shape for an M x N output before measurement.  IOS_CONV_TILE=<0..19>
-// in the environment (read when a graph is finalized or a merged stage is
-// built) forces one shape for every conv, for tuning and for tests; a
-// pipelined or split shape is forced only on convs it applies to (ok).
 // Tuning: warm-up time before the first measurement, the fraction of the
 // fastest time within which a conv tile shape with fewer workgroups is taken,
 // and how far from the fastest of a first round of a few launches a shape is
@@ -405,17 +401,26 @@ constexpr int kTuneWarmMs = 50;
 constexpr double kTuneSlack = 0.03;
 constexpr double kTuneScreen = 1.5;
 
-int choose_conv_tile(int64_t M, int N, const std::function<bool(int)> &ok) {
-  if (const char *e = std::getenv("IOS_CONV_TILE")) {
-    int v = std::atoi(e);
-    if (v >= 0 && v < TC_COUNT && ok(v)) return v;
-  }
+// Conv tile shape for an M x N output before measurement.
+static int default_conv_tile(int64_t M, int N) {
   int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64);
   int64_t t32 = ((M + 31) / 32) * ((N + 31) / 32);
   if (t64 >= 2048) return TC_128x64;
   if (t64 >= 512) return TC_64x64_K2;
   if (t32 >= 256) return TC_32x32_K8;
   return TC_16x32_K8;
+}
+
+// The same, or the one forced: IOS_CONV_TILE=<0..19>
+// in the environment (read when a graph is finalized or a merged stage is
+// built) forces one shape for every conv, for tuning and for tests; a
+// pipelined or split shape is forced only on convs it applies to (ok).
+int choose_conv_tile(int64_t M, int N, const std::function<bool(int)> &ok) {
+  if (const char *e = std::getenv("IOS_CONV_TILE")) {
+    int v = std::atoi(e);
+    if (v >= 0 && v < TC_COUNT && ok(v)) return v;
+  }
+  return default_conv_tile(M, N);
 }
 
 void finalize_graph(ios_graph *g) {
@@ -434,6 +439,7 @@ void finalize_graph(ios_graph *g) {
       op.split_ok = split_weights_ok(op.w.data(), op.w.size());
       op.tcfg = choose_conv_tile((int64_t)g->batch * op.ho * op.wo, op.d.cout,
                                  [&](int v) { return conv_tile_ok(op, v); });
+      op.tcfg_fp32 = default_conv_tile((int64_t)g->batch * op.ho * op.wo, op.d.cout);
     } else if (op.d.kind == IOS_SEPCONV) {
       op.CinP = round_up(op.cin, 16);
       op.Npad = round_up(op.d.cout, 16);
@@ -571,21 +577,31 @@ void ensure_device(ios_graph *g) {
         quick.push_back({profile_stage(g, {oi}, IOS_CONCURRENT, 2, 3, 1), cfg});
         fastest = std::min(fastest, quick.back().first);
       }
+      // (the fastest shape that is no split one in any case)
+      int64_t fastest_fp32 = INT64_MAX;
+      for (auto &m : quick)
+        if (!tile_is_split(m.second)) fastest_fp32 = std::min(fastest_fp32, m.first);
       for (auto &m : quick) {
-        if ((double)m.first > (double)fastest * kTuneScreen) continue;
+        if ((double)m.first > (double)fastest * kTuneScreen && (tile_is_split(m.second) || m.first > fastest_fp32)) continue;
         op.tcfg = m.second;
         meas.push_back({profile_stage(g, {oi}, IOS_CONCURRENT, 3, 20, 5), m.second});
       }
-      fastest = INT64_MAX;
-      for (auto &m : meas) fastest = std::min(fastest, m.first);
       auto tiles = [&](int cfg) {
         return ((M + tile_bm(cfg) - 1) / tile_bm(cfg)) * ((op.d.cout + tile_bn(cfg) - 1) / tile_bn(cfg));
       };
-      int best = -1;
-      for (auto &m : meas)
-        if (m.first <= fastest + (int64_t)(fastest * kTuneSlack) &&
-            (best < 0 || tiles(m.second) < tiles(best)))
-          best = m.second;
+      auto best_of = [&](bool split) {
+        int64_t lo = INT64_MAX;
+        int best = -1;
+        for (auto &m : meas)
+          if (split || !tile_is_split(m.second)) lo = std::min(lo, m.first);
+        for (auto &m : meas)
+          if ((split || !tile_is_split(m.second)) && m.first <= lo + (int64_t)(lo * kTuneSlack) &&
+              (best < 0 || tiles(m.second) < tiles(best)))
+            best = m.second;
+        return best;
+      };
+      op.tcfg_fp32 = best_of(false);
+      const int best = best_of(true);
       op.tcfg = best;
     }
   }

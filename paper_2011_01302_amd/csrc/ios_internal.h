@@ -515,6 +515,7 @@ struct Op {
   int batch = 1;                 // CONV: the graph's batch, set at finalize
   // device copies (units only)
   int CinP = 0, Npad = 0, NG = 0, tcfg = TC_16x32_K8;
+  int tcfg_fp32 = TC_16x32_K8;   // CONV: the best shape that is no split one, for stages where those do not fit
   int sep_tile = 1;              // SEPCONV: tile choice (16 << sep_tile output pixels per tile)
   int xcd_lg = -1;               // XCD run length 2^xcd_lg of the stage holding it; -1: modelled
   float *d_wpk = nullptr, *d_bias = nullptr, *d_dw = nullptr;

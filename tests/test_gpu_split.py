@@ -189,6 +189,30 @@ def test_split_beside_sepconv(monkeypatch):
     g.close()
 
 
+def test_split_that_the_merged_window_does_not_admit(monkeypatch):
+    """A 1 x 1 conv on a split shape merged with a 5 x 5 one whose input rows do
+    not fit: the stage runs on the conv's best other shape, not on 16 x 32 (251
+    and 294 us; two runs of one shape differ by about 1%)."""
+    rng = np.random.default_rng(29)
+    ops = [conv_op("a", 512, (1, 1), (0, 0)), conv_op("b", 16, (5, 5), (2, 2))]
+    ten = {}
+    for o in ops:
+        ten[o["name"] + ".w"] = (rng.standard_normal((o["cout"], 64, o["kh"], o["kw"])) / 30).astype(np.float32)
+        ten[o["name"] + ".b"] = rng.standard_normal(o["cout"]).astype(np.float32)
+    monkeypatch.delenv("IOS_CONV_TILE", raising=False)  # (the other shape is a measured one)
+    g = I.Graph({"batch": 1, "inputs": [{"name": "x", "c": 64, "h": 40, "w": 310}], "ops": ops, "outputs": ["a", "b"]}, ten)
+    u = [g.tid["a"], g.tid["b"]]
+    split, small = profiled(g, u, I.IOS_MERGE, (14, 1))
+    assert split < 0.93 * small, (split, small)
+    x = rng.standard_normal((1, 64, 40, 310)).astype(np.float32)
+    I.ios_set_conv_tile(g.handle, u[0], 14)
+    for o, y in zip(ops, launch(g, [u], [I.IOS_MERGE], x, ops, 40, 310)):
+        ref, bound = reference(x, ten[o["name"] + ".w"], ten[o["name"] + ".b"], o)
+        bound = bound * (25 * 64 + 8) / (64 * o["kh"] * o["kw"] + 8)
+        assert np.all(np.abs(y - ref) <= bound), o["name"]
+    g.close()
+
+
 def mixed(rng, shape, scale):
     """Ordinary values, the first rows of the first image scaled: tiles that
     hold both, and windows that hold the scaled ones only."""
