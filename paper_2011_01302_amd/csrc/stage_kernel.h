@@ -39,6 +39,7 @@ __device__ __forceinline__ floatx4 mfma16x16x4(float a, float b, floatx4 c) {
 // Pointers into the global address space (plain pointers are generic and
 // would make the compiler emit flat loads).
 typedef __attribute__((address_space(1))) const float gcfloat;
+typedef __attribute__((address_space(1))) float gfloat;
 __device__ __forceinline__ gcfloat *gp(const float *p) { return (gcfloat *)p; }
 
 // Raw buffer loads: SGPR resource + 32-bit VGPR offset + SGPR offset, no
@@ -74,7 +75,11 @@ __device__ __forceinline__ float bias32_of(float bl, int r, int lane) {
 
 // Activation accesses.  COH = true for outputs consumed by another tile of
 // the same launch: agent-coherent (sc1) stores, performed beyond the
-// XCD-private caches, so no L2 writeback is needed before signalling.
+// XCD-private caches, so no L2 writeback is needed before signalling.  Stores
+// go to the global address space: with a flat store possibly in flight on some
+// path (the variants of a tile follow one another in the control flow graph)
+// the compiler waits for every load, and a loop that keeps its next weights in
+// flight would wait for those too.
 template <bool COH>
 __device__ __forceinline__ float ld(const float *p) {
   if constexpr (COH) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -82,8 +87,8 @@ __device__ __forceinline__ float ld(const float *p) {
 }
 template <bool COH>
 __device__ __forceinline__ void st(float *p, float v) {
-  if constexpr (COH) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  else *p = v;
+  if constexpr (COH) __hip_atomic_store((gfloat *)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *(gfloat *)p = v;
 }
 
 // Operator descriptors and buffer pointers live in LDS (the workgroup copies
@@ -785,7 +790,6 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
     for (int k = 0; k < 3; ++k)
       a[k] = __builtin_bit_cast(uintx4, __builtin_amdgcn_raw_buffer_load_b128(wr, alane + k * 1024, soff, 0));
   };
-  uintx4 a0[3], a1[3];
 
   // virtual row of the tile's first pixel
   int vlo = 0;
@@ -906,6 +910,7 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
   };
 
   auto rounds = [&](auto fp32) {
+    uintx4 a0[3], a1[3];
 #pragma unroll
     for (int pb = 0; pb < PB; ++pb)
 #pragma unroll
@@ -914,8 +919,11 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
       if constexpr (PB == 1 && !fp32) weights(c0, wk, a0);   // the first weights in flight beside the patch
       stage(c0, fp32);
       if constexpr (PB != 1 || fp32) weights(c0, wk, a0);
-      if constexpr (!fp32)
+      if constexpr (!fp32) {
         if (c0 == 0 && tid < BN) biasl[tid] = bias;
+        // the tile's range check, complete with the last round
+        if (c0 + SC >= nch && __ballot(range.out()) && lane == 0) *flags = 1;
+      }
       ring_barrier();
       const int nks = min(SC, nch - c0) * taps;
       for (int ks = wk; ks < nks;) {                   // one k-step of weights in flight
@@ -934,9 +942,6 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
     }
   };
   rounds(std::false_type{});
-  // the tile's range check
-  if (__ballot(range.out()) && lane == 0) *flags = 1;
-  ring_barrier();
   if (__builtin_amdgcn_readfirstlane((int)*flags)) rounds(std::true_type{});
   float *red = lds;                                   // [wk][block][16][64]
   const int nblk = (PB << lwm) << lwn;
@@ -1900,6 +1905,8 @@ __device__ __forceinline__ void sep_split_tile(const Slots &sl, const SepSplitDe
 #pragma unroll
           for (int i = 0; i < PX; ++i)
             if (px0 + i < cnt) range.add(d[i][q]);
+        // the tile's range check, complete with the last chunk
+        if (c + 1 == nch && __ballot(range.out()) && lane == 0) *flags = 1;
       }
       filters(c + 1);
       // the three parts: two bf16 of the 16 bytes of (part, half, px)
@@ -1958,9 +1965,6 @@ __device__ __forceinline__ void sep_split_tile(const Slots &sl, const SepSplitDe
     }
   };
   chunks(std::false_type{});
-  // the tile's range check
-  if (__ballot(range.out()) && lane == 0) *flags = 1;
-  ring_barrier();
   if (__builtin_amdgcn_readfirstlane((int)*flags)) chunks(std::true_type{});
   const bool post = o.post_relu != 0;
   float *const out0 = sl[o.route_slot];
