@@ -65,6 +65,88 @@ static std::vector<int> ops_of_units(const ios_graph *g, const int32_t *ids, int
   return ops;
 }
 
+namespace {
+
+// A stage whose best choice without split shapes is within this of its best
+// choice with them is decided in whole passes.
+constexpr double kNearTie = 1.3;
+// Passes per measurement and measurements per choice in decide_in_pass (at least).
+constexpr int kPassReps = 6, kPassRepeats = 4;
+
+std::vector<int> stage_ops(const ios_graph *g, const ios_schedule_t *q, size_t k) {
+  std::vector<int> ops;
+  for (int i = q->offsets[k]; i < q->offsets[k + 1]; ++i) ops.push_back(unit_op_of_tensor(g, q->unit_ids[i]));
+  return ops;
+}
+
+// the tile choices of a stage's operators
+typedef std::vector<std::array<int, 3>> Choice;
+Choice choice_of(const ios_graph *g, const std::vector<int> &ops) {
+  Choice c;
+  for (int op : ops) c.push_back({g->ops[op].tcfg, g->ops[op].sep_tile, g->ops[op].xcd_lg});
+  return c;
+}
+void set_choice(ios_graph *g, const std::vector<int> &ops, const Choice &c) {
+  for (size_t i = 0; i < ops.size(); ++i) {
+    g->ops[ops[i]].tcfg = c[i][0];
+    g->ops[ops[i]].sep_tile = c[i][1];
+    g->ops[ops[i]].xcd_lg = c[i][2];
+  }
+}
+
+struct Tie {
+  int stage;
+  Choice plain, split;
+  int64_t plain_ns, split_ns;    // the stage alone
+};
+
+// A stage measured alone finds its kernel's code and its weights in the
+// caches, where a pass through the whole schedule does not: a split tile's
+// weights are half as large again, and a kernel variant that no other stage
+// uses is fetched anew.  So the stages in `ties` are decided by whole passes,
+// each with its other choice in turn, the rest as chosen.  SqueezeNet stack,
+// batch 1: two stages whose split shapes were a few percent faster alone made
+// the pass 3 us (3%) longer.  Returns what the sum of the stages' times
+// changes by.
+int64_t decide_in_pass(ios_graph *g, ios_schedule_t *q, const std::vector<Tie> &ties, const ios_sched_opts &o) {
+  int64_t change = 0;
+  if (ties.empty() || q->strategies.size() < 2) return change;
+  struct Owned {
+    std::vector<std::unique_ptr<CompiledStage>> v;
+    ~Owned() {
+      for (auto &cs : v)
+        if (cs) free_stage(cs.get());
+    }
+  } pass, other;
+  auto compiled = [&](Owned &to, size_t k) {
+    to.v.emplace_back(new CompiledStage);
+    compile_stage(g, stage_ops(g, q, k), q->strategies[k], to.v.back().get(), false);
+  };
+  for (size_t k = 0; k < q->strategies.size(); ++k) compiled(pass, k);
+  for (const Tie &t : ties) {
+    const std::vector<int> ops = stage_ops(g, q, t.stage);
+    set_choice(g, ops, t.plain);
+    compiled(other, t.stage);
+    auto &slot = pass.v[t.stage], &alt = other.v.back();
+    int64_t split_ns = INT64_MAX, plain_ns = INT64_MAX;
+    for (int r = 0; r < std::max(kPassRepeats, o.repeats); ++r) {
+      split_ns = std::min(split_ns, profile_pass(g, pass.v, kPassReps));
+      std::swap(slot, alt);
+      plain_ns = std::min(plain_ns, profile_pass(g, pass.v, kPassReps));
+      std::swap(slot, alt);
+    }
+    if (plain_ns < split_ns) {
+      std::swap(slot, alt);
+      change += t.plain_ns - t.split_ns;
+    } else {
+      set_choice(g, ops, t.split);
+    }
+  }
+  return change;
+}
+
+}  // namespace
+
 extern "C" {
 
 const char *ios_last_error(void) { return g_last_error; }
@@ -280,7 +362,6 @@ static constexpr double kStageTileSlack = 0.02;
 // A value whose stage is slower than the best by more than this in a few
 // launches is not measured in full.
 static constexpr double kStageScreen = 1.25;
-
 int ios_schedule_tune_tiles(ios_graph *g, ios_schedule_t *q, const ios_sched_opts *opts,
                             int64_t *cost_ns) {
   return guarded([&] {
@@ -301,14 +382,13 @@ int ios_schedule_tune_tiles(ios_graph *g, ios_schedule_t *q, const ios_sched_opt
       saved.push_back({op, g->ops[op].tcfg, g->ops[op].xcd_lg, g->ops[op].sep_tile});
     }
     int64_t total = 0;
+    std::vector<Tie> ties;
     try {
       for (size_t k = 0; k < q->strategies.size(); ++k) {
-        std::vector<int> ops, convs;
-        for (int i = q->offsets[k]; i < q->offsets[k + 1]; ++i) {
-          const int op = unit_op_of_tensor(g, q->unit_ids[i]);
-          ops.push_back(op);
+        const std::vector<int> ops = stage_ops(g, q, k);
+        std::vector<int> convs;
+        for (int op : ops)
           if (g->ops[op].d.kind == IOS_CONV) convs.push_back(op);
-        }
         const int strat = q->strategies[k];
         auto measure = [&] { return profile_stage(g, ops, strat, o.warmup, o.reps, o.repeats); };
         // whether a value is worth measuring in full: a few launches first
@@ -316,13 +396,18 @@ int ios_schedule_tune_tiles(ios_graph *g, ios_schedule_t *q, const ios_sched_opt
           if (o.reps * o.repeats < 8) return true;
           return (double)profile_stage(g, ops, strat, 1, std::max(2, o.reps / 2), 1) <= (double)best * kStageScreen;
         };
+        const auto has_split = [&] {
+          return std::any_of(convs.begin(), convs.end(), [&](int c) { return tile_is_split(g->ops[c].tcfg); });
+        };
         for (int op : ops) g->ops[op].xcd_lg = -1;
-        int64_t best = measure();
+        int64_t best = 0;
         // the XCD run length of the stage's tile order (see the stage kernel):
         // the modelled choice, or an explicit one measured faster
         auto tune_xcd_order = [&] {
-          int keep = -1;
+          int keep = g->ops[ops[0]].xcd_lg;
+          const int was = keep;
           for (int lg : {0, 2, 4}) {
+            if (lg == was) continue;
             for (int op : ops) g->ops[op].xcd_lg = lg;
             const int64_t ns = measure();
             if ((double)ns < (double)best * (1.0 - kStageTileSlack)) {
@@ -331,7 +416,7 @@ int ios_schedule_tune_tiles(ios_graph *g, ios_schedule_t *q, const ios_sched_opt
             }
           }
           for (int op : ops) g->ops[op].xcd_lg = keep;
-          return keep >= 0;
+          return keep != was;
         };
         // knobs: the convs that take one tile shape together (all of a merge
         // stage's), and each SEPCONV's tile choice; in a concurrent stage
@@ -341,10 +426,10 @@ int ios_schedule_tune_tiles(ios_graph *g, ios_schedule_t *q, const ios_sched_opt
         struct Knob {
           std::vector<int> ops;
           bool sep;
-          int lo, hi;
         };
         std::vector<Knob> knobs;
         std::vector<int> seps;
+        int plain_shape = -1;    // a merge stage's shape in place of a split one
         for (int op : ops)
           if (g->ops[op].d.kind == IOS_SEPCONV) seps.push_back(op);
         if (!forced && !convs.empty()) {
@@ -353,29 +438,32 @@ int ios_schedule_tune_tiles(ios_graph *g, ios_schedule_t *q, const ios_sched_opt
             for (int c : convs)
               if (g->ops[c].d.cout > g->ops[largest].d.cout) largest = c;
             for (int c : convs) g->ops[c].tcfg = g->ops[largest].tcfg;
-            best = measure();
-            knobs.push_back({convs, false, 0, TC_COUNT - 1});
+            plain_shape = g->ops[largest].tcfg_fp32;
+            knobs.push_back({convs, false});
           } else {
-            if (convs.size() > 1) knobs.push_back({convs, false, 0, TC_COUNT - 1});
-            for (int c : convs) knobs.push_back({{c}, false, 0, TC_COUNT - 1});
+            if (convs.size() > 1) knobs.push_back({convs, false});
+            for (int c : convs) knobs.push_back({{c}, false});
           }
         }
         if (!sep_forced) {
-          if (seps.size() > 1) knobs.push_back({seps, true, 0, kSepTiles - 1});
-          for (int op : seps) knobs.push_back({{op}, true, 0, kSepTiles - 1});
+          if (seps.size() > 1) knobs.push_back({seps, true});
+          for (int op : seps) knobs.push_back({{op}, true});
         }
         auto val = [&](int op, bool sep) -> int & { return sep ? g->ops[op].sep_tile : g->ops[op].tcfg; };
         auto ok = [&](int op, bool sep, int v) {
-          return sep ? sep_tile_ok(g->ops[op], v) : conv_tile_ok(g->ops[op], v);
+          return sep ? sep_tile_runs(g->ops[op], v) : conv_tile_ok(g->ops[op], v);
         };
-        for (int pass = 0; pass < 2; ++pass) {
-          bool improved = pass == 0 && tune_xcd_order();
+        // every knob's values once (the convs' shapes lo .. hi; the SEPCONVs'
+        // too unless only split shapes are tried)
+        auto vary = [&](int lo, int hi) {
+          bool improved = false;
           for (const auto &kn : knobs) {
+            if (kn.sep && lo >= TC_S256x64) continue;
             // a value applies to the knob's operators that admit it; the
             // others keep theirs
             std::vector<int> keep;
             for (int c : kn.ops) keep.push_back(val(c, kn.sep));
-            for (int v = kn.lo; v <= kn.hi; ++v) {
+            for (int v = kn.sep ? 0 : lo; v <= (kn.sep ? kSepTiles - 1 : hi); ++v) {
               bool change = false;
               for (size_t i = 0; i < kn.ops.size(); ++i) change |= ok(kn.ops[i], kn.sep, v) && keep[i] != v;
               if (!change) continue;
@@ -391,10 +479,34 @@ int ios_schedule_tune_tiles(ios_graph *g, ios_schedule_t *q, const ios_sched_opt
             }
             for (size_t i = 0; i < kn.ops.size(); ++i) val(kn.ops[i], kn.sep) = keep[i];
           }
-          if (!improved) break;
+          return improved;
+        };
+        // the shapes that are no split ones first, from each conv's best of
+        // them, then the split ones from there and from the convs' own choices
+        const Choice own = choice_of(g, ops);
+        if (!forced)
+          for (int c : convs)
+            if (tile_is_split(g->ops[c].tcfg)) g->ops[c].tcfg = plain_shape >= 0 ? plain_shape : g->ops[c].tcfg_fp32;
+        best = measure();
+        bool improved = tune_xcd_order();
+        improved |= vary(0, TC_S256x64 - 1);
+        if (improved) vary(0, TC_S256x64 - 1);
+        if (!forced && !convs.empty()) {
+          const Choice plain = choice_of(g, ops);
+          const int64_t plain_ns = best;
+          set_choice(g, ops, own);
+          const int64_t ns = has_split() ? measure() : INT64_MAX;
+          if ((double)ns < (double)best * (1.0 - kStageTileSlack)) best = ns;
+          else set_choice(g, ops, plain);
+          improved = has_split() && tune_xcd_order();
+          improved |= vary(TC_S256x64, TC_COUNT - 1);
+          if (improved && has_split()) vary(0, TC_COUNT - 1);
+          if (has_split() && (double)plain_ns <= (double)best * kNearTie)
+            ties.push_back({(int)k, plain, choice_of(g, ops), plain_ns, best});
         }
         total += best;
       }
+      total += decide_in_pass(g, q, ties, o);
     } catch (...) {
       for (const auto &v : saved) {
         g->ops[v[0]].tcfg = v[1];
@@ -472,10 +584,8 @@ static void ensure_compiled(ios_graph *g, ios_schedule_t *q) {
   if (q->compiled.size() == q->strategies.size()) return;
   q->compiled.clear();
   for (size_t k = 0; k < q->strategies.size(); ++k) {
-    std::vector<int> ops;
-    for (int i = q->offsets[k]; i < q->offsets[k + 1]; ++i) ops.push_back(unit_op_of_tensor(g, q->unit_ids[i]));
     std::unique_ptr<CompiledStage> cs(new CompiledStage);
-    compile_stage(g, ops, q->strategies[k], cs.get(), false);
+    compile_stage(g, stage_ops(g, q, k), q->strategies[k], cs.get(), false);
     q->compiled.push_back(std::move(cs));
   }
 }

@@ -833,6 +833,31 @@ void launch_compiled(ios_graph *g, const CompiledStage &cs, const std::vector<fl
             "stage launch");
 }
 
+// A bounded intra-stage wait that gave up during a measurement makes the
+// latency meaningless: fail here (and clear the flag) rather than let a
+// later ios_device_status report it against ios_run.
+static void check_measured(ios_graph *g) {
+  int32_t err = 0;
+  hip_check(hipMemcpy(&err, g->d_err, sizeof(err), hipMemcpyDeviceToHost), "hipMemcpy(err)");
+  if (err) {
+    hip_check(hipMemset(g->d_err, 0, sizeof(int32_t)), "hipMemset(err)");
+    fail(IOS_E_DEVICE, "a stage kernel reported an error while the stage was being measured");
+  }
+}
+
+int64_t profile_pass(ios_graph *g, const std::vector<std::unique_ptr<CompiledStage>> &stages, int reps) {
+  const std::vector<float *> bufs = default_buffers(g);
+  hip_check(hipEventRecord(g->ev0, g->stream), "hipEventRecord");
+  for (int i = 0; i < reps; ++i)
+    for (const auto &cs : stages) launch_compiled(g, *cs, bufs, g->stream);
+  hip_check(hipEventRecord(g->ev1, g->stream), "hipEventRecord");
+  hip_check(hipEventSynchronize(g->ev1), "hipEventSynchronize");
+  float ms = 0.f;
+  hip_check(hipEventElapsedTime(&ms, g->ev0, g->ev1), "hipEventElapsedTime");
+  check_measured(g);
+  return (int64_t)((double)ms * 1e6 / reps + 0.5);
+}
+
 int64_t profile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, int warmup,
                       int reps, int repeats) {
   if (reps < 1 || repeats < 1 || warmup < 0) fail(IOS_E_ARG, "bad profiling counts");
@@ -850,15 +875,7 @@ int64_t profile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, i
     hip_check(hipEventElapsedTime(&ms, g->ev0, g->ev1), "hipEventElapsedTime");
     per.push_back((double)ms * 1e6 / reps);
   }
-  // a bounded intra-stage wait that gave up during the measurement makes the
-  // latency meaningless: fail here (and clear the flag) rather than let a
-  // later ios_device_status report it against ios_run
-  int32_t err = 0;
-  hip_check(hipMemcpy(&err, g->d_err, sizeof(err), hipMemcpyDeviceToHost), "hipMemcpy(err)");
-  if (err) {
-    hip_check(hipMemset(g->d_err, 0, sizeof(int32_t)), "hipMemset(err)");
-    fail(IOS_E_DEVICE, "a stage kernel reported an error while the stage was being measured");
-  }
+  check_measured(g);
   std::sort(per.begin(), per.end());
   return (int64_t)(per[per.size() / 2] + 0.5);
 }

@@ -383,6 +383,12 @@ bool sep_tile_ok(const Op &op, int tile) {
          sep_row_lds_bytes(round_up(op.cin, 4), K, nbt) <= kSepMaxLds;
 }
 
+bool sep_tile_runs(const Op &op, int tile) {
+  if (!sep_tile_ok(op, tile)) return false;
+  return tile < kSepgFirst || tile >= kSepLineFirst ||
+         (op.split_ok && sep_split_geometry(tile - kSepgFirst, op.batch, op.d.kh, op.ho, op.wo).tp > 0);
+}
+
 // SEPCONV tile choice before measurement (IOS_SEP_TILE=<0..10> forces one;
 // a choice the operator cannot use falls back to the staged tile of 16
 // pixels).
@@ -443,8 +449,11 @@ void finalize_graph(ios_graph *g) {
     } else if (op.d.kind == IOS_SEPCONV) {
       op.CinP = round_up(op.cin, 16);
       op.Npad = round_up(op.d.cout, 16);
+      op.batch = g->batch;
       const size_t ndw = (size_t)op.cin * op.d.kh * op.d.kw;
-      op.split_ok = split_weights_ok(op.w.data() + ndw, op.w.size() - ndw);
+      // (the kernel's byte offsets into the parts are 32 bits)
+      op.split_ok = split_weights_ok(op.w.data() + ndw, op.w.size() - ndw) &&
+                    split_words(op.d.cout, op.cin, 1, 1) * sizeof(float) < (size_t)1 << 31;
       op.sep_tile = choose_sep_tile(op);
     }
   }
@@ -613,7 +622,7 @@ void ensure_device(ios_graph *g) {
       int best = op.sep_tile;
       int64_t best_ns = INT64_MAX;
       for (int t = 0; t < kSepTiles; ++t) {
-        if (!sep_tile_ok(op, t)) continue;
+        if (!sep_tile_runs(op, t)) continue;
         op.sep_tile = t;
         int64_t ns = profile_stage(g, {oi}, IOS_CONCURRENT, 2, 10, 3);
         if (ns < best_ns) { best_ns = ns; best = t; }

@@ -303,6 +303,9 @@ SepGeom sep_geometry(int tile, int cin, int cout, int w, int ho, int wo, int kh,
 // Whether SEPCONV tile choice `tile` can run `op` (graph.cpp).
 struct Op;
 bool sep_tile_ok(const Op &op, int tile);
+// whether the choice runs as itself: 7 and 8 are taken where sep_split_ok says so, but run another tile where the
+// split tile does not apply
+bool sep_tile_runs(const Op &op, int tile);
 bool conv_tile_ok(const Op &op, int cfg);
 __host__ __device__ inline int sep_pitch(int bm) { return (bm & 31) == 16 ? bm : bm + 16; }
 // Row tile: the depthwise window padded to K x K, K = 3 or 5 (0 = too
@@ -512,7 +515,7 @@ struct Op {
   int unit = -1;                 // index among schedule units, -1 for views
   int block = -1, local = -1;    // block and bit inside the block
   int cin = 0, h = 0, wd = 0, ho = 0, wo = 0;
-  int batch = 1;                 // CONV: the graph's batch, set at finalize
+  int batch = 1;                 // CONV, SEPCONV: the graph's batch, set at finalize
   // device copies (units only)
   int CinP = 0, Npad = 0, NG = 0, tcfg = TC_16x32_K8;
   int tcfg_fp32 = TC_16x32_K8;   // CONV: the best shape that is no split one, for stages where those do not fit
@@ -643,6 +646,8 @@ void compile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, Comp
 void free_stage(CompiledStage *cs);
 void launch_compiled(ios_graph *g, const CompiledStage &cs, const std::vector<float *> &buf_ptr,
                      hipStream_t stream);
+// ns per pass through compiled stages, `reps` passes one after another
+int64_t profile_pass(ios_graph *g, const std::vector<std::unique_ptr<CompiledStage>> &stages, int reps);
 int64_t profile_stage(ios_graph *g, const std::vector<int> &ops, int strategy, int warmup,
                       int reps, int repeats);
 std::vector<float *> default_buffers(const ios_graph *g);

@@ -110,7 +110,7 @@ struct Provider {
       for (int oi : ops) {
         Op &op = g->ops[oi];
         if (op.d.kind != IOS_SEPCONV) continue;
-        const int v = sep_tile_ok(op, first) ? first : sep_tile_ok(op, second) ? second : -1;
+        const int v = sep_tile_runs(op, first) ? first : sep_tile_runs(op, second) ? second : -1;
         if (v < 0 || v == op.sep_tile) continue;
         saved.push_back({oi, op.sep_tile});
         op.sep_tile = v;
