@@ -48,24 +48,70 @@ def gfx950_code_objects(path):
     return out
 
 
-def masked_readlanes(lines):
-    """(function, line) of every v_readlane_b32 inside an exec-narrowed
-    region whose source VGPR is not a compiler spill register."""
-    spill = set(re.findall(r"v_writelane_b32 (v\d+),", "\n".join(lines)))
-    bad, depth, fn = [], 0, None
+def functions(lines):
+    """(name, [(address or None, text)]) of every function."""
+    fn, body = None, []
     for ln in lines:
         m = re.match(r"^[0-9a-f]+ <(\S+)>:", ln)
         if m:
-            fn, depth = m.group(1), 0
+            if fn is not None:
+                yield fn, body
+            fn, body = m.group(1), []
             continue
-        t = ln.strip()
-        if t.startswith("s_and_saveexec_b64"):
-            depth += 1
-        elif t.startswith("s_or_b64 exec, exec,") and depth > 0:
-            depth -= 1
-        elif t.startswith("v_readlane_b32"):
-            src = t.split()[2].rstrip(",")
-            if depth > 0 and src not in spill:
+        m = re.match(r"^\s+(\S.*?)\s*(?://\s*([0-9A-F]+):.*)?$", ln)
+        if m and fn is not None:
+            body.append((int(m.group(2), 16) if m.group(2) else None, m.group(1)))
+    if fn is not None:
+        yield fn, body
+
+
+def masked_readlanes(lines):
+    """(function, line) of every v_readlane_b32 that some path reaches with
+    the exec mask narrowed and whose source VGPR is not a compiler spill
+    register.  Along a path, s_and_saveexec opens a region, named by the
+    register that holds the mask, and s_or_b64 exec, exec, <register> ends it
+    (where there is an else part, s_xor_b64 and s_or_saveexec move the mask to
+    another register); branches are followed by their targets (the compiler places the body of a
+    region before its start where a loop is rotated)."""
+    spill = set(re.findall(r"v_writelane_b32 (v\d+),", "\n".join(lines)))
+    bad = []
+    for fn, body in functions(lines):
+        at = {addr: i for i, (addr, _) in enumerate(body) if addr is not None}
+        state = [None] * len(body)                     # open regions on entry, over all paths
+        work = [(0, frozenset())] if body else []
+        while work:
+            i, regions = work.pop()
+            while i < len(body):
+                if state[i] is not None and regions <= state[i]:
+                    break
+                state[i] = regions = regions | (state[i] or frozenset())
+                addr, t = body[i]
+                op = t.split()[0]
+                args = [w.rstrip(",") for w in t.split()[1:4]]
+                if op == "s_and_saveexec_b64":
+                    regions = regions | {args[0]}
+                elif op == "s_xor_b64" and args[1] == "exec" and args[0] != "exec" and args[2] in regions:
+                    regions = regions - {args[2]} | {args[0]}
+                elif op in ("s_or_saveexec_b64", "s_andn2_saveexec_b64"):
+                    regions = regions - {args[1]} | {args[0]}
+                elif t.startswith("s_or_b64 exec, exec,"):
+                    regions = regions - {t.split()[3]}
+                elif op == "s_mov_b64" and t.split()[1] == "exec,":
+                    regions = frozenset()
+                elif op == "s_endpgm":
+                    break
+                elif op.startswith(("s_cbranch", "s_branch")):
+                    simm = int(t.split()[1])
+                    target = addr + 4 + 4 * (simm - 65536 if simm >= 32768 else simm)
+                    if op == "s_branch":
+                        i = at[target]
+                        continue
+                    # nothing runs where no lane is on: the branch around a
+                    # region's body leads to its end
+                    work.append((at[target], regions))
+                i += 1
+        for (_, t), regions in zip(body, state):
+            if t.startswith("v_readlane_b32") and regions and t.split()[2].rstrip(",") not in spill:
                 bad.append((fn, t))
     return bad
 
@@ -87,8 +133,10 @@ def disassembly(tmp_path_factory):
 def test_stage_kernels_present(disassembly):
     names = {re.match(r"^[0-9a-f]+ <(\S+)>:", l).group(1) for l in disassembly
              if re.match(r"^[0-9a-f]+ <(\S+)>:", l)}
-    # every kernel variant (light / sep / seprow / pipe / full) x launch kind (tile / persistent)
+    # every kernel variant (light / sep / seprow / pipe / full; split / sepsplit) x launch kind (tile / persistent)
     assert len({n for n in names if "ios_stage_kernel" in n}) == 10
+    assert len({n for n in names if "ios_split_kernel" in n}) == 4
+    assert any("pack_split_kernel" in n for n in names)
 
 
 def test_no_readlane_of_possibly_disabled_lanes(disassembly):
@@ -108,4 +156,17 @@ def test_the_scan_finds_a_planted_case():
              "  s_or_b64 exec, exec, s[6:7]",
              "  v_readlane_b32 s9, v3, 1"]
     assert masked_readlanes(lines) == [("_Zkern", "v_readlane_b32 s8, v2, 7")]
+    # a region whose body stands before its start (found), and code after the
+    # branch that leaves it (allowed)
+    lines = ["0000000000001000 <_Zkern>:",
+             "  s_branch 4  // 000000001000: 00",
+             "  v_readlane_b32 s5, v3, 0  // 000000001004: 00",
+             "  s_or_b64 exec, exec, s[6:7]  // 00000000100C: 00",
+             "  s_endpgm  // 000000001010: 00",
+             "  v_readlane_b32 s4, v1, 3  // 000000001014: 00"]
+    lines += ["  s_and_saveexec_b64 s[6:7], vcc  // 00000000101C: 00",
+              "  s_cbranch_execnz 65528  // 000000001020: 00",
+              "  s_branch 65529  // 000000001024: 00",
+              "  v_readlane_b32 s9, v3, 1  // 000000001028: 00"]
+    assert masked_readlanes(lines) == [("_Zkern", "v_readlane_b32 s5, v3, 0")]
 
