@@ -159,7 +159,7 @@ def test_parity_operator_merge(config, groups):
     g.close()
 
 
-@pytest.mark.parametrize("tile", [str(t) for t in range(12)])
+@pytest.mark.parametrize("tile", [str(t) for t in range(I.IOS_CONV_TILE_SHAPES)])
 def test_parity_every_conv_tile_shape(tile, monkeypatch):
     monkeypatch.setenv("IOS_CONV_TILE", tile)
     for config in ["tiny", "inception", "squeeze"]:
@@ -274,14 +274,15 @@ def test_conv_tile_shapes_read_and_replayed():
     with pytest.raises(I.IosError) as e:
         I.ios_get_conv_tile(g.handle, g.tid["pool"])
     assert e.value.name == "IOS_E_ARG"
-    for k, n in enumerate(convs):
-        I.ios_set_conv_tile(g.handle, g.tid[n], k % I.IOS_CONV_TILE_SHAPES)
-    assert [I.ios_get_conv_tile(g.handle, g.tid[n]) for n in convs] == \
-        [k % I.IOS_CONV_TILE_SHAPES for k in range(len(convs))]
-    for mode in (I.IOS_SCHED_SEQUENTIAL, I.IOS_SCHED_GREEDY):
-        q = sched(g, mode)
-        check(run(g, q, spec, ten), reference("inception"), f"inception/replayed tiles/mode{mode}")
-        I.ios_schedule_destroy(q)
+    for first in (0, 7, 13):                        # seven convs: every shape once
+        want = [(first + k) % I.IOS_CONV_TILE_SHAPES for k in range(len(convs))]
+        for n, v in zip(convs, want):
+            I.ios_set_conv_tile(g.handle, g.tid[n], v)
+        assert [I.ios_get_conv_tile(g.handle, g.tid[n]) for n in convs] == want
+        for mode in (I.IOS_SCHED_SEQUENTIAL, I.IOS_SCHED_GREEDY):
+            q = sched(g, mode)
+            check(run(g, q, spec, ten), reference("inception"), f"inception/replayed tiles from {first}/mode{mode}")
+            I.ios_schedule_destroy(q)
     g.close()
 
 
@@ -397,7 +398,8 @@ def test_parity_batched_every_image(config, batch, kinds):
     the DP's schedule (on-device profiling, light) where the search is
     affordable, a one-stage chained schedule for NASNet and a baseline; the
     "_tuned" kinds then choose every stage's tiles in its company
-    (ios_schedule_tune_tiles: pipelined conv shapes, the GEMM SEPCONV tile)."""
+    (ios_schedule_tune_tiles: pipelined and split conv shapes, the split SEPCONV
+    tile)."""
     spec, ten, refs = batched_reference(config, batch)
     g = I.Graph(spec, ten)
     for kind in kinds:
@@ -419,8 +421,8 @@ def test_parity_batched_every_image(config, batch, kinds):
 
 
 def sepg_spec(batch):
-    """SEPCONVs the 64-column GEMM tile applies to (planes up to 32 wide):
-    21x21 planes (3 output rows per tile, the last tile of an image short),
+    """SEPCONVs the 64-pixel split tile applies to (planes up to 32 wide):
+    20x21 planes (tiles of 64 pixels, the last one of an image short),
     40 input channels (a short last chunk), 100 output channels (a short
     channel tile), 3x3 and 5x5 windows, chained."""
     sep = lambda n, i, co, k: {"name": n, "kind": "sepconv", "in": [i], "cout": co, "kh": k, "kw": k, "sh": 1,
@@ -431,10 +433,10 @@ def sepg_spec(batch):
 
 
 @pytest.mark.parametrize("tile", ["7", "8"])
-def test_parity_sepconv_gemm_batched(tile, monkeypatch):
-    """The GEMM SEPCONV tile forced on every unit of a NASNet cell (128
-    columns: 42-wide planes) or of sepg_spec (64 columns), over three images
-    (row blocks of every image, halo rows at image borders), under greedy
+def test_parity_sepconv_split_batched(tile, monkeypatch):
+    """The split SEPCONV tile forced on every unit of a NASNet cell (128
+    pixels: 42-wide planes) or of sepg_spec (64 pixels), over three images
+    (tiles of every image, halo rows at image borders), under greedy
     stages and one chained stage."""
     monkeypatch.setenv("IOS_SEP_TILE", tile)
     if tile == "7":
@@ -569,14 +571,17 @@ def ragged_spec(batch, cin=13):
 
 # tile None: shapes chosen by measurement, else forced; offset: inputs start
 # 1 or 3 floats past a 16-byte boundary; the pipelined shapes (6 .. 11) need
-# input channels in multiples of 16, so their cases take 32
+# input channels in multiples of 16, so their cases take 32; 12 .. 19 are the
+# split shapes (in the chained stages beside SEPCONVs: the full variant)
 @pytest.mark.parametrize("batch,tile,offset", [(1, None, 0), (2, None, 0), (1, "1", 1), (1, "0", 3),
                                                (2, "4", 1), (2, "6", 1), (3, "7", 0), (1, "8", 3),
-                                               (2, "9", 3), (3, "10", 1), (1, "11", 0)])
+                                               (2, "9", 3), (3, "10", 1), (1, "11", 0),
+                                               (2, "12", 1), (1, "13", 0), (3, "14", 3), (2, "15", 0),
+                                               (1, "16", 1), (3, "17", 0), (2, "18", 3), (1, "19", 1)])
 def test_parity_ragged_shapes(batch, tile, offset, monkeypatch):
     if tile is not None:
         monkeypatch.setenv("IOS_CONV_TILE", tile)
-    spec = ragged_spec(batch, 32 if tile is not None and int(tile) >= 6 else 13)
+    spec = ragged_spec(batch, 32 if tile is not None and 6 <= int(tile) <= 11 else 13)
     ten = W.make_tensors(spec, 3)
     ref = E.outputs(spec, ten)
     g = I.Graph(spec, ten)
@@ -622,7 +627,7 @@ def test_parity_pool_planes(batch):
     g.close()
 
 
-@pytest.mark.parametrize("tile", ["0", "1", "4", "6", "7", "8", "9", "10", "11"])
+@pytest.mark.parametrize("tile", ["0", "1", "4"] + [str(t) for t in range(6, I.IOS_CONV_TILE_SHAPES)])
 def test_parity_conv_tiles_batched_small(tile, monkeypatch):
     """Forced conv tile shapes over several small images (the 16-pixel
     blocks of an 8x8 plane never span two images)."""
@@ -636,16 +641,56 @@ def test_parity_conv_tiles_batched_small(tile, monkeypatch):
     g.close()
 
 
+def slices_spec(batch):
+    """Convs that write into a concat and read its slices (channel offsets 0
+    and 48 of 88) and the whole of it, in one chain."""
+    conv = lambda n, i, co, k, s=1, pre=0: {"name": n, "kind": "conv", "in": [i], "cout": co, "kh": k, "kw": k, "sh": s,
+                                            "sw": s, "ph": k // 2, "pw": k // 2, "pre_relu": pre, "post_relu": 1}
+    ops = [conv("a", "x", 48, 3), conv("b", "x", 40, 1),
+           {"name": "cat", "kind": "concat", "in": ["a", "b"]},
+           conv("d", "a", 33, 3), conv("e", "b", 50, 5, pre=1), conv("f", "cat", 20, 3, s=2),
+           {"name": "mp", "kind": "maxpool", "in": ["b"], "kh": 3, "kw": 3, "sh": 1, "sw": 1, "ph": 1, "pw": 1}]
+    return {"name": "slices", "batch": batch, "inputs": [{"name": "x", "c": 32, "h": 12, "w": 13}], "ops": ops,
+            "outputs": ["cat", "d", "e", "f", "mp"]}
+
+
+# shapes of a, b, d, e, f: all split (the split variant), and split beside
+# pipelined and direct ones (the full variant)
+@pytest.mark.parametrize("shapes", [(12, 13, 14, 15, 16), (17, 18, 19, 12, 15), (14, 17, 16, 19, 13),
+                                    (6, 4, 13, 17, 1), (18, 9, 12, 3, 16), (15, 5, 0, 14, 19)])
+@pytest.mark.parametrize("scale", [1.0, 1e25])
+def test_parity_split_tiles_in_chains(shapes, scale, monkeypatch):
+    """Split conv tiles in one chained stage (persistent: coherent stores,
+    counters, LDS reused from tile to tile), reading and writing concat slices,
+    under every XCD order, and in stages of independent units; 1e25: every tile
+    runs a second time with fp32 products."""
+    spec = slices_spec(3)
+    ten = dict(W.make_tensors(spec, 7))
+    ten["x"] = (ten["x"] * np.float32(scale)).astype(np.float32)
+    ref = E.outputs(spec, ten)
+    monkeypatch.setenv("IOS_CONV_TILE", "1")            # no tile measurement at set-up
+    g = I.Graph(spec, ten)
+    for n, v in zip("abdef", shapes):
+        I.ios_set_conv_tile(g.handle, g.tid[n], v)
+    for lg in ("0", "2", "4"):
+        monkeypatch.setenv("IOS_XCD_RUNS", lg)
+        for q in (block_stages(g), sched(g, I.IOS_SCHED_GREEDY)):
+            for r in range(2):
+                check(run(g, q, spec, ten), ref, f"slices/{shapes}/xcd {lg}/{scale:g}/run {r}")
+            I.ios_schedule_destroy(q)
+    g.close()
+
+
 @pytest.mark.parametrize("tile", [str(t) for t in range(11)])
 def test_parity_every_sepconv_tile(tile, monkeypatch):
     # SEPCONV tile choice (staged: 16, 32 or 64 output pixels per tile; row:
-    # 1 to 4 channel blocks; GEMM: whole rows in 128 or 64 columns; line:
+    # 1 to 4 channel blocks; split: 128 or 64 pixels; line:
     # 32 / W whole rows x 32 or 64 channels, RandWire's 28-wide nodes), forced
     # instead of measured (a unit a choice does not apply to falls back to
     # the staged tile: the wide 7x7 unit and multi-input sums for the row and
-    # GEMM tiles; the 3x3 unit over 280 channels, ragged's 5x5 unit over 21
+    # split tiles; the 3x3 unit over 280 channels, ragged's 5x5 unit over 21
     # channels on a 9x11 plane and the NASNet / RandWire single-input units
-    # run on the GEMM tile)
+    # run on the split tile)
     monkeypatch.setenv("IOS_SEP_TILE", tile)
     for config in ["randwire", "nasnet"]:
         spec, ten = case(config)

@@ -2,13 +2,14 @@
 products summed in fp32) at the sizes where they can go wrong: channel tails,
 tiles that cross rows and images, strides, windows of one row or column,
 padded 1 x 1 windows, merged destinations, an input ReLU, and values outside
-the range in which the parts are exact (computed in fp32 instead).
+the range in which the parts are exact (a second run of the tile, in fp32).
 
-Tolerance: an operand's three parts leave at most 2^-27 of it, the products
-left out are below 2^-26 of a product, and the fp32 sums of n terms err by at
-most n 2^-24 of the sum of the terms' magnitudes; per output the error is at
-most (K + 8) 2^-24 sum |x| |w|, K the reduction length (the six products of 16
-terms are K 6 / 16 additions)."""
+Tolerance: an operand's three parts add up to it; with |x2| <= 2^-8 and |x3| <=
+2^-17 of x's power of two the products left out (x2 w3, x3 w2, x3 w3) are below
+2^-24 + 2^-34 of a product, and the fp32 sums of n terms err by at most n 2^-24
+of the sum of the terms' magnitudes; per output the error is at most (K + 8)
+2^-24 sum |x| |w|, K the reduction length (the six products of 16 terms are
+K 6 / 16 additions, so K >= 1 leaves room for the products left out)."""
 import numpy as np
 import pytest
 
@@ -120,7 +121,7 @@ def test_split_merge_has_every_destination(tile, monkeypatch):
 @pytest.mark.parametrize("scale", [1e-38, 1e-30, 1e-14, 1e25, 1e30, "inf", "nan"])
 def test_split_values_out_of_range(scale, monkeypatch):
     """Inputs so small or large that bf16 parts would lose bits or overflow,
-    an infinity and a NaN: as plain fp32 sums give them."""
+    an infinity and a NaN: as plain fp32 sums give them (1e-30, 1e-14: in range)."""
     rng = np.random.default_rng(3)
     n, c, h, w, cout = 2, 20, 9, 9, 40
     x = rng.standard_normal((n, c, h, w)).astype(np.float32)
@@ -286,7 +287,7 @@ SEP_CASES = {
     "one row per image": (3, 16, 1, 8, 32, 3),
     "more than 192 channels": (1, 40, 8, 12, 400, 3),
     "rows of four": (2, 18, 9, 4, 33, 5),
-    "rows of three": (2, 18, 9, 3, 33, 3),
+    "rows of three (the staged tile)": (2, 18, 9, 3, 33, 3),
     "odd pixel count": (1, 48, 13, 13, 64, 5),
 }
 
