@@ -198,7 +198,10 @@ int ios_set_conv_tile(ios_graph *g, int32_t unit_id, int32_t shape);
  * input channels and windows up to 5 x 5; 7, 8: 128 or 64 output pixels x
  * 192 or 384 output channels with the pointwise operands split into three
  * bf16 parts, for one input and a 3 x 3 or 5 x 5 window that keeps the plane
- * size, at least two of whose rows fit the pixels; 9, 10: 32 / W whole
+ * size, at least two of whose rows fit the pixels (where the pointwise
+ * weights are out of the range given for conv shapes 12 .. 19, rows have
+ * fewer than four floats or a stage's table leaves too little LDS, choice 1,
+ * or 0, runs instead); 9, 10: 32 / W whole
  * output rows x 32 or 64 output channels, with 16-byte loads, for a 3 x 3
  * window that keeps the plane size, rows of a multiple of 4 up to 32 floats
  * and at most 96 input channels), 0 for the other kinds;
@@ -294,7 +297,11 @@ int ios_schedule_stats(const ios_schedule_t *q, int64_t *states, int64_t *transi
  * stage's company: in a concurrent stage first all its convs (all its
  * SEPCONVs) moved to one value together, then one operator at a time, each
  * value tried, a change kept when the stage gets more than 2% faster (two
- * passes); a merge stage's convs take one shape together.  The choices stay
+ * rounds); a merge stage's convs take one shape together.  Conv shapes
+ * 12 .. 19 are tried after the others; where a stage's best choice with one is
+ * less than 1.3 times as fast as its best without, (3) whole passes of q with
+ * either decide (a stage measured alone finds its code and weights in the
+ * caches).  The choices stay
  * set on the graph's units (ios_get_conv_tile reads the shapes), so call it
  * on the schedule that will run; q's stages are recompiled on its next run.
  * A unit belongs to one stage of a schedule, so the stages do not compete.

@@ -274,7 +274,7 @@ int ios_set_conv_tile(ios_graph *g, int32_t unit_id, int32_t shape) {
     const int op = unit_op_of_tensor(g, unit_id);
     need(g->ops[op].d.kind == IOS_CONV, "not a conv unit");
     need(shape >= 0 && shape < TC_COUNT, "tile shape out of range");
-    need(conv_tile_ok(g->ops[op], shape), "pipelined tile shape not applicable to this conv");
+    need(conv_tile_ok(g->ops[op], shape), "pipelined or split tile shape not applicable to this conv");
     ensure_device(g);
     g->ops[op].tcfg = shape;
   });
@@ -298,7 +298,7 @@ int ios_set_unit_tiling(ios_graph *g, int32_t unit_id, int32_t tile, int32_t xcd
     need(xcd_lg == -1 || xcd_lg == 0 || xcd_lg == 2 || xcd_lg == 4, "xcd_lg must be -1, 0, 2 or 4");
     if (op.d.kind == IOS_CONV) {
       need(tile >= 0 && tile < TC_COUNT, "conv tile shape out of range");
-      need(conv_tile_ok(op, tile), "pipelined tile shape not applicable to this conv");
+      need(conv_tile_ok(op, tile), "pipelined or split tile shape not applicable to this conv");
     } else if (op.d.kind == IOS_SEPCONV) {
       need(sep_tile_ok(op, tile), "SEPCONV tile choice out of range or not applicable to this unit");
     } else {
@@ -355,7 +355,8 @@ int ios_schedule_from_stages(ios_graph *g, int32_t n_stages, const int32_t *stag
 // with its convs' shapes varied one conv at a time (all of them together in
 // a merge stage, whose merged conv takes one shape) and with each SEPCONV's
 // tile choice varied, keeping a change only when the stage gets faster
-// by more than kStageTileSlack.  A shape measured alone
+// by more than kStageTileSlack; the split conv shapes after the others, and
+// near ties between the two in whole passes (decide_in_pass).  A shape measured alone
 // fills the GPU by itself; inside a stage other operators share the CUs, so
 // larger tiles can pay off there.
 static constexpr double kStageTileSlack = 0.02;

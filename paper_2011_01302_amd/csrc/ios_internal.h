@@ -195,8 +195,12 @@ constexpr int kSepTiles = kSepLineFirst + kSepLineTiles;
 // the plane size, at least two whole rows in 128 (choice 7) or 64 (choice 8)
 // pixels, and 16 planes of those rows (four at most) and their halo in 6144
 // floats, beside 64 (128) output channels of weights in 128 KB of LDS three
-// times over: the range these choices were given with a tile that staged them
-// so.  Kept as it was, so that a choice is taken or refused as before.
+// times over.  These are the limits of the tile that the choices first named,
+// which staged its operands so; they stay, so that a choice is taken or refused
+// as before.  The split tile's own are sep_split_geometry's (rows of at least
+// four floats, kSepSplitPieces) and the weights' range: where a choice is taken
+// but those do not hold, another tile runs it (sep_tile_runs).  Sums of several
+// inputs and wider rows have not been tried on it.
 inline bool sep_split_ok(int choice, int n_in, int kh, int kw, int ph, int pw, int H, int W, int Ho, int Wo) {
   const int bm = choice == 0 ? 128 : 64, bn = choice == 0 ? 64 : 128;
   if (n_in != 1 || kh != kw || (kh != 3 && kh != 5) || ph != kh / 2 || pw != kw / 2 || Ho != H || Wo != W || Wo < 1)

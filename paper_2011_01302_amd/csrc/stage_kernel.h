@@ -732,20 +732,24 @@ struct SplitRange {
 
 // Implicit-GEMM convolution tile on the bf16 matrix cores, in fp32 accuracy:
 // every operand is split into three bf16 parts (x = x1 + x2 + x3, 24 bits),
-// and the six products x_i w_j with i + j <= 4 are summed in fp32, which
-// leaves out terms below 2^-26 of a product.  v_mfma_f32_32x32x16_bf16 does
+// and the six products x_i w_j with i + j <= 4 are summed in fp32.  That
+// leaves out x2 w3, x3 w2 and x3 w3, below 2^-24 of a product together (|x2|
+// <= 2^-8, |x3| <= 2^-17 of x's power of two; 2^-27.5 in the mean): a single
+// product carries 24 bits where the fp32 matrix core's is exact, and a sum of
+// one term is up to 1.0e-7 off instead of 6e-8.  v_mfma_f32_32x32x16_bf16 does
 // 16 times the multiply-adds per cycle of v_mfma_f32_32x32x2_f32, so a
 // product costs 6/16 of an fp32 one.  x1 w1 has an accumulator of its own, the
 // five small products another (added at the end): the large one is rounded
-// once per 16 channels and tap.  The 2-norm error against 64 bits is below the
-// fp32 tiles' at every size measured (4e-8 .. 3e-7 against 6e-8 .. 8e-7).
+// once per 16 channels and tap, so that from two terms on the 2-norm error
+// against 64 bits is below the fp32 tiles' at every size measured (4e-8 ..
+// 3e-7 against 6e-8 .. 8e-7).
 // 3 x 3, 32 -> 128 channels, 55 x 55, batch 32: 50 us, 142 TFLOP/s (the best
 // fp32 tile 76 us); 5 x 5, 48 -> 64, 35 x 35, batch 16: 30 us (49 us).
 //
 // BM = 32 PB WM output pixels (flattened over the batch) x BN = 32 WN output
 // channels; wave (wm, wn, wk) owns PB blocks of 32 pixels, one of 32 channels
 // and every wk-th k-step (16 channels of one tap).  Per round the workgroup
-// stages sp_sc sub-chunks of 16 channels of the patch of input rows that its
+// stages sc sub-chunks of 16 channels of the patch of input rows that its
 // windows read (SplitGeom): each value is loaded and split once and then read
 // by every tap and every wave, as one 16-byte LDS read per part.  A lane of
 // the staging loads holds 8 channels of one position (8 loads, consecutive
@@ -2441,7 +2445,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(
   stage_body<KV, PERSIST>(table, table_words, a);
 }
 
-// The split variants (KV_SPLIT, KV_SEPSPLIT): two workgroups per CU.
+// The split variants.  One tile per workgroup: KV_SPLIT keeps two workgroups
+// per CU (at most 128 VGPRs); KV_SEPSPLIT, whose tile holds 48 accumulators and
+// both channels' windows, one (about 220).  Persistent launches: one.
 template <int KV, bool PERSIST>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(PERSIST ? 1 : KV == KV_SEPSPLIT ? 2 : 4))) void ios_split_kernel(
     const int4 *__restrict__ table, int table_words, StageArgs a) {
