@@ -31,13 +31,15 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK_FP32_TFLOPS = 157.3          # MI355X dense fp32 MFMA (256 CU x 2.4 GHz x 256 flop/clk)
+PEAK_FP32_TFLOPS = 157.3          # MI355X dense fp32 MFMA (256 CU x 2.4 GHz x 256 flop/clk); split tiles, six bf16
+                                  # products each, have a sixth of dense bf16 (417) for their ceiling
 PEAK_HBM_GBS = 8000.0
 KERNEL_SOURCES = ["paper_2011_01302_amd/csrc/" + f for f in (
     "stage_kernel.h", "stage_kernel_full.hip", "stage_kernel_full_persist.hip", "stage_kernel_sep.hip",
     "stage_kernel_sep_persist.hip", "stage_kernel_seprow.hip", "stage_kernel_seprow_persist.hip",
     "stage_kernel_pipe.hip", "stage_kernel_pipe_persist.hip", "stage_kernel_light.hip",
-    "stage_kernel_light_persist.hip",
+    "stage_kernel_light_persist.hip", "stage_kernel_split.hip", "stage_kernel_split_persist.hip",
+    "stage_kernel_sepsplit.hip", "stage_kernel_sepsplit_persist.hip", "pack.hip",
     "stage_launch.cpp", "exec.cpp", "ios_internal.h")]
 
 
@@ -280,19 +282,25 @@ def write_traffic(args, fetch_dir, write_dir, out_dir=None):
 
 
 def write_mfma(args, d, out_dir=None):
-    """fp32 MFMA work the hardware counted per stage launch of the timed loop
-    (rocprofv3 --pmc SQ_INSTS_VALU_MFMA_MOPS_F32 SQ_INSTS_VALU_MFMA_F32: add
-    and mul ops / 512, and MFMA instructions) against the stages' algorithmic
-    MFMA flops (2 x MAC of the convolutions as defined).  The excess is the
-    padding the kernel multiplies by zero: output channels to multiples of 16,
-    input channels to multiples of 4 and the reduction to multiples of 16,
-    pixel rows of the last M-tile, and the zero taps of merged kernels.
-    Products of split tiles run on bf16 and are not in these counters."""
+    """MFMA work the hardware counted per stage launch of the timed loop
+    (rocprofv3 --pmc SQ_INSTS_VALU_MFMA_MOPS_F32 SQ_INSTS_VALU_MFMA_F32
+    SQ_INSTS_VALU_MFMA_MOPS_BF16 SQ_INSTS_VALU_MFMA_BF16: add and mul ops / 512,
+    and MFMA instructions) against the stages' algorithmic MFMA flops (2 x MAC
+    of the convolutions as defined).  A split tile takes six bf16 products for
+    one of these, so bf16 ops count a sixth.  The excess is the padding the
+    kernel multiplies by zero: output channels to multiples of 16 (split tiles:
+    32), input channels to multiples of 4 (16) and the reduction to multiples of
+    16, pixel rows of the last M-tile, and the zero taps of merged kernels."""
     import workloads as W
     meta = json.load(open(os.path.join(d, "bench.json")))
     ns, steps = meta["stages"], meta["steps"]
-    mops = [v for _, k, v in _pmc_rows(d, "SQ_INSTS_VALU_MFMA_MOPS_F32") if _is_stage(k)][-steps * ns:]
-    inst = [v for _, k, v in _pmc_rows(d, "SQ_INSTS_VALU_MFMA_F32") if _is_stage(k)][-steps * ns:]
+
+    def counter(name):
+        return [v for _, k, v in _pmc_rows(d, name) if _is_stage(k)][-steps * ns:] or [0.0] * (steps * ns)
+
+    ops32, ops16 = counter("SQ_INSTS_VALU_MFMA_MOPS_F32"), counter("SQ_INSTS_VALU_MFMA_MOPS_BF16")
+    mops = [a + b / 6 for a, b in zip(ops32, ops16)]
+    inst = [a + b for a, b in zip(counter("SQ_INSTS_VALU_MFMA_F32"), counter("SQ_INSTS_VALU_MFMA_BF16"))]
     spec, _ = W.make(args.config, args.batch, args.seed)
     work = unit_work(spec, args.batch)
     rows = []
@@ -302,6 +310,7 @@ def write_mfma(args, d, out_dir=None):
         counted = statistics.mean(mops[k::ns]) * 512
         rows.append({"units": units, "strategy": meta["schedule"][k]["strategy"],
                      "algorithmic_flop": alg, "counted_flop": counted,
+                     "counted_bf16_ops": statistics.mean(ops16[k::ns]) * 512,
                      "mfma_instructions": statistics.mean(inst[k::ns]),
                      "counted_over_algorithmic": round(counted / alg, 4) if alg else None})
     out = {"workload": f"{args.config}_bs{args.batch}", "kernel_sha": kernel_sha(), "per_stage": rows,
@@ -890,7 +899,7 @@ def main():
                     help="turn two rocprofv3 --pmc MeanOccupancyPerCU GRBM_GUI_ACTIVE runs (IOS "
                          "schedule, --mode sequential) into profiles/occupancy_<workload>.json and exit")
     ap.add_argument("--mfma-from", default="", metavar="PMC_DIR",
-                    help="turn a rocprofv3 --pmc SQ_INSTS_VALU_MFMA_MOPS_F32 SQ_INSTS_VALU_MFMA_F32 run "
+                    help="turn a rocprofv3 --pmc run (the MFMA counters of fp32 and bf16, see write_mfma) "
                          "into profiles/mfma_<workload>.json and exit")
     ap.add_argument("--traffic-from", nargs=2, metavar=("FETCH_DIR", "WRITE_DIR"),
                     help="turn two rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE) of this benchmark "

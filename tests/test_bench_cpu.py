@@ -127,6 +127,22 @@ def test_write_mfma_compares_with_the_algorithmic_flops(tmp_path):
     assert out["per_stage"][1]["mfma_instructions"] == pytest.approx(alg["B2"] / 2048)
 
 
+def test_write_mfma_counts_split_tiles(tmp_path):
+    """Six bf16 products stand for one: a stage on split tiles, one on both."""
+    alg = {"A": 2 * 64 * 16 * 16, "B1": 2 * 64 * 8 * 16, "B2": 2 * 64 * 16 * 72}
+    sched = [{"units": ["A", "B1"], "strategy": "concurrent"}, {"units": ["B2"], "strategy": "concurrent"}]
+    rows = [(STAGE.replace("ios_stage_kernel", "ios_split_kernel"),
+             {"SQ_INSTS_VALU_MFMA_MOPS_F32": f / 512, "SQ_INSTS_VALU_MFMA_F32": 1,
+              "SQ_INSTS_VALU_MFMA_MOPS_BF16": 6 * h / 512, "SQ_INSTS_VALU_MFMA_BF16": 2}, 4, 0, 1)
+            for _ in range(3) for f, h in ((alg["A"], alg["B1"]), (0, 2 * alg["B2"]))]
+    d = counter_dir(tmp_path, "mfma", rows, {"steps": 3, "stages": 2, "schedule": sched})
+    bench.write_mfma(args(), d, out_dir=str(tmp_path))
+    out = json.load(open(tmp_path / "mfma_tiny_bs1.json"))["per_stage"]
+    assert [p["counted_over_algorithmic"] for p in out] == [1.0, 2.0]
+    assert [p["counted_bf16_ops"] for p in out] == [6 * alg["B1"], 12 * alg["B2"]]
+    assert [p["mfma_instructions"] for p in out] == [3, 3]
+
+
 def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, os.path.join(bench.ROOT, "bench.py"), "--gpus", "2"],
                        capture_output=True, text=True, timeout=120)
