@@ -947,6 +947,11 @@ __device__ __forceinline__ void conv_split_tile(const Slots &sl, const DevOp &op
   };
   rounds(std::false_type{});
   if (__builtin_amdgcn_readfirstlane((int)*flags)) rounds(std::true_type{});
+  // The last k-step's weights in flight, which nothing reads: while they are,
+  // the epilogue's reuse of their registers waits for every store before it,
+  // one by one (an Inception block at batch 16 in one chained stage 161 us
+  // instead of 149).
+  wait_vmcnt<0>();
   float *red = lds;                                   // [wk][block][16][64]
   const int nblk = (PB << lwm) << lwn;
   if (WK > 1) {
