@@ -501,7 +501,7 @@ int ios_schedule_tune_tiles(ios_graph *g, ios_schedule_t *q, const ios_sched_opt
           else set_choice(g, ops, plain);
           improved = has_split() && tune_xcd_order();
           improved |= vary(TC_S256x64, TC_COUNT - 1);
-          if (improved && has_split()) vary(0, TC_COUNT - 1);
+          if (improved && has_split()) vary(TC_S256x64, TC_COUNT - 1);
           if (has_split() && (double)plain_ns <= (double)best * kNearTie)
             ties.push_back({(int)k, plain, choice_of(g, ops), plain_ns, best});
         }

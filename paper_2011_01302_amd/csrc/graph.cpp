@@ -591,9 +591,10 @@ void ensure_device(ios_graph *g) {
       for (auto &m : quick)
         if (!tile_is_split(m.second)) fastest_fp32 = std::min(fastest_fp32, m.first);
       for (auto &m : quick) {
-        if ((double)m.first > (double)fastest * kTuneScreen && (tile_is_split(m.second) || m.first > fastest_fp32)) continue;
+        const bool near = (double)m.first <= (double)fastest * kTuneScreen;
+        if (!near && (tile_is_split(m.second) || m.first > fastest_fp32)) continue;
         op.tcfg = m.second;
-        meas.push_back({profile_stage(g, {oi}, IOS_CONCURRENT, 3, 20, 5), m.second});
+        meas.push_back({profile_stage(g, {oi}, IOS_CONCURRENT, 3, near ? 20 : 5, near ? 5 : 1), m.second});
       }
       auto tiles = [&](int cfg) {
         return ((M + tile_bm(cfg) - 1) / tile_bm(cfg)) * ((op.d.cout + tile_bn(cfg) - 1) / tile_bn(cfg));
